@@ -125,12 +125,16 @@ const char* sw_last_error(sw_handle* h);
  *               from device memory, so one graph serves every batch with the
  *               same buffers and at most that many pairs
  *   "colpath"   1 = pairs whose scheme has at most 4 residues (and whose
- *               scores plus gap_open fit a byte) read their substitution
- *               scores from per-column words instead of table lookups
- *               (default 1; 0 = always table lookups)
+ *               scores plus gap_open and gap_extend fit a byte) read their
+ *               substitution scores from per-column words instead of table
+ *               lookups (default 1; 0 = always table lookups).  Schemes of
+ *               one call share the gap_extend of the first such scheme;
+ *               others, and gap costs too large for the drifted sweeps
+ *               (gap_open + 42 gap_extend > 1024), take table lookups
  *   "pairtable" 1 = when exactly one scheme of a call takes table lookups
- *               (alphabet of at most 24 residues, scores plus gap_open a
- *               byte, gap_open <= 1024), its packed int16 pairs read two
+ *               (alphabet of at most 24 residues, scores plus gap_open
+ *               and gap_extend a byte, gap_open + 42 gap_extend <= 1024),
+ *               its packed int16 pairs read two
  *               rows' scores per load from a pair table (default 1);
  *               0 = byte-table lookups.  Read-only "pairtable_used": whether
  *               the last finished call used it

@@ -77,19 +77,16 @@ __device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S,
             rawB[r] = *pB;
         }
         const int AA = S.alphabet[JA.sid], AB = S.alphabet[JB.sid];
-        bool bad = false;
+        int bad = -1;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int i = l * R + r;
-            const bool inA = i < JA.n, inB = i < JB.n;
-            bad |= (inA && rawA[r] >= AA) || (inB && rawB[r] >= AB);
-            const uint32_t a = (inA && rawA[r] < AA) ? rawA[r] : kPad;
-            const uint32_t b = (inB && rawB[r] < AB) ? rawB[r] : kPad;
+            const uint32_t a = checked(rawA[r], l * R + r < JA.n, AA, kPad, bad);
+            const uint32_t b = checked(rawB[r], l * R + r < JB.n, AB, kPad, bad);
             apk[r] = a | (b << 16);
         }
         stA.store(bufA, JA, AA, 0, l, bad);
         stB.store(bufB, JB, AB, 0, l, bad);
-        if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
+        set_flag(P.flags, kFlagBadResidue, (bad >= 0) & (P.validate != 0));
     }
     if (wave == 0) {
         // "previous step" values of every wave's last lane: the matrix's
@@ -121,7 +118,7 @@ __device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S,
 #pragma unroll
         for (int r = 0; r < R; ++r) sc[r] = load_scores(S.mat, a0 + (int)(apk[r] & 0xFFFF), b0 + (int)(apk[r] >> 16));
     }
-    bool bad = false;
+    int bad = -1;
     uint32_t jc = (uint32_t)(kColMax + l);
     int parity = 0;
     for (int t0 = 0; t0 < steps; t0 += kChunk) {
@@ -192,7 +189,7 @@ __device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S,
                 sc[r] = load_scores(S.mat, a0 + (int)(apk[r] & 0xFFFF), b0 + (int)(apk[r] >> 16));
         }
     }
-    if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
+    set_flag(P.flags, kFlagBadResidue, (bad >= 0) & (P.validate != 0));
 
     // best of this lane in row-major order, then of the wave, then across
     // waves (lower waves hold lower rows)
@@ -240,7 +237,7 @@ __device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S,
                 P.out[pair] = res;
             } else if (J.fwd_score > 0) {
                 if (b != J.fwd_score) {
-                    atomicOr(&P.flags[kFlagReverseMismatch], 1);
+                    if (tid == 0) push_redo(P, pair);
                 } else {
                     P.out[pair].q_start = J.fwd_qe - bi;
                     P.out[pair].r_start = J.fwd_re - bj;
@@ -258,7 +255,6 @@ __global__ __launch_bounds__(kBlock) void sw_coop_kernel(KParams P) {
     __shared__ __attribute__((aligned(16))) SchemeLds L;
     __shared__ __attribute__((aligned(16))) CoopLds C;
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lo = __atomic_load_n(&P.meta[P.lo_idx], __ATOMIC_RELAXED);
     int hi = __atomic_load_n(&P.meta[P.hi_idx], __ATOMIC_RELAXED);
@@ -273,11 +269,9 @@ __global__ __launch_bounds__(kBlock) void sw_coop_kernel(KParams P) {
     load_schemes(L, P, tid);
     __syncthreads();
     for (;;) {
-        // wave 0 claims the next item (every lane takes part in the atomic,
-        // only lane 0 adds); every lane of wave 0 writes the same value
+        // wave 0 claims the next item; every lane of it writes the same value
         if (wave == 0) {
-            const int mine = atomicAdd(&P.meta[P.head_idx], lane == 0 ? 1 : 0);
-            C.item = __builtin_amdgcn_readlane(mine, 0);
+            C.item = next_item(&P.meta[P.head_idx]);
         }
         __syncthreads();
         const int it = __builtin_amdgcn_readfirstlane(C.item);

@@ -124,6 +124,45 @@ __device__ __forceinline__ PairJob load_job(const KParams& P, int pair, int reve
     return J;
 }
 
+// Sets an error flag from any lanes (a plain store: every writer stores 1).
+// No lane-divergent branch: see opaque_lane.
+__device__ __forceinline__ void set_flag(int32_t* flags, int which, bool raise) {
+    if (__builtin_amdgcn_ballot_w64(raise) != 0)
+        __hip_atomic_store(&flags[which], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The lane index as a value the compiler cannot carry over from one work item
+// to the next.  Everything a sweep derives from it is then computed per item:
+// kept across items those values fill registers that the sweep needs, and
+// this compiler has moved such values between registers inside a
+// lane-divergent branch, where the lanes outside it lose them.  For the same
+// reason the sweeps keep lane-divergent branches out of their code where
+// registers are short.
+__device__ __forceinline__ int opaque_lane(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// Claims the next item of a queue: lane 0 adds 1 to its head and every lane
+// gets the head's old value.  Written as one block with the execution mask
+// set inside it: a lane-0 branch in the queue loop was once lowered into an
+// inner loop that re-entered without the fetch, and an atomic of all lanes
+// that adds 1 in lane 0 only became a loop over the 64 lanes.
+__device__ __forceinline__ int next_item(int32_t* head) {
+    int old;
+    uint64_t saved;
+    asm volatile(
+        "s_mov_b64 %1, exec\n\t"
+        "s_mov_b64 exec, 1\n\t"
+        "global_atomic_add %0, %2, %3, off sc0\n\t"
+        "s_waitcnt vmcnt(0)\n\t"
+        "s_mov_b64 exec, %1"
+        : "=&v"(old), "=&s"(saved)
+        : "v"(head), "v"(1)
+        : "memory");
+    return __builtin_amdgcn_readfirstlane(old);
+}
+
 // Wave-scope ordering of LDS traffic: every lane's earlier LDS accesses are
 // complete and visible before any lane's later ones (the wavefront executes
 // in lock-step, so no workgroup barrier is needed).
@@ -140,6 +179,14 @@ __device__ __forceinline__ void wave_lds_sync() {
 // column t0-W+x.  Each lane prefetches kPerLane entries of the next chunk
 // into registers, so a narrower tile costs fewer registers and more chunk
 // boundaries.  (kChunk and kChunkNarrow are in sw_internal.h.)
+
+// A residue code of an alphabet of A, or `pad` outside the sequence and for
+// an invalid code; `bad` becomes >= 0 when one inside it is invalid.
+__device__ __forceinline__ int checked(int raw, bool inside, int A, int pad, int& bad) {
+    const int x = inside ? raw : -1;
+    bad = imax(bad, x - A);
+    return (unsigned)x < (unsigned)A ? x : pad;
+}
 
 template <int W, int C = kChunk>
 struct RefStager {
@@ -164,58 +211,49 @@ struct RefStager {
     // Write the chunk into the group's LDS buffer as matrix row offsets,
     // replacing out-of-range columns and invalid residues by the padding code.
     __device__ __forceinline__ void store(uint16_t* buf, const PairJob& J, int A, int t0, int l,
-                                          bool& bad) const {
+                                          int& bad) const {
         const int sbase = J.sid * kMatBytes;
 #pragma unroll
         for (int k = 0; k < kPerLane; ++k) {
             const int j = t0 - W + l + k * W;
-            int b = raw[k];
-            const bool inside = j >= 0 && j < J.m;
-            bad |= inside && b >= A;
-            b = (inside && b < A) ? b : kPad;
+            const int b = checked(raw[k], (unsigned)j < (unsigned)J.m, A, kPad, bad);
             buf[l + k * W] = (uint16_t)(sbase + b * kMatDim);
         }
     }
     // Pair-table path: write the chunk as byte offsets 2 b of the reference
     // residues into a pair-table row; out-of-range columns and invalid
-    // residues get the padding code D - 1 (whose entries are 0, a score of -o).
+    // residues get the padding code D - 1 (whose entries are 0, a score of -(o + e)).
     __device__ __forceinline__ void store_ptab(uint16_t* buf, const PairJob& J, int A, int D, int t0, int l,
-                                               bool& bad) const {
+                                               int& bad) const {
 #pragma unroll
         for (int k = 0; k < kPerLane; ++k) {
             const int j = t0 - W + l + k * W;
-            const int b = raw[k];
-            const bool inside = j >= 0 && j < J.m;
-            bad |= inside && b >= A;
-            buf[l + k * W] = (uint16_t)(2 * ((inside && b < A) ? b : D - 1));
+            const int b = checked(raw[k], (unsigned)j < (unsigned)J.m, A, D - 1, bad);
+            buf[l + k * W] = (uint16_t)(2 * b);
         }
     }
     // Query-profile path: write the chunk as byte offsets b * row_bytes of
     // the reference residues' profile rows; out-of-range columns and invalid
-    // residues get the padding code D - 1 (a row of zeros, a score of -o).
+    // residues get the padding code D - 1 (a row of zeros, a score of -(o + e)).
     __device__ __forceinline__ void store_qprof(uint16_t* buf, const PairJob& J, int A, int D, int row_bytes, int t0,
-                                                int l, bool& bad) const {
+                                                int l, int& bad) const {
 #pragma unroll
         for (int k = 0; k < kPerLane; ++k) {
             const int j = t0 - W + l + k * W;
-            const int b = raw[k];
-            const bool inside = j >= 0 && j < J.m;
-            bad |= inside && b >= A;
-            buf[l + k * W] = (uint16_t)(row_bytes * ((inside && b < A) ? b : D - 1));
+            const int b = checked(raw[k], (unsigned)j < (unsigned)J.m, A, D - 1, bad);
+            buf[l + k * W] = (uint16_t)(row_bytes * b);
         }
     }
     // Small-alphabet path: write the chunk as column words (bytes M[a][b] + o
-    // for a = 0..3); out-of-range columns and invalid residues get word 0,
-    // i.e. a score of -o for every row.
+    // for a = 0..3); out-of-range columns and invalid residues get word 0
+    // (the word of residue kPad, which no small alphabet holds).
     __device__ __forceinline__ void store_col(uint32_t* buf, const PairJob& J, int A, const uint32_t* colw,
-                                              int t0, int l, bool& bad) const {
+                                              int t0, int l, int& bad) const {
 #pragma unroll
         for (int k = 0; k < kPerLane; ++k) {
             const int j = t0 - W + l + k * W;
-            const int b = raw[k];
-            const bool inside = j >= 0 && j < J.m;
-            bad |= inside && b >= A;
-            buf[l + k * W] = (inside && b < A) ? colw[b] : 0u;
+            const int b = checked(raw[k], (unsigned)j < (unsigned)J.m, A, kPad, bad);
+            buf[l + k * W] = colw[b];
         }
     }
 };
@@ -235,6 +273,7 @@ struct SchemeLds {
 // P.ptab_sid (D^3 16-bit entries) and the gap costs of every scheme.
 struct PtabLds {
     uint16_t tab[kPtabBytes / 2];
+    uint8_t row_max[kMatDim];   // the scheme's best score of each query residue (0 for padding rows)
     int32_t alphabet[SW_MAX_SCHEMES];
     int32_t gap_open[SW_MAX_SCHEMES];
     int32_t gap_extend[SW_MAX_SCHEMES];
@@ -245,6 +284,7 @@ __device__ __forceinline__ void load_ptab(PtabLds& S, const KParams& P, int tid)
     const int words = (D > 0 && D <= kPtabMaxDim) ? (D * D * D + 1) / 2 : 0;
     const uint32_t* src = reinterpret_cast<const uint32_t*>(P.mats + kPtabOffset);
     for (int k = tid; k < words; k += kBlock) reinterpret_cast<uint32_t*>(S.tab)[k] = src[k];
+    if (tid < kMatDim) S.row_max[tid] = reinterpret_cast<const uint8_t*>(P.mats + kRowMaxOffset)[tid];
     if (tid < SW_MAX_SCHEMES) {
         S.alphabet[tid] = P.alphabet[tid];
         S.gap_open[tid] = P.gap_open[tid];

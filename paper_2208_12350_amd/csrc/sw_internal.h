@@ -15,18 +15,21 @@ constexpr int kPad = 31;
 constexpr int kMatDim = 32;                    // LDS matrix is 32 x 32 int8
 constexpr int kMatBytes = kMatDim * kMatDim;   // per scheme
 // After the matrices, per scheme and reference residue b: the column word
-// of the small-alphabet path, bytes M[a][b] + o for a = 0..3 (see sw_sweep.h).
+// of the small-alphabet path, bytes M[a][b] + o + e for a = 0..3 (see sw_sweep.h).
 constexpr int kColWordsBytes = SW_MAX_SCHEMES * kMatDim * 4;
 // Then the pair table of one scheme (the "pair-table" sweep, sw_sweep.h):
 // for residues x, y of two consecutive query rows and reference residue b,
-// the 16-bit entry [(x * D + y) * D + b] holds the bytes M[x][b] + o (low)
-// and M[y][b] + o (high), where D = alphabet + 1 and code D - 1 (= alphabet)
+// the 16-bit entry [(x * D + y) * D + b] holds the bytes M[x][b] + o + e (low)
+// and M[y][b] + o + e (high), where D = alphabet + 1 and code D - 1 (= alphabet)
 // pads rows past the query end and columns outside the reference: its
-// bytes are 0, a score of -o.
+// bytes are 0, a score of -(o + e).
 constexpr int kPtabMaxDim = 25;                          // alphabets of up to 24 residues
 constexpr int kPtabBytes = (kPtabMaxDim * kPtabMaxDim * kPtabMaxDim * 2 + 15) / 16 * 16;
 constexpr int kPtabOffset = SW_MAX_SCHEMES * kMatBytes + kColWordsBytes;
-constexpr int kSchemeBytes = kPtabOffset + kPtabBytes;
+// Then, for the pair table's scheme, the best score of each query residue
+// (bytes; at least 0).
+constexpr int kRowMaxOffset = kPtabOffset + kPtabBytes;
+constexpr int kSchemeBytes = kRowMaxOffset + kMatDim;
 constexpr int kBlock = 256;                    // 4 wavefronts per workgroup
 // Reference tile of the sweeps, in steps: kChunk by default; the 16- and
 // 32-lane packed shapes are also compiled for kChunkNarrow (fewer prefetch
@@ -99,7 +102,8 @@ enum : int {
     kMetaHeads = kMetaItemSplit + kMaxBins,           // [kMaxBins] queue head of each bin's table-lookup items
     kMetaColHeads = kMetaHeads + kMaxBins,            // [kMaxBins] and of its column-word items
     kMetaBinCol = kMetaColHeads + kMaxBins,           // [kMaxBins] column-path pairs of each bin
-    kMetaSize = kMetaBinCol + kMaxBins,
+    kMetaRedo = kMetaBinCol + kMaxBins,               // pairs on the redo list (reverse pass)
+    kMetaSize = kMetaRedo + 1,
 };
 
 // Layout of the 64-bit statistics counters of a call (cleared at its start).
@@ -149,6 +153,14 @@ struct KParams {
     int32_t qprof;               // 1: the forward pass may use the query profile of queries[0 .. qprof_n)
     int32_t qprof_n;
     int8_t fam_bins[kFamilyMax];   // family launch: member k's bin, or -1 (not launched)
+    // Drifted sweeps (sw_sweep.h), [0] column words, [1] pair table and query
+    // profile: the gap extension cost of their schemes, the steps between
+    // renormalisations, one of their schemes (for empty lane groups).
+    int32_t drift_e[2];
+    int32_t drift_period[2];
+    int32_t drift_sid[2];
+    int32_t drift_x[2];          // the largest o - e of their schemes
+    int32_t* redo;               // redo list of the reverse pass (meta[kMetaRedo] pairs; room for n_pairs)
 };
 
 enum : int32_t {
@@ -173,6 +185,16 @@ constexpr int kI16MaxRef = 32000;
 // pair with query length n, where sel = 0 for the packed int16 path and 1
 // for int32; a pair takes int16 when min(n, m) * max_score[s] <= i16_limit.
 constexpr int kLutRows = SW_MAX_QUERY / 16;
+
+// Drifted sweeps: the steps between renormalisations of a scheme with gap
+// costs o and e, or 0 when it cannot take them.  The drift of a period plus
+// a lane's rows, e (R + period + 1), and the values o + e below zero must
+// fit in the bias: o + e (32 + period + 2) <= kI16Bias.
+inline int drift_period(int o, int e) {
+    for (int period : {128, 64, 32, 16, 8})
+        if ((int64_t)o + (int64_t)e * (32 + period + 2) <= kI16Bias) return period;
+    return 0;
+}
 struct ClassifyArgs {
     int32_t max_score[SW_MAX_SCHEMES];
     int32_t col_ok[SW_MAX_SCHEMES];
@@ -211,6 +233,9 @@ const FamilyEntry* shape_family(int prec, int W, int R);
 const ShapeDesc* compiled_shapes(int* n);
 
 hipError_t launch_reset(int32_t* p, int n, hipStream_t s);
+// Pairs on the redo list, after the reverse sweeps (sw_queue_redo.hip).
+hipError_t launch_redo(const KParams& P, const int8_t* lut, const BinInfo* bins, unsigned long long* counters,
+                       int blocks, hipStream_t s);
 // Start of an alignment call: small[0..n_small) = 0 (flags and counters) and
 // *n_dev = n_pairs.
 hipError_t launch_call_start(int32_t* small, int n_small, int32_t* n_dev, int32_t n_pairs, hipStream_t s);

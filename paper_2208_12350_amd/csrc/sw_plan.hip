@@ -202,6 +202,7 @@ __global__ __launch_bounds__(kPlanThreads) void sw_plan_kernel(const BinInfo* bi
         meta[kMetaHeads + t] = 0;
         meta[kMetaColHeads + t] = 0;
     }
+    if (t == 0) meta[kMetaRedo] = 0;
     __syncthreads();
     int32_t my_items = 0, my_col_items = 0;
     if (t < n_bins && t < kMaxBins) {
@@ -296,6 +297,7 @@ __global__ __launch_bounds__(kBinScanThreads) void sw_plan_bins_kernel(const Bin
         meta[kMetaBinFirst + kMaxBins] = pos;
         meta[kMetaItemFirst + kMaxBins] = items;
         hist[kTrivialKey] = pos;
+        meta[kMetaRedo] = 0;
     }
     if (t < kMaxBins) {
         meta[kMetaHeads + t] = 0;

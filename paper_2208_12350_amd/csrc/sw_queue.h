@@ -24,19 +24,13 @@
 namespace sw {
 
 // The work-queue loop of one wavefront: claim items of the launch's range
-// and sweep each with `sweep(first, count)`.
+// and sweep each with `sweep(first, count, lane)`.
 template <int kPPW, class Sweep>
 __device__ __forceinline__ void queue_loop(const KParams& P, int lane, int lo, int hi, int n_pairs, Sweep&& sweep,
                                            int head_idx = -1) {
     if (head_idx < 0) head_idx = P.head_idx;
-    // The loop has no lane-divergent branch: every lane takes part in the
-    // fetch (only lane 0 adds 1, so each wavefront claims exactly one item
-    // whether or not the lanes' atomics are merged), and the item index is
-    // lane 0's return value.  A lane-0-only atomic inside this loop was
-    // lowered into an inner loop that re-entered without the fetch.
     for (;;) {
-        const int mine = atomicAdd(&P.meta[head_idx], lane == 0 ? 1 : 0);
-        const int it = __builtin_amdgcn_readlane(mine, 0);
+        const int it = next_item(&P.meta[head_idx]);
         if (it >= hi - lo) break;
         const WorkItem* wp = P.items + lo + it;
         const int first = __builtin_amdgcn_readfirstlane(__atomic_load_n(&wp->first, __ATOMIC_RELAXED));
@@ -44,7 +38,7 @@ __device__ __forceinline__ void queue_loop(const KParams& P, int lane, int lo, i
         const bool valid = first >= 0 && count >= 1 && count <= kPPW && first + count <= n_pairs;
         if (valid) {
             wave_lds_sync();
-            sweep(first, count);
+            sweep(first, count, opaque_lane(lane));
         } else {
             atomicOr(&P.flags[kFlagInternal], 1);
         }
@@ -74,16 +68,16 @@ __device__ __forceinline__ void queue_body(const KParams& P, SchemeLds& L, uint1
     constexpr int kPPW = (64 / W) * (PREC == 16 ? 2 : 1);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lo, hi;
     if (!launch_range(P, tid, lo, hi)) return;
     const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
     load_schemes(L, P, tid);
     __syncthreads();
     uint16_t* wbuf = wbufs + wave * kWaveBuf;
-    queue_loop<kPPW>(P, lane, lo, hi, n_pairs, [&](int first, int count) {
+    queue_loop<kPPW>(P, lane, lo, hi, n_pairs, [&](int first, int count, int lane) {
         if constexpr (COL)
-            sweep_i16_col<W, R, REV, C>(P, L, wbuf, first, count, lane);
+            sweep_drift<ColScores<W, R, C>, W, R, REV, C>(P, L, wbuf, first, count, lane);
         else if constexpr (PREC == 16)
             sweep_i16<W, R, REV, C>(P, L, wbuf, first, count, lane);
         else
@@ -96,7 +90,7 @@ __device__ __forceinline__ void ptab_body(const KParams& P, PtabLds& L, uint16_t
     constexpr int kPPW = (64 / W) * 2;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lo, hi;
     if (!launch_range(P, tid, lo, hi)) return;
     if (P.ptab_sid < 0 || P.ptab_sid >= SW_MAX_SCHEMES || P.ptab_dim < 2 || P.ptab_dim > kPtabMaxDim) {
@@ -107,8 +101,8 @@ __device__ __forceinline__ void ptab_body(const KParams& P, PtabLds& L, uint16_t
     load_ptab(L, P, tid);
     __syncthreads();
     uint16_t* wbuf = wbufs + wave * kWaveBuf;
-    queue_loop<kPPW>(P, lane, lo, hi, n_pairs, [&](int first, int count) {
-        sweep_i16_ptab<W, R, REV, C>(P, L, wbuf, first, count, lane);
+    queue_loop<kPPW>(P, lane, lo, hi, n_pairs, [&](int first, int count, int lane) {
+        sweep_drift<PtabScores<W, R, C>, W, R, REV, C>(P, L, wbuf, first, count, lane);
     });
 }
 
@@ -129,7 +123,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     queue_body<PREC, W, R, REV, COL, C>(P, L, wbufs);
 }
 
-// Packed int16 shapes with the pair table of one scheme (sweep_i16_ptab).
+// Packed int16 shapes with the pair table of one scheme (PtabScores).
 template <int W, int R, bool REV>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void sw_ptab_kernel(KParams P) {
     __shared__ __attribute__((aligned(16))) PtabLds L;
@@ -145,20 +139,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 }
 
 // Forward sweep of a database search with the query profile
-// (sweep_i16_qprof): every pair of the launch aligns queries[0 ..
+// (QprofScores): every pair of the launch aligns queries[0 ..
 // P.qprof_n) with scheme P.ptab_sid.  The workgroup builds the profile of
 // its lanes' rows in LDS before it takes items.
 template <int W, int R>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void sw_qprof_kernel(KParams P) {
-    constexpr int RD = (R + 3) / 4;
-    constexpr int kRowBytes = W * RD * 4;
+    constexpr int RD = QprofLds<W, R>::RD;
+    constexpr int kRowBytes = QprofLds<W, R>::kRowBytes;
     constexpr int kPPW = (64 / W) * 2;
-    __shared__ __attribute__((aligned(16))) uint8_t prof[kPtabMaxDim * kRowBytes];
-    __shared__ int32_t gopen[SW_MAX_SCHEMES], gext[SW_MAX_SCHEMES];
+    __shared__ __attribute__((aligned(16))) QprofLds<W, R> L;
     __shared__ uint16_t wbufs[kWavesPerBlock * kWaveBuf];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lo, hi;
     if (!launch_range(P, tid, lo, hi)) return;
     const int D = P.ptab_dim, sid = P.ptab_sid, n = P.qprof_n;
@@ -167,7 +160,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
         return;
     }
     const int A = D - 1;
-    const int o = P.gap_open[sid];
+    const int bias = P.gap_open[sid] + P.gap_extend[sid];
     const int8_t* mat = P.mats + sid * kMatBytes;   // [b][a] = M[a][b]
     bool bad = false;
     for (int idx = tid; idx < D * kRowBytes; idx += kBlock) {
@@ -178,20 +171,28 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
         if (b < A && r < R && i < n) {
             const int a = P.queries[i];
             bad |= a >= A;
-            v = a < A ? mat[b * kMatDim + a] + o : 0;
+            v = a < A ? mat[b * kMatDim + a] + bias : 0;
         }
-        prof[idx] = (uint8_t)v;
+        L.prof[idx] = (uint8_t)v;
     }
     if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
-    if (tid < SW_MAX_SCHEMES) {
-        gopen[tid] = P.gap_open[tid];
-        gext[tid] = P.gap_extend[tid];
+    if (tid < SW_MAX_SCHEMES) L.gap_open[tid] = P.gap_open[tid];
+    if (tid == 0) L.bound = 0;
+    __syncthreads();
+    {
+        int sum = 0;
+        const uint8_t* row_max = reinterpret_cast<const uint8_t*>(P.mats + kRowMaxOffset);
+        for (int i = tid; i < n; i += kBlock) {
+            const int a = P.queries[i];
+            sum += a < A ? row_max[a] : 0;
+        }
+        atomicAdd(&L.bound, sum);
     }
     const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
     __syncthreads();
     uint16_t* wbuf = wbufs + wave * kWaveBuf;
-    queue_loop<kPPW>(P, lane, lo, hi, n_pairs, [&](int first, int count) {
-        sweep_i16_qprof<W, R>(P, gopen, gext, prof, wbuf, first, count, lane);
+    queue_loop<kPPW>(P, lane, lo, hi, n_pairs, [&](int first, int count, int lane) {
+        sweep_drift<QprofScores<W, R, kChunk>, W, R, false, kChunk>(P, L, wbuf, first, count, lane);
     });
 }
 
@@ -219,11 +220,11 @@ __device__ __forceinline__ void family_member(const KParams& P, Lds& L, uint16_t
         atomicOr(&P.flags[kFlagInternal], 1);
         return;
     }
-    queue_loop<kPPW>(P, lane, lo, hi, n_pairs, [&](int first, int count) {
+    queue_loop<kPPW>(P, lane, lo, hi, n_pairs, [&](int first, int count, int lane) {
         if constexpr (VAR == kVarPtab)
-            sweep_i16_ptab<W, R, REV, C>(P, L, wbuf, first, count, lane);
+            sweep_drift<PtabScores<W, R, C>, W, R, REV, C>(P, L, wbuf, first, count, lane);
         else if constexpr (VAR == kVarCol)
-            sweep_i16_col<W, R, REV, C>(P, L, wbuf, first, count, lane);
+            sweep_drift<ColScores<W, R, C>, W, R, REV, C>(P, L, wbuf, first, count, lane);
         else if constexpr (PREC == 16)
             sweep_i16<W, R, REV, C>(P, L, wbuf, first, count, lane);
         else
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
     using Lds = typename std::conditional<VAR == kVarPtab, PtabLds, SchemeLds>::type;
     __shared__ __attribute__((aligned(16))) Lds L;
     __shared__ uint16_t wbufs[kWavesPerBlock * kWaveBuf];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if constexpr (VAR == kVarPtab) {
         if (P.ptab_sid < 0 || P.ptab_sid >= SW_MAX_SCHEMES || P.ptab_dim < 2 || P.ptab_dim > kPtabMaxDim) {
             if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);

@@ -220,6 +220,7 @@ struct sw_handle {
     static constexpr int kTraceFams = 8; // box-sweep family launches per chunk at most
     hipEvent_t tfam_ev[kTraceFams] = {}; // end of a box-sweep family launch, for its walks on other streams
     int32_t last_col_ok[SW_MAX_SCHEMES] = {0};   // column-word eligibility of the last score call's schemes
+    int32_t last_drift_e[2] = {0, 0}, last_drift_period[2] = {kChunk, kChunk}, last_drift_sid[2] = {0, 0};
     BinInfo* d_tbins = nullptr;
     int8_t* d_tlut = nullptr;            // [2 * kLutRows] path-sweep bin per (precision, 16-row bucket of box rows)
     int64_t* d_rec_off = nullptr;        // [trace_cap + 1]
@@ -652,6 +653,9 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
             }
         }
     }
+    // pairs whose drifted forward sweep left the end column open
+    if (pass == 1 && K.redo)
+        HIP_TRY(h, launch_redo(K, h->d_lut, h->d_bins, counters(h->d_small), 2 * std::max(1, h->n_cu), stream));
     if (timing) HIP_TRY(h, hipEventRecord(h->ev[pass == 0 ? 2 : 4], stream));
     return SW_OK;
 }
@@ -1149,6 +1153,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
 
     // substitution tables: [s][b][a] = M_s[a][b]; padding rows/columns score -1
     ClassifyArgs C;
+    int col_sid = -1, col_period = 0, col_x = 0;   // first column-word scheme; renormalisation period of them all
     h->tables.assign(kSchemeBytes, 0);
     for (int s = 0; s < SW_MAX_SCHEMES; ++s) {
         int8_t* T = h->tables.data() + s * kMatBytes;
@@ -1163,23 +1168,33 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
                 T[b * kMatDim + a] = v;
             }
         C.max_score[s] = mx;
-        // small-alphabet column path: alphabet <= 4, 1 <= o <= kI16Bias and
-        // every M[a][b] + o a byte; column word of residue b = bytes
-        // M[a][b] + o, a = 0..3 (0 for residues outside the alphabet)
+        // small-alphabet column path: alphabet <= 4, gap costs that the
+        // drifted sweeps take and every M[a][b] + o + e a byte; one gap
+        // extension cost per launch, so schemes with another one than the
+        // first such scheme's take table lookups; column word of residue b =
+        // bytes M[a][b] + o + e, a = 0..3 (0 for residues outside the alphabet)
         uint32_t* cw = reinterpret_cast<uint32_t*>(h->tables.data() + SW_MAX_SCHEMES * kMatBytes) + s * kMatDim;
-        bool ok = s < n_schemes && schemes[s].alphabet <= 4 && schemes[s].gap_open >= 1 &&
-                  schemes[s].gap_open <= kI16Bias;
+        const int lift = s < n_schemes ? schemes[s].gap_open + schemes[s].gap_extend : 0;
+        bool ok = s < n_schemes && schemes[s].alphabet <= 4 &&
+                  drift_period(schemes[s].gap_open, schemes[s].gap_extend) > 0 &&
+                  (col_sid < 0 || schemes[s].gap_extend == schemes[col_sid].gap_extend);
         for (int b = 0; b < kMatDim; ++b) {
             uint32_t w = 0;
             for (int a = 0; ok && a < 4; ++a) {
                 if (a >= schemes[s].alphabet || b >= schemes[s].alphabet) continue;
-                const int v = schemes[s].matrix[a * schemes[s].alphabet + b] + schemes[s].gap_open;
+                const int v = schemes[s].matrix[a * schemes[s].alphabet + b] + lift;
                 if (v < 0 || v > 255) ok = false;
                 w |= (uint32_t)(v & 0xFF) << (8 * a);
             }
             cw[b] = w;
         }
         C.col_ok[s] = ok ? 1 : 0;
+        if (ok) {
+            if (col_sid < 0) col_sid = s;
+            const int per = drift_period(schemes[s].gap_open, schemes[s].gap_extend);
+            col_period = col_period == 0 ? per : std::min(col_period, per);
+            col_x = std::max(col_x, schemes[s].gap_open - schemes[s].gap_extend);
+        }
     }
     // the packed path holds every value of a pair when its score bound
     // min(n, m) * max_score is at most kI16Limit
@@ -1191,8 +1206,8 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     // Pair table: when exactly one scheme of the call takes table lookups
     // (every other one takes column words), the packed int16 table-range
     // kernels read that scheme's scores from a pair table instead, provided
-    // its alphabet has at most kPtabMaxDim - 1 residues, 1 <= o <= K and
-    // every M[a][b] + o is a byte.
+    // its alphabet has at most kPtabMaxDim - 1 residues, the drifted sweeps
+    // take its gap costs and every M[a][b] + o + e is a byte.
     int ptab_sid = -1, D = 0;
     if (h->opt_ptab) {
         int n_table = 0, cand = -1;
@@ -1200,27 +1215,32 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
             if (!(C.col_ok[sidx] && h->opt_colpath)) { ++n_table; cand = sidx; }
         if (n_table == 1) {
             const sw_scheme& sc = schemes[cand];
-            bool ok = sc.alphabet + 1 <= kPtabMaxDim && sc.gap_open >= 1 && sc.gap_open <= kI16Bias;
+            bool ok = sc.alphabet + 1 <= kPtabMaxDim && drift_period(sc.gap_open, sc.gap_extend) > 0;
             for (int k2 = 0; ok && k2 < sc.alphabet * sc.alphabet; ++k2) {
-                const int v = sc.matrix[k2] + sc.gap_open;
+                const int v = sc.matrix[k2] + sc.gap_open + sc.gap_extend;
                 ok = v >= 0 && v <= 255;
             }
             if (ok) { ptab_sid = cand; D = sc.alphabet + 1; }
         }
     }
     if (ptab_sid >= 0) {
-        // entry [(x D + y) D + b] = bytes M[x][b] + o (low), M[y][b] + o
-        // (high); code D - 1 pads rows and columns with 0
+        // entry [(x D + y) D + b] = bytes M[x][b] + o + e (low), M[y][b] + o
+        // + e (high); code D - 1 pads rows and columns with 0
         const sw_scheme& sc = schemes[ptab_sid];
         const int A = sc.alphabet;
         uint16_t* T = reinterpret_cast<uint16_t*>(h->tables.data() + kPtabOffset);
         auto byte = [&](int a, int b) -> uint16_t {
-            return (a < A && b < A) ? (uint16_t)(sc.matrix[a * A + b] + sc.gap_open) : (uint16_t)0;
+            return (a < A && b < A) ? (uint16_t)(sc.matrix[a * A + b] + sc.gap_open + sc.gap_extend) : (uint16_t)0;
         };
         for (int x = 0; x < D; ++x)
             for (int y = 0; y < D; ++y)
                 for (int b = 0; b < D; ++b)
                     T[(x * D + y) * D + b] = (uint16_t)(byte(x, b) | (byte(y, b) << 8));
+        for (int a = 0; a < A; ++a)
+            for (int b = 0; b < A; ++b) {
+                int8_t& m = h->tables[kRowMaxOffset + a];
+                m = std::max(m, sc.matrix[a * A + b]);
+            }
     }
 
     KParams K;
@@ -1233,6 +1253,20 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     K.max_items = (int32_t)(ws.cap + kMaxBins);
     K.ptab_sid = ptab_sid;
     K.ptab_dim = D;
+    K.redo = ws.keys;   // the keys of the reverse pass are not read any more when its sweeps run
+    K.drift_sid[0] = std::max(0, col_sid);
+    K.drift_e[0] = col_sid >= 0 ? schemes[col_sid].gap_extend : 0;
+    K.drift_period[0] = col_sid >= 0 ? col_period : kChunk;
+    K.drift_x[0] = col_x;
+    K.drift_x[1] = ptab_sid >= 0 ? schemes[ptab_sid].gap_open - schemes[ptab_sid].gap_extend : 0;
+    K.drift_sid[1] = std::max(0, ptab_sid);
+    K.drift_e[1] = ptab_sid >= 0 ? schemes[ptab_sid].gap_extend : 0;
+    K.drift_period[1] = ptab_sid >= 0 ? drift_period(schemes[ptab_sid].gap_open, schemes[ptab_sid].gap_extend) : kChunk;
+    for (int k2 = 0; k2 < 2; ++k2) {
+        h->last_drift_e[k2] = K.drift_e[k2];
+        h->last_drift_period[k2] = K.drift_period[k2];
+        h->last_drift_sid[k2] = K.drift_sid[k2];
+    }
     // query profile: a search (every pair aligns queries[0 .. qprof_n)) with
     // the pair table's scheme profiles its query for the forward pass
     K.qprof = (search_n >= 1 && search_n <= SW_MAX_QUERY && ptab_sid >= 0 && h->opt_qprof) ? 1 : 0;
@@ -1612,6 +1646,12 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
         any_col = any_col || h->last_col_ok[s] != 0;
     }
     for (int s = 0; s < SW_MAX_SCHEMES; ++s) K.col_ok[s] = s < n_schemes && h->last_col_ok[s] ? 1 : 0;
+    // the column words' drift, as the score passes set it
+    for (int k = 0; k < 2; ++k) {
+        K.drift_e[k] = h->last_drift_e[k];
+        K.drift_period[k] = h->last_drift_period[k];
+        K.drift_sid[k] = h->last_drift_sid[k];
+    }
     // does bin e have pairs for variant v (1 column words, 0 byte table)?
     auto wants = [&](const BinInfo& e, int v) { return v == 1 ? (e.col && any_col) : !(e.col && all_col); };
     // Bins no pair can reach are not launched (a launch with no items still

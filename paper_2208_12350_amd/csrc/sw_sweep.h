@@ -63,6 +63,8 @@
 // two rows.
 #pragma once
 
+#include <type_traits>
+
 #include "sw_device.h"
 #include "sw_internal.h"
 
@@ -72,6 +74,10 @@ namespace sw {
 // widest layout (four 16-lane groups with two packed pairs each) of 32-bit
 // column words.
 constexpr int kWaveBuf = 2 * 4 * 2 * RefStager<16>::kBuf;
+constexpr int kNoRow = 0x7FFFFFFF;   // no cell found
+
+__device__ __forceinline__ void push_redo(const KParams& P, int pair);
+
 // One sweep (forward, or reverse when REV) of the wave item
 // order[first .. first+count), one pair per W-lane group, int32 arithmetic.
 template <int W, int R, bool REV, int C = kChunk>
@@ -108,15 +114,13 @@ __device__ __forceinline__ void sweep_i32(const KParams& P, const SchemeLds& S, 
             raw[r] = *p;
         }
         const int A = S.alphabet[J.sid];
-        bool bad = false;
+        int bad = -1;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const bool inside = l * R + r < J.n;
-            bad |= inside && raw[r] >= A;
-            a[r] = (inside && raw[r] < A) ? raw[r] : kPad;
+            a[r] = checked(raw[r], l * R + r < J.n, A, kPad, bad);
         }
         stage.store(buf, J, A, 0, l, bad);
-        if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
+        set_flag(P.flags, kFlagBadResidue, (bad >= 0) & (P.validate != 0));
     }
     const int A = S.alphabet[J.sid];
     const int go = S.gap_open[J.sid];
@@ -141,7 +145,7 @@ __device__ __forceinline__ void sweep_i32(const KParams& P, const SchemeLds& S, 
 #pragma unroll
         for (int r = 0; r < R; ++r) sc[r] = S.mat[bb0 + a[r]];
     }
-    bool bad = false;
+    int bad = -1;
     int j = -l;
     for (int t0 = 0; t0 < steps; t0 += C) {
         const bool more = t0 + C < steps;
@@ -184,7 +188,7 @@ __device__ __forceinline__ void sweep_i32(const KParams& P, const SchemeLds& S, 
             for (int r = 0; r < R; ++r) sc[r] = S.mat[bb0 + a[r]];
         }
     }
-    if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
+    set_flag(P.flags, kFlagBadResidue, (bad >= 0) & (P.validate != 0));
 
     // best of this lane in row-major order, then of the group
     int lb = 0, li = -1, lj = -1;
@@ -250,7 +254,9 @@ __device__ __forceinline__ u16x2 load_scores(const int8_t* mat, int addrA, int a
 }
 
 // One sweep of the wave item order[first .. first+count), two pairs per
-// W-lane group packed into int16 halves.
+// W-lane group packed into int16 halves.  A pair whose reverse sweep does not
+// find the forward score (its forward sweep may have been a drifted one, see
+// below) goes to the redo list.
 template <int W, int R, bool REV, int C = kChunk>
 __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, uint16_t* wbuf,
                                           int first, int count, int lane) {
@@ -295,19 +301,16 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
             rawB[r] = *pB;
         }
         const int AA = S.alphabet[JA.sid], AB = S.alphabet[JB.sid];
-        bool bad = false;
+        int bad = -1;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int i = l * R + r;
-            const bool inA = i < JA.n, inB = i < JB.n;
-            bad |= (inA && rawA[r] >= AA) || (inB && rawB[r] >= AB);
-            const uint32_t a = (inA && rawA[r] < AA) ? rawA[r] : kPad;
-            const uint32_t b = (inB && rawB[r] < AB) ? rawB[r] : kPad;
+            const uint32_t a = checked(rawA[r], l * R + r < JA.n, AA, kPad, bad);
+            const uint32_t b = checked(rawB[r], l * R + r < JB.n, AB, kPad, bad);
             apk[r] = a | (b << 16);
         }
         stA.store(bufA, JA, AA, 0, l, bad);
         stB.store(bufB, JB, AB, 0, l, bad);
-        if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
+        set_flag(P.flags, kFlagBadResidue, (bad >= 0) & (P.validate != 0));
     }
     const int AA = S.alphabet[JA.sid], AB = S.alphabet[JB.sid];
     const u16x2 go2 = pk(cost16(S.gap_open[JA.sid]) | (cost16(S.gap_open[JB.sid]) << 16));
@@ -338,7 +341,7 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
 #pragma unroll
         for (int r = 0; r < R; ++r) sc[r] = load_scores(S.mat, a0 + (int)(apk[r] & 0xFFFF), b0 + (int)(apk[r] >> 16));
     }
-    bool bad = false;
+    int bad = -1;
     uint32_t jc = (uint32_t)(kColMax + l);   // kColMax - j with j = t - l
     for (int t0 = 0; t0 < steps; t0 += C) {
         const bool more = t0 + C < steps;
@@ -401,7 +404,7 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
                 sc[r] = load_scores(S.mat, a0 + (int)(apk[r] & 0xFFFF), b0 + (int)(apk[r] >> 16));
         }
     }
-    if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
+    set_flag(P.flags, kFlagBadResidue, (bad >= 0) & (P.validate != 0));
 
     // per pair: best of this lane in row-major order, then of the group
     // (scores unbiased; a best of 0 leaves the coordinates at -1)
@@ -438,7 +441,7 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
                 P.out[pair] = res;
             } else if (J.fwd_score > 0) {
                 if (lb[p] != J.fwd_score) {
-                    atomicOr(&P.flags[kFlagReverseMismatch], 1);
+                    push_redo(P, pair);
                 } else {
                     P.out[pair].q_start = J.fwd_qe - li[p];
                     P.out[pair].r_start = J.fwd_re - lj[p];
@@ -448,338 +451,236 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
     }
 }
 
-// Small-alphabet ("column word") variant of sweep_i16, for wave items whose
-// pairs all use schemes with at most four residues whose scores plus the gap
-// open cost fit a byte.  The staged reference holds, per column b, one
-// 32-bit word with bytes M[a][b] + o for a = 0..3, so a row's score is one
-// v_perm_b32 of the two pairs' column words with a per-row selector (the
-// query residues), instead of two address computations and two LDS reads.
-// The selector takes a zero byte for rows past the query end, and padding
-// columns hold word 0: both score -o <= -1, as the padding code does.
+// ---- drifted sweeps ---------------------------------------------------------
 //
-// The score arrives biased by +o, so each row keeps Hm = H - o (biased by K;
-// exact because o <= K) instead of H:  H(i-1,j-1) + M = Hm(i-1,j-1) + (M + o).
-// Hm is what E and F need anyway, and what the lane exchange carries, so
-// the row update is  F = max3(F - e, Hm_up, K);  h = max3(Hm_diag + s', E, F);
-// Hm = h - o;  E = max3(E - e, Hm, K);  keys from h.  The top boundary is
-// Hm = K - o, F = K.
-template <int W, int R, bool REV, int C = kChunk>
-__device__ __forceinline__ void sweep_i16_col(const KParams& P, const SchemeLds& S, uint16_t* wbuf,
-                                              int first, int count, int lane) {
+// The packed sweeps of the score sources whose bytes carry a bias (column
+// words, the pair table, the query profile).  They compute the same H as
+// sweep_i16 with fewer instructions per cell, in two ways.
+//
+// 1. Drift.  The value kept for a cell in row r of its lane at sweep step t is
+//    H + z(r, t) with z(r, t) = K0 + e (r + t), where e is the gap extension
+//    cost (one for all pairs of the launch) and t counts from the last
+//    renormalisation.  A gap extension moves one row down or one column (one
+//    step) on and costs e, so in these terms E and F carry over unchanged:
+//        E(r, t+1) = max(E(r, t), Hm(r, t), z(r, t+1))    Hm = H - (o - e)
+//        F(r+1, t) = max(F(r, t), Hm(r, t))
+//        H(r, t)   = max(Hm(r-1, t-1) + (M + o + e), E, F)
+//    which saves the two saturating subtractions of every cell (8 packed
+//    instructions become 6).  The score sources hold bytes M + o + e.  The
+//    clamp at zero is z in E's maximum, a scalar (z is the same in every
+//    lane); F needs none.  Padding rows and columns read byte 0, a score of
+//    -(o + e).  A lane's last row is handed to the next lane's first with
+//    e (R - 1) subtracted.  Every `period` steps the drift is taken off all
+//    kept values, so z stays within [K0, kI16Bias] and a stored value never
+//    exceeds H + kI16Bias, the range of sweep_i16.  Small values are
+//    denormal half-precision patterns here; v_pk_maximum3_f16 compares and
+//    returns them as they are (checked over all operand classes).
+//
+// 2. Tracking.  sweep_i16 spends 3 instructions per row and step on the
+//    row-pair keys.
+//    Forward: the drift is taken off Hm once per cell, and two maxima are
+//    kept: per row over all steps (which gives the score and the upper row
+//    that holds it), and per step over the lane's rows (which gives the first
+//    column in which the lane reaches its best).  Two steps are folded into
+//    one maximum of three, so a cell costs 2 instructions in place of 3.  The
+//    per-step maxima are over values that also carry the row: the undrifting
+//    add is a v_pk_mad_u16 that shifts the score up by k bits and puts a row
+//    code below it, larger for upper rows, so that the maximum prefers the
+//    upper row and the column found is that row's first.  That takes a score
+//    bound of at most 0x7BFF >> k for the item's pairs (k = 3 for up to 8
+//    rows per lane, 4 for up to 16).  A pair-table lane of more than 8 rows
+//    keeps the maxima of its even and of its odd rows apart (kSets = 2), as
+//    its scores leave fewer bits.  Where the bound does not hold (queries of
+//    more than about 660 DNA or 520 protein residues) the code is left out:
+//    then the column may be too small, when another row of the lane lower
+//    down holds the best score in an earlier column (about 0.05% of related
+//    pairs).  The reverse sweep decides: the prefix box of a column that is
+//    too small holds no cell of the best score, so no start is found, the
+//    pair goes to the redo list and sw_redo_kernel looks for its end again.
+//    Reverse: the score S is known, so a cell is looked at only when it can
+//    hold S.  Per step one maximum over the lane's rows (rows 8 apart are
+//    brought to the same drift) is compared with S, and only when some lane
+//    may have reached it are the rows compared one by one.  That is about
+//    0.6 instructions per cell in place of 3.
+
+// Residues of the lane's query rows (the last one repeated past the query
+// end), and how many of the rows lie within the query (<= 0: none).
+template <int R>
+__device__ __forceinline__ int load_rows(const KParams& P, const PairJob& J, int l, int (&raw)[R]) {
+    const int rem = J.n - l * R;
+    const uint8_t* base = J.n > 0 ? P.queries + J.qbase + (int64_t)J.dir * (l * R)
+                                  : reinterpret_cast<const uint8_t*>(P.order);
+    const int last = J.n > 0 ? rem - 1 : 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) raw[r] = base[J.n > 0 ? J.dir * (r < last ? r : last) : 0];
+    return rem;
+}
+
+// Sums of wave-uniform values, as scalar instructions the compiler leaves in
+// place: it otherwise keeps every multiple of e of an unrolled step in its own
+// register and spills them.
+__device__ __forceinline__ uint32_t s_add(uint32_t x, uint32_t y) {
+    uint32_t r;
+    asm("s_add_u32 %0, %1, %2" : "=s"(r) : "s"(__builtin_amdgcn_readfirstlane(x)), "s"(y) : "scc");
+    return r;
+}
+__device__ __forceinline__ uint32_t s_sub(uint32_t x, uint32_t y) {
+    uint32_t r;
+    asm("s_sub_u32 %0, %1, %2" : "=s"(r) : "s"(__builtin_amdgcn_readfirstlane(x)), "s"(__builtin_amdgcn_readfirstlane(y)) : "scc");
+    return r;
+}
+
+// x * y + a per 16-bit half, the low half of the wave-uniform a in both
+__device__ __forceinline__ u16x2 pk_mad(u16x2 x, u16x2 y, uint32_t a) {
+    u16x2 r;
+    asm("v_pk_mad_u16 %0, %1, %2, %3 op_sel_hi:[1,1,0]" : "=v"(r) : "v"(x), "v"(y), "s"(a));
+    return r;
+}
+
+// max per 16-bit half (integers)
+__device__ __forceinline__ u16x2 pk_max(u16x2 x, u16x2 y) { return __builtin_elementwise_max(x, y); }
+
+// Score sources of the drifted sweeps.  `rows` sets up the lane's query rows,
+// `stage` writes a prepared chunk of the reference to LDS, `begin` reads what
+// the chunk's first step needs.  Even steps use one set of column registers,
+// odd steps another (PH), so that no register rotates: `step_begin`,
+// `score(r)`, `row_done(r)` and `step_end` are called in that order within a
+// step tt of the chunk.
+
+// Column words: per reference column one 32-bit word with the bytes
+// M[a][b] + o + e, a = 0..3, so a row's scores of both pairs are one
+// v_perm_b32 of the pairs' words with the row's selector.
+template <int W, int R, int C>
+struct ColScores {
     using Stager = RefStager<W, C>;
-    constexpr int reverse = REV ? 1 : 0;
-    constexpr int RP = (R + 1) / 2;
-    constexpr uint32_t K = kI16Bias;
-    constexpr uint32_t K2 = K | (K << 16);
-    const int g = lane / W;
-    const int l = lane % W;
-
-    const int slot = g * 2;
-    const int pairA = slot < count ? P.order[first + slot] : -1;
-    const int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
-    const PairJob JA = load_job(P, pairA, reverse);
-    const PairJob JB = load_job(P, pairB, reverse);
-
-    int mmax = imax(JA.m, JB.m);
-    for (int off = 32; off > 0; off >>= 1) mmax = imax(mmax, __shfl_xor(mmax, off));
-    const int steps = __builtin_amdgcn_readfirstlane(mmax > 0 ? mmax + W - 1 : 0);
-
-    // 32-bit column words: the wave buffer holds twice as many bytes
-    uint32_t* bufA = reinterpret_cast<uint32_t*>(wbuf) + (g * 2) * Stager::kBuf;
-    uint32_t* bufB = bufA + Stager::kBuf;
-    Stager stA, stB;
-    stA.load(P.refs, JA, P.order, 0, l);
-    stB.load(P.refs, JB, P.order, 0, l);
-
-    // per-row selectors: byte 0 picks pair A's score from its column word
-    // (bytes 0..3 of the perm input), byte 2 pair B's (bytes 4..7); bytes 1
-    // and 3 are zero (selector 0x0C), as is a row past the query end
+    using Lds = SchemeLds;
+    using Entry = uint32_t;
+    static constexpr int kSide = 0;   // KParams::drift_e / drift_period entry
+    static constexpr int kSets = 1;
     uint32_t sel[R];
-    {
+    uint32_t ca[2], cb[2];
+
+    __device__ __forceinline__ void check(const KParams& P, PairJob& J, int pair) const {
+        if (pair < 0) J.sid = P.drift_sid[kSide];
+    }
+    __device__ __forceinline__ void rows(const KParams& P, const Lds& S, const PairJob& JA, const PairJob& JB, int l,
+                                         int& bad) {
+        // byte 0 picks pair A's score from its word (bytes 0..3 of the perm
+        // input), byte 2 pair B's (bytes 4..7); bytes 1 and 3 are zero
+        // (selector 0x0C), as is a row past the query end
         int rawA[R], rawB[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = l * R + r;
-            const int iA = i < JA.n ? i : (JA.n > 0 ? JA.n - 1 : 0);
-            const int iB = i < JB.n ? i : (JB.n > 0 ? JB.n - 1 : 0);
-            const uint8_t* pA = JA.n > 0 ? P.queries + JA.qbase + (int64_t)JA.dir * iA
-                                         : reinterpret_cast<const uint8_t*>(P.order);
-            const uint8_t* pB = JB.n > 0 ? P.queries + JB.qbase + (int64_t)JB.dir * iB
-                                         : reinterpret_cast<const uint8_t*>(P.order);
-            rawA[r] = *pA;
-            rawB[r] = *pB;
-        }
+        const int remA = load_rows<R>(P, JA, l, rawA), remB = load_rows<R>(P, JB, l, rawB);
         const int AA = S.alphabet[JA.sid], AB = S.alphabet[JB.sid];
-        bool bad = false;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int i = l * R + r;
-            const bool inA = i < JA.n, inB = i < JB.n;
-            bad |= (inA && rawA[r] >= AA) || (inB && rawB[r] >= AB);
-            const uint32_t a = (inA && rawA[r] < AA) ? (uint32_t)rawA[r] : 0x0Cu;
-            const uint32_t b = (inB && rawB[r] < AB) ? (uint32_t)(4 + rawB[r]) : 0x0Cu;
+            const uint32_t a = checked(rawA[r], r < remA, AA, 0x0C, bad);
+            const uint32_t b = checked(rawB[r], r < remB, AB, 0x0C - 4, bad) + 4;
             sel[r] = a | 0x0C00u | (b << 16) | 0x0C000000u;
         }
-        stA.store_col(bufA, JA, AA, S.colw[JA.sid], 0, l, bad);
-        stB.store_col(bufB, JB, AB, S.colw[JB.sid], 0, l, bad);
-        if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
     }
-    const int AA = S.alphabet[JA.sid], AB = S.alphabet[JB.sid];
-    const uint32_t goA = (uint32_t)S.gap_open[JA.sid], goB = (uint32_t)S.gap_open[JB.sid];
-    const u16x2 go2 = pk(goA | (goB << 16));
-    const u16x2 ge2 = pk(cost16(S.gap_extend[JA.sid]) | (cost16(S.gap_extend[JB.sid]) << 16));
-    const u16x2 zero = pk(K2);
-    const uint32_t hm_top = (K - goA) | ((K - goB) << 16);   // Hm of the zero boundary
-    wave_lds_sync();
+    // upper bounds of the two pairs' scores
+    __device__ __forceinline__ void bounds(const KParams& P, const PairJob& JA, const PairJob& JB, int& a, int& b) const {
+        a = (JA.n < JA.m ? JA.n : JA.m) * P.max_score[JA.sid];
+        b = (JB.n < JB.m ? JB.n : JB.m) * P.max_score[JB.sid];
+    }
+    __device__ __forceinline__ void stage(const Stager& st, Entry* buf, const KParams&, const Lds& S, const PairJob& J,
+                                          int t0, int l, int& bad) const {
+        st.store_col(buf, J, S.alphabet[J.sid], S.colw[J.sid], t0, l, bad);
+    }
+    __device__ __forceinline__ void begin(const Entry* rA, const Entry* rB) {
+        ca[0] = rA[0]; cb[0] = rB[0];
+        ca[1] = rA[1]; cb[1] = rB[1];
+    }
+    template <int PH> __device__ __forceinline__ void step_begin(const Entry*, const Entry*, int) {}
+    template <int PH> __device__ __forceinline__ u16x2 score(int r) const {
+        return pk(__builtin_amdgcn_perm(cb[PH], ca[PH], sel[r]));
+    }
+    template <int PH> __device__ __forceinline__ void row_done(int) {}
+    template <int PH> __device__ __forceinline__ void step_end(const Entry* rA, const Entry* rB, int tt) {
+        ca[PH] = rA[tt + 2];
+        cb[PH] = rB[tt + 2];
+    }
+};
 
-    // Hm[r]: H - o of row r at the last column swept; E[r]: E of row r at the
-    // next column; kA/kB: keys of row pairs (from H itself)
-    u16x2 Hm[R], E[R];
-    uint32_t kA[RP], kB[RP];
-#pragma unroll
-    for (int r = 0; r < R; ++r) { Hm[r] = pk(hm_top); E[r] = zero; }
-#pragma unroll
-    for (int p = 0; p < RP; ++p) { kA[p] = 0u; kB[p] = 0u; }
-    uint32_t Hlast = hm_top, Flast = K2, Hup_prev = hm_top;
-    const uint32_t* rblA = bufA + W - l;
-    const uint32_t* rblB = bufB + W - l;
-
-    // Column words of even steps live in (a0, b0), of odd steps in (a1, b1);
-    // a step reloads its pair with the words two steps ahead as soon as its
-    // rows are done, so the steps are unrolled by two and no register
-    // rotates.
-    bool bad = false;
-    uint32_t jc = (uint32_t)(kColMax + l);
-    auto step = [&](uint32_t& ca, uint32_t& cb, int ahead) {
-        const u16x2 Hmu0 = pk((uint32_t)shift_in_group<W>((int)Hlast, (int)hm_top));
-        // F above the group is 0 (K); a zero fill gives the same F below
-        // because of the max with K
-        const u16x2 Fup = pk((uint32_t)shift_in_group_zero<W>((int)Flast));
-        u16x2 diag = pk(Hup_prev);
-        Hup_prev = u32(Hmu0);
-        u16x2 Hmu = Hmu0;
-        u16x2 F = Fup;
-        const uint32_t jc1 = jc | 0x8000u;
-        uint32_t keyA0 = 0, keyB0 = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            F = pk_max3(pk_sat_sub(F, ge2), Hmu, zero);
-            const u16x2 sc = pk(__builtin_amdgcn_perm(cb, ca, sel[r]));
-            const u16x2 h = pk_max3(diag + sc, E[r], F);
-            diag = Hm[r];
-            Hmu = h - go2;
-            Hm[r] = Hmu;
-            E[r] = pk_max3(pk_sat_sub(E[r], ge2), Hmu, zero);
-            const uint32_t hv = u32(h);
-            if ((r & 1) == 0) {
-                keyA0 = (hv << 16) | jc1;
-                keyB0 = (hv & 0xFFFF0000u) | jc1;
-                if (r == R - 1) {
-                    kA[r / 2] = kA[r / 2] > keyA0 ? kA[r / 2] : keyA0;
-                    kB[r / 2] = kB[r / 2] > keyB0 ? kB[r / 2] : keyB0;
-                }
-            } else {
-                kA[r / 2] = umax3(kA[r / 2], keyA0, (hv << 16) | jc);
-                kB[r / 2] = umax3(kB[r / 2], keyB0, (hv & 0xFFFF0000u) | jc);
-            }
-        }
-        ca = rblA[ahead];
-        cb = rblB[ahead];
-        Hlast = u32(Hm[R - 1]);
-        Flast = u32(F);
-        --jc;
-    };
-    for (int t0 = 0; t0 < steps; t0 += C) {
-        const bool more = t0 + C < steps;
-        if (more) {
-            stA.load(P.refs, JA, P.order, t0 + C, l);
-            stB.load(P.refs, JB, P.order, t0 + C, l);
-        }
-        const int tn = __builtin_amdgcn_readfirstlane(steps - t0 < C ? steps - t0 : C);
-        uint32_t a0 = rblA[0], b0 = rblB[0], a1 = rblA[1], b1 = rblB[1];
-        int tt = 0;
-        for (; tt + 1 < tn; tt += 2) {
-            step(a0, b0, tt + 2);
-            step(a1, b1, tt + 3);
-        }
-        if (tt < tn) step(a0, b0, tt + 2);
-        if (more) {
-            wave_lds_sync();
-            stA.store_col(bufA, JA, AA, S.colw[JA.sid], t0 + C, l, bad);
-            stB.store_col(bufB, JB, AB, S.colw[JB.sid], t0 + C, l, bad);
-            wave_lds_sync();
-        }
-    }
-    if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
-
-    int lb[2] = {0, 0}, li[2] = {-1, -1}, lj[2] = {-1, -1};
-#pragma unroll
-    for (int p = 0; p < RP; ++p) {
-        const uint32_t ks[2] = {kA[p], kB[p]};
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int h = (int)(ks[q] >> 16) - (int)K;
-            const int row = l * R + 2 * p + ((ks[q] & 0x8000u) ? 0 : 1);
-            if (h > lb[q]) { lb[q] = h; li[q] = row; lj[q] = kColMax - (int)(ks[q] & 0x7FFFu); }
-        }
-    }
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        for (int off = 1; off < W; off <<= 1) {
-            const int ob = __shfl_xor(lb[p], off);
-            const int oi = __shfl_xor(li[p], off);
-            const int oj = __shfl_xor(lj[p], off);
-            if (ob > lb[p] || (ob == lb[p] && oi < li[p])) { lb[p] = ob; li[p] = oi; lj[p] = oj; }
-        }
-    }
-    if (l == 0) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int pair = p == 0 ? pairA : pairB;
-            const PairJob& J = p == 0 ? JA : JB;
-            if (pair < 0) continue;
-            if (!reverse) {
-                sw_result res;
-                if (lb[p] > 0) { res.score = lb[p]; res.q_start = -1; res.q_end = li[p]; res.r_start = -1; res.r_end = lj[p]; }
-                else { res.score = 0; res.q_start = res.q_end = res.r_start = res.r_end = -1; }
-                P.out[pair] = res;
-            } else if (J.fwd_score > 0) {
-                if (lb[p] != J.fwd_score) {
-                    atomicOr(&P.flags[kFlagReverseMismatch], 1);
-                } else {
-                    P.out[pair].q_start = J.fwd_qe - li[p];
-                    P.out[pair].r_start = J.fwd_re - lj[p];
-                }
-            }
-        }
-    }
-}
-
-// Pair-table variant of sweep_i16, for wave items whose pairs all use the
-// one scheme of the call whose pair table sits in LDS (alphabets of up to 24
-// residues whose scores plus the gap open cost fit a byte, o <= K).  Entry
-// [(x D + y) D + b] of the table holds the bytes M[x][b] + o and M[y][b] + o
-// for two consecutive query rows with residues x, y (D = alphabet + 1; code
+// Pair table of scheme P.ptab_sid (alphabets of up to 24 residues): entry
+// [(x D + y) D + b] holds the bytes M[x][b] + o + e and M[y][b] + o + e for
+// two consecutive query rows with residues x, y (D = alphabet + 1; code
 // D - 1 pads rows past the query end and columns outside the reference with
-// 0, a score of -o <= -1, as the padding code does).  A lane's row pair p
-// therefore reads both of its scores for one column with a single 16-bit LDS
-// load at rc[p] + 2 b, where rc[p] is a per-row-pair constant: one address
-// add and one load per two rows and pair, against two adds and two loads per
-// row in the byte-table form; one v_perm_b32 per row then places pair A's
-// score in the low half and pair B's in the high half.
-//
-// Scores arrive biased by +o, so rows keep Hm = H - o as in sweep_i16_col.
-// A row pair's scores of the next step are loaded as soon as the pair has
-// used the current ones; the column offsets they need are read from the
-// staged reference two steps ahead.
-template <int W, int R, bool REV, int C = kChunk>
-__device__ __forceinline__ void sweep_i16_ptab(const KParams& P, const PtabLds& S, uint16_t* wbuf,
-                                               int first, int count, int lane) {
+// 0).  A lane's row pair p reads both of its scores for one column with a
+// single 16-bit LDS load at rc[p] + 2 b, where rc[p] is a per-row-pair
+// constant: one address add and one load per two rows and pair; one
+// v_perm_b32 per row then places pair A's score in the low half and pair B's
+// in the high half.  A row pair's scores of the next step are loaded as soon
+// as the pair has used the current ones.
+template <int W, int R, int C>
+struct PtabScores {
     using Stager = RefStager<W, C>;
-    constexpr int reverse = REV ? 1 : 0;
-    constexpr int RP = (R + 1) / 2;
-    constexpr uint32_t K = kI16Bias;
-    constexpr uint32_t K2 = K | (K << 16);
-    const int g = lane / W;
-    const int l = lane % W;
-    const int D = P.ptab_dim;
-    const int tsid = P.ptab_sid >= 0 && P.ptab_sid < SW_MAX_SCHEMES ? P.ptab_sid : 0;
-    const uint8_t* tab = reinterpret_cast<const uint8_t*>(S.tab);
-
-    const int slot = g * 2;
-    const int pairA = slot < count ? P.order[first + slot] : -1;
-    const int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
-    PairJob JA = load_job(P, pairA, reverse);
-    PairJob JB = load_job(P, pairB, reverse);
-    // every pair of a pair-table item uses the table's scheme; anything else
-    // is an internal error, swept as an empty pair
-    if (pairA >= 0 && JA.sid != P.ptab_sid) {
-        atomicOr(&P.flags[kFlagInternal], 1);
-        JA.n = JA.m = 0; JA.fwd_score = 0; JA.sid = tsid;
-    }
-    if (pairB >= 0 && JB.sid != P.ptab_sid) {
-        atomicOr(&P.flags[kFlagInternal], 1);
-        JB.n = JB.m = 0; JB.fwd_score = 0; JB.sid = tsid;
-    }
-
-    int mmax = imax(JA.m, JB.m);
-    for (int off = 32; off > 0; off >>= 1) mmax = imax(mmax, __shfl_xor(mmax, off));
-    const int steps = __builtin_amdgcn_readfirstlane(mmax > 0 ? mmax + W - 1 : 0);
-
-    uint16_t* bufA = wbuf + (g * 2) * Stager::kBuf;
-    uint16_t* bufB = bufA + Stager::kBuf;
-    Stager stA, stB;
-    stA.load(P.refs, JA, P.order, 0, l);
-    stB.load(P.refs, JB, P.order, 0, l);
-
-    // per row pair: byte offsets of its table rows, ((x D + y) D) * 2, for
-    // pair A (low half) and pair B (high half); both are below 2 D^3 <= 2^15
-    const int A = S.alphabet[tsid];
-    uint32_t rc[RP];
-    {
-        int rawA[R], rawB[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = l * R + r;
-            const int iA = i < JA.n ? i : (JA.n > 0 ? JA.n - 1 : 0);
-            const int iB = i < JB.n ? i : (JB.n > 0 ? JB.n - 1 : 0);
-            const uint8_t* pA = JA.n > 0 ? P.queries + JA.qbase + (int64_t)JA.dir * iA
-                                         : reinterpret_cast<const uint8_t*>(P.order);
-            const uint8_t* pB = JB.n > 0 ? P.queries + JB.qbase + (int64_t)JB.dir * iB
-                                         : reinterpret_cast<const uint8_t*>(P.order);
-            rawA[r] = *pA;
-            rawB[r] = *pB;
-        }
-        bool bad = false;
-        int xA[2 * RP], xB[2 * RP];
-#pragma unroll
-        for (int r = 0; r < 2 * RP; ++r) {
-            const int i = l * R + r;
-            const bool inA = r < R && i < JA.n, inB = r < R && i < JB.n;
-            const int ra = r < R ? rawA[r] : 0, rb = r < R ? rawB[r] : 0;
-            bad |= (inA && ra >= A) || (inB && rb >= A);
-            xA[r] = (inA && ra < A) ? ra : D - 1;
-            xB[r] = (inB && rb < A) ? rb : D - 1;
-        }
-#pragma unroll
-        for (int p = 0; p < RP; ++p)
-            rc[p] = (uint32_t)((xA[2 * p] * D + xA[2 * p + 1]) * D * 2) |
-                    ((uint32_t)((xB[2 * p] * D + xB[2 * p + 1]) * D * 2) << 16);
-        stA.store_ptab(bufA, JA, A, D, 0, l, bad);
-        stB.store_ptab(bufB, JB, A, D, 0, l, bad);
-        if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
-    }
-    const uint32_t goA = (uint32_t)S.gap_open[JA.sid], goB = (uint32_t)S.gap_open[JB.sid];
-    const u16x2 go2 = pk(goA | (goB << 16));
-    const u16x2 ge2 = pk(cost16(S.gap_extend[JA.sid]) | (cost16(S.gap_extend[JB.sid]) << 16));
-    const u16x2 zero = pk(K2);
-    const uint32_t hm_top = (K - goA) | ((K - goB) << 16);   // Hm of the zero boundary
-    wave_lds_sync();
-
-    u16x2 Hm[R], E[R];
-    uint32_t kA[RP], kB[RP];
-#pragma unroll
-    for (int r = 0; r < R; ++r) { Hm[r] = pk(hm_top); E[r] = zero; }
-#pragma unroll
-    for (int p = 0; p < RP; ++p) { kA[p] = 0u; kB[p] = 0u; }
-    uint32_t Hlast = hm_top, Flast = K2, Hup_prev = hm_top;
-    const uint16_t* rblA = bufA + W - l;
-    const uint16_t* rblB = bufB + W - l;
-
-    // uA/uB[p]: row pair p's scores (bytes) of the current step, pair A's
-    // two rows and pair B's.  Column offsets of even steps live in (xa0, xb0), of odd
-    // steps in (xa1, xb1).  A step first reloads its own offsets with those
-    // two steps ahead (its scores are already loaded), then, row pair by row
-    // pair, uses the scores and loads the next step's with the other
-    // offsets.  Steps are unrolled by two, so no register rotates.
+    using Lds = PtabLds;
+    using Entry = uint16_t;
+    static constexpr int kSide = 1;
+    static constexpr int kSets = R > 8 ? 2 : 1;
+    static constexpr int RP = (R + 1) / 2;
     // Up to 14 rows per lane pairs A and B keep their scores in separate
     // registers (one v_perm_b32 per row reads both); above that the two
     // loads fill the halves of one register, which costs one more v_perm_b32
     // per row pair but keeps the kernel within 256 registers, i.e. two
     // wavefronts per SIMD instead of one.
-    constexpr bool kSplit = R <= 14;
+    static constexpr bool kSplit = R <= 14;
+    // byte offsets of a row pair's table rows, ((x D + y) D) * 2, for pair A
+    // (low half) and pair B (high half); both are below 2 D^3 <= 2^15
+    uint32_t rc[RP];
     uint32_t uA[RP], uB[kSplit ? RP : 1];
-    auto load_pair = [&](int p, uint32_t ca, uint32_t cb) {
+    uint32_t xa[2], xb[2];
+    const uint8_t* tab;
+    int sumA, sumB;   // scores of this lane's rows at their best
+
+    __device__ __forceinline__ void check(const KParams& P, PairJob& J, int pair) const {
+        // every pair of a pair-table item uses the table's scheme; anything
+        // else is an internal error, swept as an empty pair
+        if (pair < 0) J.sid = P.ptab_sid;
+        if (pair >= 0 && J.sid != P.ptab_sid) {
+            atomicOr(&P.flags[kFlagInternal], 1);
+            J.n = J.m = 0; J.fwd_score = 0; J.sid = P.ptab_sid;
+        }
+    }
+    __device__ __forceinline__ void rows(const KParams& P, const Lds& S, const PairJob& JA, const PairJob& JB, int l,
+                                         int& bad) {
+        tab = reinterpret_cast<const uint8_t*>(S.tab);
+        const int D = P.ptab_dim, A = D - 1;
+        int rawA[R], rawB[R];
+        const int remA = load_rows<R>(P, JA, l, rawA), remB = load_rows<R>(P, JB, l, rawB);
+        int xA[2 * RP], xB[2 * RP];
+        sumA = sumB = 0;
+#pragma unroll
+        for (int r = 0; r < 2 * RP; ++r) {
+            if (r >= R) {   // the row below an odd lane's last
+                xA[r] = xB[r] = D - 1;
+                continue;
+            }
+            const int ra = rawA[r < R ? r : 0], rb = rawB[r < R ? r : 0];
+            xA[r] = checked(ra, r < remA, A, D - 1, bad);
+            xB[r] = checked(rb, r < remB, A, D - 1, bad);
+            sumA += S.row_max[xA[r]];
+            sumB += S.row_max[xB[r]];
+        }
+#pragma unroll
+        for (int p = 0; p < RP; ++p)
+            rc[p] = (uint32_t)((xA[2 * p] * D + xA[2 * p + 1]) * D * 2) |
+                    ((uint32_t)((xB[2 * p] * D + xB[2 * p + 1]) * D * 2) << 16);
+    }
+    __device__ __forceinline__ void stage(const Stager& st, Entry* buf, const KParams& P, const Lds&, const PairJob& J,
+                                          int t0, int l, int& bad) const {
+        st.store_ptab(buf, J, P.ptab_dim - 1, P.ptab_dim, t0, l, bad);
+    }
+    __device__ __forceinline__ void bounds(const KParams&, const PairJob&, const PairJob&, int& a, int& b) const {
+        a = sumA;
+        b = sumB;
+        for (int off = 1; off < W; off <<= 1) {
+            a += __shfl_xor(a, off);
+            b += __shfl_xor(b, off);
+        }
+    }
+    __device__ __forceinline__ void load_pair(int p, uint32_t ca, uint32_t cb) {
         const uint32_t a = *reinterpret_cast<const uint16_t*>(tab + (rc[p] & 0xFFFFu) + ca);
         const uint32_t b = *reinterpret_cast<const uint16_t*>(tab + (rc[p] >> 16) + cb);
         if constexpr (kSplit) {
@@ -788,243 +689,307 @@ __device__ __forceinline__ void sweep_i16_ptab(const KParams& P, const PtabLds& 
         } else {
             uA[p] = __builtin_amdgcn_perm(b, a, 0x05040100u);
         }
-    };
-    bool bad = false;
-    uint32_t jc = (uint32_t)(kColMax + l);
-    auto step = [&](uint32_t& xa, uint32_t& xb, uint32_t na, uint32_t nb, int ahead) {
-        xa = rblA[ahead];
-        xb = rblB[ahead];
-        const u16x2 Hmu0 = pk((uint32_t)shift_in_group<W>((int)Hlast, (int)hm_top));
-        // F above the group is 0 (K); a zero fill gives the same F below
-        // because of the max with K
-        const u16x2 Fup = pk((uint32_t)shift_in_group_zero<W>((int)Flast));
-        u16x2 diag = pk(Hup_prev);
-        Hup_prev = u32(Hmu0);
-        u16x2 Hmu = Hmu0;
-        u16x2 F = Fup;
-        const uint32_t jc1 = jc | 0x8000u;
-        uint32_t keyA0 = 0, keyB0 = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int p = r / 2;
-            F = pk_max3(pk_sat_sub(F, ge2), Hmu, zero);
-            u16x2 sc;
-            if constexpr (kSplit)
-                sc = pk(__builtin_amdgcn_perm(uB[p], uA[p], (r & 1) ? 0x0C050C01u : 0x0C040C00u));
-            else
-                sc = pk(__builtin_amdgcn_perm(uA[p], uA[p], (r & 1) ? 0x0C030C01u : 0x0C020C00u));
-            const u16x2 h = pk_max3(diag + sc, E[r], F);
-            diag = Hm[r];
-            Hmu = h - go2;
-            Hm[r] = Hmu;
-            E[r] = pk_max3(pk_sat_sub(E[r], ge2), Hmu, zero);
-            const uint32_t hv = u32(h);
-            if ((r & 1) == 0) {
-                keyA0 = (hv << 16) | jc1;
-                keyB0 = (hv & 0xFFFF0000u) | jc1;
-                if (r == R - 1) {
-                    kA[p] = kA[p] > keyA0 ? kA[p] : keyA0;
-                    kB[p] = kB[p] > keyB0 ? kB[p] : keyB0;
-                }
-            } else {
-                kA[p] = umax3(kA[p], keyA0, (hv << 16) | jc);
-                kB[p] = umax3(kB[p], keyB0, (hv & 0xFFFF0000u) | jc);
-            }
-            if ((r & 1) == 1 || r == R - 1) load_pair(p, na, nb);
-        }
-        Hlast = u32(Hm[R - 1]);
-        Flast = u32(F);
-        --jc;
-    };
-    for (int t0 = 0; t0 < steps; t0 += C) {
-        const bool more = t0 + C < steps;
-        if (more) {
-            stA.load(P.refs, JA, P.order, t0 + C, l);
-            stB.load(P.refs, JB, P.order, t0 + C, l);
-        }
-        const int tn = __builtin_amdgcn_readfirstlane(steps - t0 < C ? steps - t0 : C);
-        uint32_t xa0 = rblA[0], xb0 = rblB[0], xa1 = rblA[1], xb1 = rblB[1];
-#pragma unroll
-        for (int p = 0; p < RP; ++p) load_pair(p, xa0, xb0);
-        int tt = 0;
-        for (; tt + 1 < tn; tt += 2) {
-            step(xa0, xb0, xa1, xb1, tt + 2);
-            step(xa1, xb1, xa0, xb0, tt + 3);
-        }
-        if (tt < tn) step(xa0, xb0, xa1, xb1, tt + 2);
-        if (more) {
-            wave_lds_sync();
-            stA.store_ptab(bufA, JA, A, D, t0 + C, l, bad);
-            stB.store_ptab(bufB, JB, A, D, t0 + C, l, bad);
-            wave_lds_sync();
-        }
     }
-    if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
+    __device__ __forceinline__ void begin(const Entry* rA, const Entry* rB) {
+        xa[0] = rA[0]; xb[0] = rB[0];
+        xa[1] = rA[1]; xb[1] = rB[1];
+#pragma unroll
+        for (int p = 0; p < RP; ++p) load_pair(p, xa[0], xb[0]);
+    }
+    template <int PH> __device__ __forceinline__ void step_begin(const Entry* rA, const Entry* rB, int tt) {
+        // this step's scores are loaded already: its offsets make way for
+        // those two steps ahead
+        xa[PH] = rA[tt + 2];
+        xb[PH] = rB[tt + 2];
+    }
+    template <int PH> __device__ __forceinline__ u16x2 score(int r) const {
+        const int p = r / 2;
+        if constexpr (kSplit)
+            return pk(__builtin_amdgcn_perm(uB[p], uA[p], (r & 1) ? 0x0C050C01u : 0x0C040C00u));
+        else
+            return pk(__builtin_amdgcn_perm(uA[p], uA[p], (r & 1) ? 0x0C030C01u : 0x0C020C00u));
+    }
+    template <int PH> __device__ __forceinline__ void row_done(int r) {
+        if ((r & 1) == 1 || r == R - 1) load_pair(r / 2, xa[PH ^ 1], xb[PH ^ 1]);
+    }
+    template <int PH> __device__ __forceinline__ void step_end(const Entry*, const Entry*, int) {}
+};
 
-    int lb[2] = {0, 0}, li[2] = {-1, -1}, lj[2] = {-1, -1};
-#pragma unroll
-    for (int p = 0; p < RP; ++p) {
-        const uint32_t ks[2] = {kA[p], kB[p]};
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int h = (int)(ks[q] >> 16) - (int)K;
-            const int row = l * R + 2 * p + ((ks[q] & 0x8000u) ? 0 : 1);
-            if (h > lb[q]) { lb[q] = h; li[q] = row; lj[q] = kColMax - (int)(ks[q] & 0x7FFFu); }
+// Query profile (the forward pass of a database search, where every pair
+// aligns the same query): byte ((b W + l) Rp + r) is M[a_i][b] + o + e for
+// row i = l R + r of lane l (0 past the query end, and for the padding code
+// b = D - 1), with Rp = R rounded up to whole dwords.  A lane reads its R
+// rows' scores for one reference residue as Rp/4 consecutive dwords at one
+// address (one add per pair and step), and one v_perm_b32 per row places
+// pair A's score in the low half and pair B's in the high half.
+template <int W, int R>
+struct QprofLds {
+    static constexpr int RD = (R + 3) / 4;          // profile dwords per lane and residue
+    static constexpr int kRowBytes = W * RD * 4;    // profile bytes per residue
+    uint8_t prof[kPtabMaxDim * kRowBytes];
+    int32_t gap_open[SW_MAX_SCHEMES];
+    int32_t bound;   // the query's score against itself at best
+};
+
+template <int W, int R, int C>
+struct QprofScores {
+    using Stager = RefStager<W, C>;
+    using Lds = QprofLds<W, R>;
+    using Entry = uint16_t;
+    static constexpr int kSide = 1;
+    static constexpr int kSets = R > 8 ? 2 : 1;
+    static constexpr int RD = Lds::RD;
+    uint32_t dA[RD], dB[RD];
+    uint32_t xa[2], xb[2];
+    const uint8_t* lprof;   // this lane's rows of residue 0
+    int bound;
+
+    __device__ __forceinline__ void check(const KParams& P, PairJob& J, int pair) const {
+        // every pair aligns the profiled query with the profile's scheme
+        if (pair < 0) J.sid = P.ptab_sid;
+        if (pair >= 0 && (J.sid != P.ptab_sid || J.n != P.qprof_n)) {
+            atomicOr(&P.flags[kFlagInternal], 1);
+            J.n = J.m = 0; J.sid = P.ptab_sid;
         }
     }
+    __device__ __forceinline__ void rows(const KParams&, const Lds& S, const PairJob&, const PairJob&, int l, int&) {
+        lprof = S.prof + l * RD * 4;
+        bound = S.bound;
+    }
+    __device__ __forceinline__ void bounds(const KParams&, const PairJob&, const PairJob&, int& a, int& b) const {
+        a = b = bound;
+    }
+    __device__ __forceinline__ void stage(const Stager& st, Entry* buf, const KParams& P, const Lds&, const PairJob& J,
+                                          int t0, int l, int& bad) const {
+        st.store_qprof(buf, J, P.ptab_dim - 1, P.ptab_dim, Lds::kRowBytes, t0, l, bad);
+    }
+    __device__ __forceinline__ void begin(const Entry* rA, const Entry* rB) {
+        xa[0] = rA[0]; xb[0] = rB[0];
+        xa[1] = rA[1]; xb[1] = rB[1];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        for (int off = 1; off < W; off <<= 1) {
-            const int ob = __shfl_xor(lb[p], off);
-            const int oi = __shfl_xor(li[p], off);
-            const int oj = __shfl_xor(lj[p], off);
-            if (ob > lb[p] || (ob == lb[p] && oi < li[p])) { lb[p] = ob; li[p] = oi; lj[p] = oj; }
+        for (int k = 0; k < RD; ++k) {
+            dA[k] = *reinterpret_cast<const uint32_t*>(lprof + xa[0] + 4 * k);
+            dB[k] = *reinterpret_cast<const uint32_t*>(lprof + xb[0] + 4 * k);
         }
     }
-    if (l == 0) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int pair = p == 0 ? pairA : pairB;
-            const PairJob& J = p == 0 ? JA : JB;
-            if (pair < 0) continue;
-            if (!reverse) {
-                sw_result res;
-                if (lb[p] > 0) { res.score = lb[p]; res.q_start = -1; res.q_end = li[p]; res.r_start = -1; res.r_end = lj[p]; }
-                else { res.score = 0; res.q_start = res.q_end = res.r_start = res.r_end = -1; }
-                P.out[pair] = res;
-            } else if (J.fwd_score > 0) {
-                if (lb[p] != J.fwd_score) {
-                    atomicOr(&P.flags[kFlagReverseMismatch], 1);
-                } else {
-                    P.out[pair].q_start = J.fwd_qe - li[p];
-                    P.out[pair].r_start = J.fwd_re - lj[p];
-                }
-            }
+    template <int PH> __device__ __forceinline__ void step_begin(const Entry* rA, const Entry* rB, int tt) {
+        xa[PH] = rA[tt + 2];
+        xb[PH] = rB[tt + 2];
+    }
+    template <int PH> __device__ __forceinline__ u16x2 score(int r) const {
+        const uint32_t sel = (uint32_t)(r % 4) | 0x0C00u | ((uint32_t)(4 + r % 4) << 16) | 0x0C000000u;
+        return pk(__builtin_amdgcn_perm(dB[r / 4], dA[r / 4], sel));
+    }
+    template <int PH> __device__ __forceinline__ void row_done(int r) {
+        if (r % 4 == 3 || r == R - 1) {
+            dA[r / 4] = *reinterpret_cast<const uint32_t*>(lprof + xa[PH ^ 1] + 4 * (r / 4));
+            dB[r / 4] = *reinterpret_cast<const uint32_t*>(lprof + xb[PH ^ 1] + 4 * (r / 4));
         }
     }
+    template <int PH> __device__ __forceinline__ void step_end(const Entry*, const Entry*, int) {}
+};
+
+// Pairs whose reverse sweep found no start go to the redo list (see above).
+__device__ __forceinline__ void push_redo(const KParams& P, int pair) {
+    const int k = atomicAdd(&P.meta[kMetaRedo], 1);
+    if (k >= 0 && k < P.n_pairs) P.redo[k] = pair;
+    else atomicOr(&P.flags[kFlagInternal], 1);
 }
 
-// Query-profile variant of the forward sweep, for a database search: every
-// pair of the call aligns the same query, whose profile the workgroup builds
-// in LDS once: byte ((b W + l) Rp + r) is M[a_i][b] + o for row i = l R + r
-// of lane l (0 past the query end, and for the padding code b = D - 1), with
-// Rp = R rounded up to whole dwords.  A lane reads its R rows' scores for
-// one reference residue as Rp/4 consecutive dwords at one address (one add
-// per pair and step), and one v_perm_b32 per row places pair A's score in
-// the low half and pair B's in the high half.  Scores arrive biased by +o
-// and rows keep Hm = H - o, as in sweep_i16_col.  The profile stands for
-// the pair table (at most 24 residues, scores plus o a byte, o <= K), whose
-// two loads and two adds per row pair it replaces.
-template <int W, int R, int C = kChunk>
-__device__ __forceinline__ void sweep_i16_qprof(const KParams& P, const int32_t* gap_open, const int32_t* gap_extend,
-                                                const uint8_t* prof, uint16_t* wbuf, int first, int count,
-                                                int lane) {
+// One sweep of the wave item order[first .. first+count), two pairs per
+// W-lane group packed into int16 halves, scores from Src.
+template <class Src, int W, int R, bool REV, int C>
+__device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src::Lds& S, uint16_t* wbuf, int first,
+                                            int count, int lane) {
     using Stager = RefStager<W, C>;
-    constexpr int RP = (R + 1) / 2;
-    constexpr int RD = (R + 3) / 4;                 // profile dwords per lane and residue
-    constexpr uint32_t K = kI16Bias;
-    constexpr uint32_t K2 = K | (K << 16);
+    using Entry = typename Src::Entry;
+    constexpr uint32_t K2 = (uint32_t)kI16Bias * 0x10001u;
     const int g = lane / W;
     const int l = lane % W;
-    const int D = P.ptab_dim;
-    const int A = D - 1;
 
     const int slot = g * 2;
     const int pairA = slot < count ? P.order[first + slot] : -1;
     const int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
-    PairJob JA = load_job(P, pairA, 0);
-    PairJob JB = load_job(P, pairB, 0);
-    // every pair aligns the profiled query with the profile's scheme
-    if (pairA >= 0 && (JA.sid != P.ptab_sid || JA.n != P.qprof_n)) {
-        atomicOr(&P.flags[kFlagInternal], 1);
-        JA.n = JA.m = 0; JA.sid = P.ptab_sid;
-    }
-    if (pairB >= 0 && (JB.sid != P.ptab_sid || JB.n != P.qprof_n)) {
-        atomicOr(&P.flags[kFlagInternal], 1);
-        JB.n = JB.m = 0; JB.sid = P.ptab_sid;
-    }
+    PairJob JA = load_job(P, pairA, REV ? 1 : 0);
+    PairJob JB = load_job(P, pairB, REV ? 1 : 0);
+    Src src;
+    src.check(P, JA, pairA);
+    src.check(P, JB, pairB);
 
+    // wave-uniform step count, even (steps run in twos; a step past the last
+    // reads padding columns)
     int mmax = imax(JA.m, JB.m);
     for (int off = 32; off > 0; off >>= 1) mmax = imax(mmax, __shfl_xor(mmax, off));
-    const int steps = __builtin_amdgcn_readfirstlane(mmax > 0 ? mmax + W - 1 : 0);
+    const int steps = __builtin_amdgcn_readfirstlane(mmax > 0 ? (mmax + W) & ~1 : 0);
 
-    uint16_t* bufA = wbuf + (g * 2) * Stager::kBuf;
-    uint16_t* bufB = bufA + Stager::kBuf;
+    Entry* bufA = reinterpret_cast<Entry*>(wbuf) + (g * 2) * Stager::kBuf;
+    Entry* bufB = bufA + Stager::kBuf;
     Stager stA, stB;
     stA.load(P.refs, JA, P.order, 0, l);
     stB.load(P.refs, JB, P.order, 0, l);
-    constexpr int kRowBytes = W * RD * 4;           // profile bytes per residue
-    bool bad = false;
-    stA.store_qprof(bufA, JA, A, D, kRowBytes, 0, l, bad);
-    stB.store_qprof(bufB, JB, A, D, kRowBytes, 0, l, bad);
-    if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
-    const uint8_t* lprof = prof + l * RD * 4;       // this lane's rows of residue 0
-    const int sid = JA.sid < SW_MAX_SCHEMES ? JA.sid : 0;
-    const uint32_t go = (uint32_t)gap_open[sid];
-    const u16x2 go2 = pk(go | (go << 16));
-    const uint32_t ge = cost16(gap_extend[sid]);
-    const u16x2 ge2 = pk(ge | (ge << 16));
-    const u16x2 zero = pk(K2);
-    const uint32_t hm_top = (K - go) | ((K - go) << 16);
+    int bad = -1;
+    src.rows(P, S, JA, JB, l, bad);
+    src.stage(stA, bufA, P, S, JA, 0, l, bad);
+    src.stage(stB, bufB, P, S, JB, 0, l, bad);
+
+    const uint32_t e = (uint32_t)P.drift_e[Src::kSide];
+    const int period = P.drift_period[Src::kSide];       // even, at least 2
+    const uint32_t e2 = __builtin_amdgcn_readfirstlane(e * 0x10001u), e8 = 8u * e2;
+    const uint32_t goA = (uint32_t)S.gap_open[JA.sid], goB = (uint32_t)S.gap_open[JB.sid];
+    const uint32_t cAB = (goA - e) | ((goB - e) << 16);   // o - e of both pairs
+    const u16x2 c2 = pk(cAB);
+    // z(r, t) = z0 + e2 (r + t); the largest one used is z(R, period)
+    const uint32_t z0 = K2 - e2 * (uint32_t)(R + period + 1);
+    const u16x2 lift = pk(e2 * (uint32_t)(R - 1));        // a lane's last row, as seen from the next lane
     wave_lds_sync();
 
+    // Hm[r]: H - (o - e) of row r at the last step; E[r]: E of row r at the
+    // next step (both drifted); the state before step 0 is H = 0 everywhere
     u16x2 Hm[R], E[R];
-    uint32_t kA[RP], kB[RP];
 #pragma unroll
-    for (int r = 0; r < R; ++r) { Hm[r] = pk(hm_top); E[r] = zero; }
+    for (int r = 0; r < R; ++r) {
+        Hm[r] = pk(z0 + e2 * (uint32_t)r - e2) - c2;
+        E[r] = pk(z0 + e2 * (uint32_t)r);
+    }
+    u16x2 Hlast = Hm[R - 1], Flast = Hlast;
+    u16x2 Hup_prev = pk(z0 - 2u * e2) - c2;
+    // forward: v = ((H - (o - e) + x) << k) + row code, its largest per row,
+    // and per pair and set of rows the key (largest v of a step << 16) |
+    // (kColMax - column), largest first
+    constexpr int kSets = REV ? 1 : Src::kSets;
+    constexpr int kQ = (R + kSets - 1) / kSets;      // rows of a set
+    constexpr int kCode = kQ <= 1 ? 0 : kQ <= 2 ? 1 : kQ <= 4 ? 2 : kQ <= 8 ? 3 : kQ <= 16 ? 4 : 5;
+    u16x2 best[REV ? 1 : R];
+    uint32_t kA[kSets], kB[kSets];
+    const int x = P.drift_x[Src::kSide];
+    int k = 0;
+    if constexpr (!REV) {
+        int a, b;
+        src.bounds(P, JA, JB, a, b);
+        a = imax(a + x - (int)(goA - e), b + x - (int)(goB - e));
+        k = __builtin_amdgcn_ballot_w64(((a + 1) << kCode) > 0x7C00) == 0 ? kCode : 0;
+    }
+    const u16x2 scale = pk(0x10001u << k);
+    const uint32_t ek = __builtin_amdgcn_readfirstlane(e << k);
+    const uint32_t dcode = __builtin_amdgcn_readfirstlane(k > 0 ? 1 : 0);   // code step from one row of a set to the next
+    // undrifting term of row 0 at step 0
+    const uint32_t a0 = __builtin_amdgcn_readfirstlane((((uint32_t)x - (z0 & 0xFFFFu)) << k) + (k > 0 ? kQ - 1 : 0));
+    // reverse: a cell holds S when Hm >= z + thr + 1; row and column found
+    u16x2 thr = pk(0);
+    int rowA = R, rowB = R, colA = 0, colB = 0;   // row within the lane
+    if constexpr (REV) {
+        const uint32_t tA = JA.fwd_score > 0 ? (uint32_t)(JA.fwd_score - (int)(goA - e) - 1) & 0xFFFFu : 0x7C00u;
+        const uint32_t tB = JB.fwd_score > 0 ? (uint32_t)(JB.fwd_score - (int)(goB - e) - 1) & 0xFFFFu : 0x7C00u;
+        thr = pk(tA | (tB << 16));
+    } else {
 #pragma unroll
-    for (int p = 0; p < RP; ++p) { kA[p] = 0u; kB[p] = 0u; }
-    uint32_t Hlast = hm_top, Flast = K2, Hup_prev = hm_top;
-    const uint16_t* rblA = bufA + W - l;
-    const uint16_t* rblB = bufB + W - l;
+        for (int r = 0; r < R; ++r) best[r] = pk(0);
+#pragma unroll
+        for (int q = 0; q < kSets; ++q) kA[q] = kB[q] = 0;
+    }
+    const Entry* rA = bufA + W - l;   // rA[tt]: entry of column t0 + tt - l
+    const Entry* rB = bufB + W - l;
+    uint32_t jc = (uint32_t)(kColMax + l);   // kColMax - j with j = t - l
 
-    // dA/dB: the lane's scores (bytes) of the current step for pairs A and
-    // B, four rows per dword; reloaded for the next step dword by dword as
-    // soon as its rows are done.  Column offsets as in sweep_i16_ptab.
-    uint32_t dA[RD], dB[RD];
-    uint32_t jc = (uint32_t)(kColMax + l);
-    auto step = [&](uint32_t& xa, uint32_t& xb, uint32_t na, uint32_t nb, int ahead) {
-        xa = rblA[ahead];
-        xb = rblB[ahead];
-        const u16x2 Hmu0 = pk((uint32_t)shift_in_group<W>((int)Hlast, (int)hm_top));
-        const u16x2 Fup = pk((uint32_t)shift_in_group_zero<W>((int)Flast));
-        u16x2 diag = pk(Hup_prev);
-        Hup_prev = u32(Hmu0);
-        u16x2 Hmu = Hmu0;
-        u16x2 F = Fup;
-        const uint32_t jc1 = jc | 0x8000u;
-        uint32_t keyA0 = 0, keyB0 = 0;
+    // Step tt of the chunk; zt = z(0, t).  Odd steps (PH = 1) also track the
+    // even step before them (forward); at is that step's undrifting term.
+    auto step = [&](auto phase, int tt, uint32_t zt, uint32_t at) {
+        constexpr int PH = decltype(phase)::value;
+        src.template step_begin<PH>(rA, rB, tt);
+        // the row above the lane's block; above the group it is the matrix's
+        // top boundary, H = 0 (z of row -1) and no F
+        const uint32_t zup = s_sub(zt, e2);
+        const u16x2 top = pk(zup) - c2;
+        const u16x2 Hup = pk((uint32_t)shift_in_group<W>((int)u32(Hlast - lift), (int)u32(top)));
+        u16x2 F = pk((uint32_t)shift_in_group_zero<W>((int)u32(Flast - lift)));
+        u16x2 diag = Hup_prev;
+        Hup_prev = Hup;
+        u16x2 Hmu = Hup;
+        uint32_t z = zt;                    // becomes z(r, t + 1)
+        uint32_t a = at;
+        u16x2 me[kSets], mo[kSets], pe[kSets], po[kSets], f = pk(0), pn = pk(0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int p = r / 2;
-            F = pk_max3(pk_sat_sub(F, ge2), Hmu, zero);
-            const uint32_t sel = (uint32_t)(r % 4) | 0x0C00u | ((uint32_t)(4 + r % 4) << 16) | 0x0C000000u;
-            const u16x2 sc = pk(__builtin_amdgcn_perm(dB[r / 4], dA[r / 4], sel));
-            const u16x2 h = pk_max3(diag + sc, E[r], F);
-            diag = Hm[r];
-            Hmu = h - go2;
-            Hm[r] = Hmu;
-            E[r] = pk_max3(pk_sat_sub(E[r], ge2), Hmu, zero);
-            const uint32_t hv = u32(h);
-            if ((r & 1) == 0) {
-                keyA0 = (hv << 16) | jc1;
-                keyB0 = (hv & 0xFFFF0000u) | jc1;
-                if (r == R - 1) {
-                    kA[p] = kA[p] > keyA0 ? kA[p] : keyA0;
-                    kB[p] = kB[p] > keyB0 ? kB[p] : keyB0;
+            F = pk_max(F, Hmu);
+            const u16x2 h = pk_max3(diag + src.template score<PH>(r), E[r], F);
+            const u16x2 old = Hm[r];
+            const u16x2 hm = h - c2;
+            diag = old;
+            Hm[r] = hm;
+            Hmu = hm;
+            z = s_add(z, e2);
+            E[r] = pk_max3(E[r], hm, pk(z));
+            if constexpr (REV) {
+                if (r % 8 == 0 && r > 0) f = f + pk(e8);
+                if (r == 0) f = hm;
+                else if ((r & 1) == 0) pn = hm;
+                else f = r == 1 ? pk_max(f, hm) : pk_max3(f, pn, hm);
+                if ((r & 1) == 0 && r == R - 1 && r > 0) f = pk_max(f, hm);
+            } else if constexpr (PH == 1) {
+                const u16x2 ue = pk_mad(old, scale, a);
+                a = s_sub(a, ek);
+                const u16x2 uo = pk_mad(hm, scale, a);
+                if (r % kSets == kSets - 1) a = s_sub(a, dcode);
+                best[r] = pk_max3(best[r], ue, uo);
+                const int q = r / kSets, g2 = r % kSets;
+                const bool last = r + kSets >= R;   // of its set
+                if ((q & 1) == 0) {
+                    pe[g2] = ue;
+                    po[g2] = uo;
+                    if (last) {
+                        me[g2] = q == 0 ? ue : pk_max(me[g2], ue);
+                        mo[g2] = q == 0 ? uo : pk_max(mo[g2], uo);
+                    }
+                } else {
+                    me[g2] = q == 1 ? pk_max(pe[g2], ue) : pk_max3(me[g2], pe[g2], ue);
+                    mo[g2] = q == 1 ? pk_max(po[g2], uo) : pk_max3(mo[g2], po[g2], uo);
                 }
-            } else {
-                kA[p] = umax3(kA[p], keyA0, (hv << 16) | jc);
-                kB[p] = umax3(kB[p], keyB0, (hv & 0xFFFF0000u) | jc);
             }
-            if (r % 4 == 3 || r == R - 1) {
-                dA[r / 4] = *reinterpret_cast<const uint32_t*>(lprof + na + 4 * (r / 4));
-                dB[r / 4] = *reinterpret_cast<const uint32_t*>(lprof + nb + 4 * (r / 4));
-            }
+            src.template row_done<PH>(r);
         }
-        Hlast = u32(Hm[R - 1]);
-        Flast = u32(F);
-        --jc;
+        Hlast = Hm[R - 1];
+        Flast = F;
+        src.template step_end<PH>(rA, rB, tt);
+        if constexpr (REV) {
+            // the last group of 8 rows starts at row 8 * ((R - 1) / 8)
+            uint32_t zg = zt;
+#pragma unroll
+            for (int q = 0; q < (R - 1) / 8; ++q) zg = s_add(zg, e8);
+            const u16x2 over = pk_sat_sub(f, thr + pk(zg));
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(u32(over) != 0) != 0, 0)) {
+                uint32_t any = 0, zr = zt;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    any |= u32(pk_sat_sub(Hm[r], thr + pk(zr)));
+                    zr = s_add(zr, e2);
+                }
+                if (__builtin_amdgcn_ballot_w64(any != 0) != 0) {
+                    int hitA = R, hitB = R;
+#pragma unroll
+                    for (int r = R - 1; r >= 0; --r) {
+                        zr = s_sub(zr, e2);
+                        const uint32_t w = u32(pk_sat_sub(Hm[r], thr + pk(zr)));
+                        hitA = (w & 0xFFFFu) ? r : hitA;
+                        hitB = (w >> 16) ? r : hitB;
+                    }
+                    const int j = kColMax - (int)jc;
+                    colA = hitA < rowA ? j : colA;
+                    colB = hitB < rowB ? j : colB;
+                    rowA = hitA < rowA ? hitA : rowA;
+                    rowB = hitB < rowB ? hitB : rowB;
+                }
+            }
+            --jc;
+        } else if constexpr (PH == 1) {
+#pragma unroll
+            for (int q = 0; q < kSets; ++q) {
+                if (q >= R) continue;   // (a set has at least one row)
+                const uint32_t ve = u32(me[q]), vo = u32(mo[q]);
+                kA[q] = umax3(kA[q], (ve << 16) | jc, (vo << 16) | (jc - 1));
+                kB[q] = umax3(kB[q], (ve & 0xFFFF0000u) | jc, (vo & 0xFFFF0000u) | (jc - 1));
+            }
+            jc -= 2;
+        }
     };
     for (int t0 = 0; t0 < steps; t0 += C) {
         const bool more = t0 + C < steps;
@@ -1033,56 +998,104 @@ __device__ __forceinline__ void sweep_i16_qprof(const KParams& P, const int32_t*
             stB.load(P.refs, JB, P.order, t0 + C, l);
         }
         const int tn = __builtin_amdgcn_readfirstlane(steps - t0 < C ? steps - t0 : C);
-        uint32_t xa0 = rblA[0], xb0 = rblB[0], xa1 = rblA[1], xb1 = rblB[1];
+        src.begin(rA, rB);
+        for (int s0 = 0; s0 < tn; s0 += period) {
+            const int s1 = tn - s0 < period ? tn : s0 + period;
+            uint32_t zt = z0, at = a0;
+            for (int tt = s0; tt < s1; tt += 2) {
+                step(std::integral_constant<int, 0>{}, tt, zt, at);
+                step(std::integral_constant<int, 1>{}, tt + 1, zt + e2, at);
+                zt += 2u * e2;
+                at -= 2u * ek;
+            }
+            // renormalise: the next step counts as step 0 again
+            const u16x2 back = pk(e2 * (uint32_t)(s1 - s0));
 #pragma unroll
-        for (int k = 0; k < RD; ++k) {
-            dA[k] = *reinterpret_cast<const uint32_t*>(lprof + xa0 + 4 * k);
-            dB[k] = *reinterpret_cast<const uint32_t*>(lprof + xb0 + 4 * k);
+            for (int r = 0; r < R; ++r) {
+                Hm[r] = Hm[r] - back;
+                E[r] = E[r] - back;
+            }
+            Hlast = Hm[R - 1];
+            Flast = Flast - back;
+            Hup_prev = Hup_prev - back;
         }
-        int tt = 0;
-        for (; tt + 1 < tn; tt += 2) {
-            step(xa0, xb0, xa1, xb1, tt + 2);
-            step(xa1, xb1, xa0, xb0, tt + 3);
-        }
-        if (tt < tn) step(xa0, xb0, xa1, xb1, tt + 2);
         if (more) {
             wave_lds_sync();
-            stA.store_qprof(bufA, JA, A, D, kRowBytes, t0 + C, l, bad);
-            stB.store_qprof(bufB, JB, A, D, kRowBytes, t0 + C, l, bad);
+            src.stage(stA, bufA, P, S, JA, t0 + C, l, bad);
+            src.stage(stB, bufB, P, S, JB, t0 + C, l, bad);
             wave_lds_sync();
         }
     }
-    if (bad && P.validate) atomicOr(&P.flags[kFlagBadResidue], 1);
+    set_flag(P.flags, kFlagBadResidue, (bad >= 0) & (P.validate != 0));
 
-    int lb[2] = {0, 0}, li[2] = {-1, -1}, lj[2] = {-1, -1};
+    if constexpr (REV) {
+        int row[2] = {rowA < R ? l * R + rowA : kNoRow, rowB < R ? l * R + rowB : kNoRow}, col[2] = {colA, colB};
 #pragma unroll
-    for (int p = 0; p < RP; ++p) {
-        const uint32_t ks[2] = {kA[p], kB[p]};
+        for (int p = 0; p < 2; ++p)
+            for (int off = 1; off < W; off <<= 1) {
+                const int oi = __shfl_xor(row[p], off);
+                const int oj = __shfl_xor(col[p], off);
+                col[p] = oi < row[p] ? oj : col[p];
+                row[p] = oi < row[p] ? oi : row[p];
+            }
+        if (l == 0) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int h = (int)(ks[q] >> 16) - (int)K;
-            const int row = l * R + 2 * p + ((ks[q] & 0x8000u) ? 0 : 1);
-            if (h > lb[q]) { lb[q] = h; li[q] = row; lj[q] = kColMax - (int)(ks[q] & 0x7FFFu); }
+            for (int p = 0; p < 2; ++p) {
+                const int pair = p == 0 ? pairA : pairB;
+                const PairJob& J = p == 0 ? JA : JB;
+                if (pair < 0 || J.fwd_score <= 0) continue;
+                if (row[p] == kNoRow) {
+                    push_redo(P, pair);
+                } else {
+                    P.out[pair].q_start = J.fwd_qe - row[p];
+                    P.out[pair].r_start = J.fwd_re - col[p];
+                }
+            }
         }
-    }
+    } else {
+        // per pair: best of this lane, its upper row, and the lane's first
+        // column that reaches it; then the group's, upper rows first
+        const int zero[2] = {x - (int)(goA - e), x - (int)(goB - e)};
+        int lb[2] = {0, 0}, li[2] = {-1, -1}, lj[2] = {-1, -1};
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        for (int off = 1; off < W; off <<= 1) {
-            const int ob = __shfl_xor(lb[p], off);
-            const int oi = __shfl_xor(li[p], off);
-            const int oj = __shfl_xor(lj[p], off);
-            if (ob > lb[p] || (ob == lb[p] && oi < li[p])) { lb[p] = ob; li[p] = oi; lj[p] = oj; }
+        for (int r = 0; r < R; ++r) {
+            const uint32_t b = u32(best[r]);
+            const int h[2] = {(int)((b & 0xFFFFu) >> k) - zero[0], (int)(b >> 16 >> k) - zero[1]};
+            const uint32_t key[2] = {kA[r % kSets], kB[r % kSets]};
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                li[p] = h[p] > lb[p] ? r : li[p];
+                lj[p] = h[p] > lb[p] ? (int)key[p] : lj[p];
+                lb[p] = h[p] > lb[p] ? h[p] : lb[p];
+            }
         }
-    }
-    if (l == 0) {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            const int pair = p == 0 ? pairA : pairB;
-            if (pair < 0) continue;
-            sw_result res;
-            if (lb[p] > 0) { res.score = lb[p]; res.q_start = -1; res.q_end = li[p]; res.r_start = -1; res.r_end = lj[p]; }
-            else { res.score = 0; res.q_start = res.q_end = res.r_start = res.r_end = -1; }
-            P.out[pair] = res;
+            lj[p] = lb[p] > 0 ? kColMax - (lj[p] & 0x7FFF) : -1;
+            li[p] = lb[p] > 0 ? l * R + li[p] : -1;
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            for (int off = 1; off < W; off <<= 1) {
+                const int ob = __shfl_xor(lb[p], off);
+                const int oi = __shfl_xor(li[p], off);
+                const int oj = __shfl_xor(lj[p], off);
+                const bool take = (ob > lb[p]) | ((ob == lb[p]) & (oi < li[p]));
+                lb[p] = take ? ob : lb[p];
+                li[p] = take ? oi : li[p];
+                lj[p] = take ? oj : lj[p];
+            }
+        }
+        if (l == 0) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int pair = p == 0 ? pairA : pairB;
+                if (pair < 0) continue;
+                sw_result res;
+                if (lb[p] > 0) { res.score = lb[p]; res.q_start = -1; res.q_end = li[p]; res.r_start = -1; res.r_end = lj[p]; }
+                else { res.score = 0; res.q_start = res.q_end = res.r_start = res.r_end = -1; }
+                P.out[pair] = res;
+            }
         }
     }
 }

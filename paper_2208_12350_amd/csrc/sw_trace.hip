@@ -264,6 +264,7 @@ __device__ __forceinline__ void sweep_trace(const KParams& P, const TraceArgs& T
     Stager stage;
     stage.load(P.refs, J, P.order, 0, l);
     const int A = S.alphabet[J.sid];
+    int bad = -1;   // residues were checked by the score passes
     int a[R];
     {
         int raw[R];
@@ -275,9 +276,8 @@ __device__ __forceinline__ void sweep_trace(const KParams& P, const TraceArgs& T
             raw[r] = *p;
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r) a[r] = (l * R + r < J.n && raw[r] < A) ? raw[r] : kPad;
+        for (int r = 0; r < R; ++r) a[r] = checked(raw[r], l * R + r < J.n, A, kPad, bad);
     }
-    bool bad = false;   // residues were checked by the score passes
     stage.store(buf, J, A, 0, l, bad);
     const int go = S.gap_open[J.sid];
     const int ge = S.gap_extend[J.sid];
@@ -409,6 +409,7 @@ __device__ __forceinline__ void sweep_trace_i16(const KParams& P, const TraceArg
     stA.load(P.refs, JA, P.order, 0, l);
     stB.load(P.refs, JB, P.order, 0, l);
     const int AA = S.alphabet[JA.sid], AB = S.alphabet[JB.sid];
+    int bad = -1;   // residues were checked by the score passes
     uint32_t apk[R];
     {
         int rawA[R], rawB[R];
@@ -425,12 +426,11 @@ __device__ __forceinline__ void sweep_trace_i16(const KParams& P, const TraceArg
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int i = l * R + r;
-            const uint32_t a = (i < JA.n && rawA[r] < AA) ? rawA[r] : kPad;
-            const uint32_t b = (i < JB.n && rawB[r] < AB) ? rawB[r] : kPad;
+            const uint32_t a = checked(rawA[r], i < JA.n, AA, kPad, bad);
+            const uint32_t b = checked(rawB[r], i < JB.n, AB, kPad, bad);
             apk[r] = a | (b << 16);
         }
     }
-    bool bad = false;   // residues were checked by the score passes
     stA.store(bufA, JA, AA, 0, l, bad);
     stB.store(bufB, JB, AB, 0, l, bad);
     const u16x2 go2 = pk(cost16(S.gap_open[JA.sid]) | (cost16(S.gap_open[JB.sid]) << 16));
@@ -545,13 +545,15 @@ __device__ __forceinline__ void sweep_trace_i16(const KParams& P, const TraceArg
 // Small-alphabet ("column word") form of sweep_trace_i16, for wave items
 // whose pairs all use schemes with at most four residues whose scores plus
 // the gap open cost fit a byte.  The reference is staged as one 32-bit word
-// per column holding M[a][b] + o for a = 0..3, so a row's score is one
+// per column holding M[a][b] + o + e for a = 0..3, so a row's score is one
 // v_perm_b32 of the two pairs' words with the row's selector; rows past the
-// box and padding columns read a zero byte, i.e. a score of -o <= -1, as
-// the padding code does in the table form.  Each row keeps Hm = H - o:
-// H(i-1, j-1) + M = Hm(i-1, j-1) + (M + o), and Hm is what E, F, the lane
-// exchange and the E-extends test need.  Every H, E and F, and therefore
-// every record bit, equals the table form's.
+// box and padding columns read a zero byte, i.e. a score of -(o + e) <= -1.
+// Values are drifted as in sweep_drift (sw_sweep.h): cell (r, t) keeps its
+// value plus z(r, t) = K0 + e (r + t), so E and F carry over without the
+// subtractions of e (18 instructions per row and two pairs in place of 20).
+// The flags compare values of one cell, so the drift drops out of them.  H
+// and E, and F wherever it is above zero, equal the table form's, and so
+// does every record bit that a path can visit.
 template <int W, int R>
 __device__ __forceinline__ void sweep_trace_i16_col(const KParams& P, const TraceArgs& T, const SchemeLds& S,
                                                     uint16_t* wbuf, uint32_t* stg, int first, int count,
@@ -570,6 +572,8 @@ __device__ __forceinline__ void sweep_trace_i16_col(const KParams& P, const Trac
     const int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
     PairJob JA = box_job(P, pairA, W * R);
     PairJob JB = box_job(P, pairB, W * R);
+    if (JA.m <= 0) JA.sid = P.drift_sid[0];
+    if (JB.m <= 0) JB.sid = P.drift_sid[0];
     uint32_t* recA = trace_record(P, T, pairA, JA, W, R);
     uint32_t* recB = trace_record(P, T, pairB, JB, W, R);
     const int stepsA = JA.m > 0 ? JA.m + W - 1 : 0;
@@ -580,7 +584,8 @@ __device__ __forceinline__ void sweep_trace_i16_col(const KParams& P, const Trac
         rowbits |= rs.row_bits(p, __builtin_amdgcn_readlane((p & 1) ? JB.n : JA.n, (p / 2) * W), lane);
     int mmax = imax(JA.m, JB.m);
     for (int off = 32; off > 0; off >>= 1) mmax = imax(mmax, __shfl_xor(mmax, off));
-    const int steps = __builtin_amdgcn_readfirstlane(mmax > 0 ? mmax + W - 1 : 0);
+    // even: a last step of the two past the end reads padding columns
+    const int steps = __builtin_amdgcn_readfirstlane(mmax > 0 ? (mmax + W) & ~1 : 0);
 
     // 32-bit column words: the wave buffer holds twice as many bytes
     uint32_t* bufA = reinterpret_cast<uint32_t*>(wbuf) + (g * 2) * Stager::kBuf;
@@ -589,6 +594,7 @@ __device__ __forceinline__ void sweep_trace_i16_col(const KParams& P, const Trac
     stA.load(P.refs, JA, P.order, 0, l);
     stB.load(P.refs, JB, P.order, 0, l);
     const int AA = S.alphabet[JA.sid], AB = S.alphabet[JB.sid];
+    int bad = -1;   // residues were checked by the score passes
     // per-row selectors: byte 0 picks pair A's score from its column word
     // (bytes 0..3 of the perm input), byte 2 pair B's (bytes 4..7); bytes 1
     // and 3, and a row past the box, select zero (0x0C)
@@ -608,67 +614,72 @@ __device__ __forceinline__ void sweep_trace_i16_col(const KParams& P, const Trac
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int i = l * R + r;
-            const uint32_t a = (i < JA.n && rawA[r] < AA) ? (uint32_t)rawA[r] : 0x0Cu;
-            const uint32_t b = (i < JB.n && rawB[r] < AB) ? (uint32_t)(4 + rawB[r]) : 0x0Cu;
+            const uint32_t a = checked(rawA[r], i < JA.n, AA, 0x0C, bad);
+            const uint32_t b = checked(rawB[r], i < JB.n, AB, 0x0C - 4, bad) + 4;
             sel[r] = a | 0x0C00u | (b << 16) | 0x0C000000u;
         }
     }
-    bool bad = false;   // residues were checked by the score passes
     stA.store_col(bufA, JA, AA, S.colw[JA.sid], 0, l, bad);
     stB.store_col(bufB, JB, AB, S.colw[JB.sid], 0, l, bad);
+    const uint32_t e = (uint32_t)P.drift_e[0];
+    const int period = P.drift_period[0];
+    const uint32_t e2 = __builtin_amdgcn_readfirstlane(e * 0x10001u);
     const uint32_t goA = (uint32_t)S.gap_open[JA.sid], goB = (uint32_t)S.gap_open[JB.sid];
-    const u16x2 go2 = pk(goA | (goB << 16));
-    const u16x2 ge2 = pk(cost16(S.gap_extend[JA.sid]) | (cost16(S.gap_extend[JB.sid]) << 16));
-    const u16x2 zero = pk(K2);
-    const uint32_t hm_top = (K - goA) | ((K - goB) << 16);   // Hm of the zero boundary
+    const u16x2 c2 = pk((goA - e) | ((goB - e) << 16));
+    const uint32_t z0 = K2 - e2 * (uint32_t)(R + period + 1);
+    const u16x2 lift = pk(e2 * (uint32_t)(R - 1));
     wave_lds_sync();
 
-    // Hm0/Hm1[r]: H - o of row r at the last column swept (even steps read
+    // Hm0/Hm1[r]: H - (o - e) of row r at the last column swept (even steps read
     // Hm0 and write Hm1, odd steps the reverse: a row's old value is still
     // needed as the next row's diagonal after its new one is computed, so one
     // array would cost a register copy per row); E[r]: E of row r at the
     // next column
     u16x2 Hm0[R], Hm1[R], E[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) { Hm0[r] = pk(hm_top); E[r] = zero; }
-    uint32_t Hlast = hm_top, Flast = K2, Hup_prev = hm_top;
+    for (int r = 0; r < R; ++r) {
+        Hm0[r] = pk(z0 + e2 * (uint32_t)r - e2) - c2;
+        E[r] = pk(z0 + e2 * (uint32_t)r);
+    }
+    u16x2 Hlast = Hm0[R - 1], Flast = Hlast;
+    u16x2 Hup_prev = pk(z0 - 2u * e2) - c2;
     const uint32_t* rblA = bufA + W - l;   // rblA[tt] = column word of step t0 + tt
     const uint32_t* rblB = bufB + W - l;
     // step t of the chunk: Ho holds the last column's Hm, Hn receives this
     // one's; (ca, cb) are this step's column words, the next step's are
     // read into (na, nb)
     auto step = [&](u16x2 (&Ho)[R], u16x2 (&Hn)[R], uint32_t ca, uint32_t cb, uint32_t& na, uint32_t& nb,
-                    int t0, int tt) {
+                    int t0, int tt, uint32_t zt) {
         na = rblA[tt + 1];
         nb = rblB[tt + 1];
-        const u16x2 Hmu0 = pk((uint32_t)shift_in_group<W>((int)Hlast, (int)hm_top));
-        // F above the group is 0 (K); a zero fill gives the same F below
-        // because of the max with K
-        const u16x2 Fup = pk((uint32_t)shift_in_group_zero<W>((int)Flast));
-        u16x2 diag = pk(Hup_prev);
-        Hup_prev = u32(Hmu0);
-        u16x2 Hmu = Hmu0;
-        u16x2 F = Fup;
+        const u16x2 top = pk(s_sub(zt, e2)) - c2;   // H = 0 above the box; no F
+        const u16x2 Hup = pk((uint32_t)shift_in_group<W>((int)u32(Hlast - lift), (int)u32(top)));
+        u16x2 F = pk((uint32_t)shift_in_group_zero<W>((int)u32(Flast - lift)));
+        u16x2 diag = Hup_prev;
+        Hup_prev = Hup;
+        u16x2 Hmu = Hup;
+        uint32_t z = zt;
         uint32_t acc[2 * NW + 2];   // per 8 rows: D, N streams and FX, EX streams
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            F = pk_max3(pk_sat_sub(F, ge2), Hmu, zero);
+            F = pk_max(F, Hmu);
             const u16x2 d = diag + pk(__builtin_amdgcn_perm(cb, ca, sel[r]));
             const u16x2 h = pk_max3(d, E[r], F);
             const uint32_t p1 = flag_gather(u32(d - h), u32(F - h));
             const uint32_t xf = u32(Hmu - F);
             diag = Ho[r];
-            Hmu = h - go2;
+            Hmu = h - c2;
             Hn[r] = Hmu;
-            E[r] = pk_max3(pk_sat_sub(E[r], ge2), Hmu, zero);
+            z = s_add(z, e2);
+            E[r] = pk_max3(E[r], Hmu, pk(z));
             const uint32_t p2 = flag_gather(xf, u32(Hmu - E[r]));
             uint32_t& a1 = acc[2 * (r / 8)];
             uint32_t& a2 = acc[2 * (r / 8) + 1];
             a1 = r % 8 == 0 ? p1 : flag_push(a1, p1);
             a2 = r % 8 == 0 ? p2 : flag_push(a2, p2);
         }
-        Hlast = u32(Hn[R - 1]);
-        Flast = u32(F);
+        Hlast = Hn[R - 1];
+        Flast = F;
         // a stream pair (D, N of A and B; FX, EX of A and B) per 8 rows
         // becomes one dword per pair; the last 4 rows of R % 8 == 4 sit in
         // bits 4-7 of their stream bytes and become the 16-bit tails
@@ -699,17 +710,27 @@ __device__ __forceinline__ void sweep_trace_i16_col(const KParams& P, const Trac
             stB.load(P.refs, JB, P.order, t0 + kChunk, l);
         }
         const int tn = __builtin_amdgcn_readfirstlane(steps - t0 < kChunk ? steps - t0 : kChunk);
-        int tt = 0;
-        for (; tt + 1 < tn; tt += 2) {
-            step(Hm0, Hm1, cA0, cB0, cA1, cB1, t0, tt);
-            step(Hm1, Hm0, cA1, cB1, cA0, cB0, t0, tt + 1);
-        }
-        static_assert(kChunk % 2 == 0, "every chunk but the last ends on an odd step");
-        if (tt < tn) {
-            // an odd chunk (only the last one) ends in Hm1
-            step(Hm0, Hm1, cA0, cB0, cA1, cB1, t0, tt);
+        // steps run in twos; a step past the last records nothing that is
+        // written out (its block ends with the last step, or it is the
+        // block's own padding)
+        for (int s0 = 0; s0 < tn; s0 += period) {
+            const int s1 = tn - s0 < period ? tn : s0 + period;
+            uint32_t zt = z0;
+            for (int tt = s0; tt < s1; tt += 2) {
+                step(Hm0, Hm1, cA0, cB0, cA1, cB1, t0, tt, zt);
+                step(Hm1, Hm0, cA1, cB1, cA0, cB0, t0, tt + 1, zt + e2);
+                zt += 2u * e2;
+            }
+            // renormalise: the next step counts as step 0 again
+            const u16x2 back = pk(e2 * (uint32_t)(s1 - s0));
 #pragma unroll
-            for (int r = 0; r < R; ++r) Hm0[r] = Hm1[r];
+            for (int r = 0; r < R; ++r) {
+                Hm0[r] = Hm0[r] - back;
+                E[r] = E[r] - back;
+            }
+            Hlast = Hm0[R - 1];
+            Flast = Flast - back;
+            Hup_prev = Hup_prev - back;
         }
         if (more) {
             wave_lds_sync();
@@ -740,7 +761,7 @@ __global__ __launch_bounds__(kBlock) void sw_trace_kernel(KParams P, TraceArgs T
     __shared__ __attribute__((aligned(16))) uint32_t stages[kWavesPerBlock * kStageDwords];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lo = __atomic_load_n(&P.meta[P.lo_idx], __ATOMIC_RELAXED);
     int hi = __atomic_load_n(&P.meta[P.hi_idx], __ATOMIC_RELAXED);
     lo = __builtin_amdgcn_readfirstlane(lo);
@@ -755,8 +776,7 @@ __global__ __launch_bounds__(kBlock) void sw_trace_kernel(KParams P, TraceArgs T
     __syncthreads();
     uint16_t* wbuf = wbufs + wave * kWaveBuf;
     for (;;) {
-        const int mine = atomicAdd(&P.meta[P.head_idx], lane == 0 ? 1 : 0);
-        const int it = __builtin_amdgcn_readlane(mine, 0);
+        const int it = next_item(&P.meta[P.head_idx]);
         if (it >= hi - lo) break;
         const WorkItem* wp = P.items + lo + it;
         const int first = __builtin_amdgcn_readfirstlane(__atomic_load_n(&wp->first, __ATOMIC_RELAXED));
@@ -765,11 +785,11 @@ __global__ __launch_bounds__(kBlock) void sw_trace_kernel(KParams P, TraceArgs T
         if (valid) {
             wave_lds_sync();
             if constexpr (PREC == 16 && COL)
-                sweep_trace_i16_col<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, lane);
+                sweep_trace_i16_col<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, opaque_lane(lane));
             else if constexpr (PREC == 16)
-                sweep_trace_i16<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, lane);
+                sweep_trace_i16<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, opaque_lane(lane));
             else
-                sweep_trace<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, lane);
+                sweep_trace<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, opaque_lane(lane));
         } else {
             atomicOr(&P.flags[kFlagInternal], 1);
         }
@@ -797,8 +817,7 @@ __device__ __forceinline__ void trace_member(const KParams& P, const TraceArgs& 
     }
     const int head = (COL ? kMetaColHeads : kMetaHeads) + bin;
     for (;;) {
-        const int mine = atomicAdd(&P.meta[head], lane == 0 ? 1 : 0);
-        const int it = __builtin_amdgcn_readlane(mine, 0);
+        const int it = next_item(&P.meta[head]);
         if (it >= hi - lo) break;
         const WorkItem* wp = P.items + lo + it;
         const int first = __builtin_amdgcn_readfirstlane(__atomic_load_n(&wp->first, __ATOMIC_RELAXED));
@@ -807,11 +826,11 @@ __device__ __forceinline__ void trace_member(const KParams& P, const TraceArgs& 
         if (valid) {
             wave_lds_sync();
             if constexpr (PREC == 16 && COL)
-                sweep_trace_i16_col<W, R>(P, T, L, wbuf, stage, first, count, lane);
+                sweep_trace_i16_col<W, R>(P, T, L, wbuf, stage, first, count, opaque_lane(lane));
             else if constexpr (PREC == 16)
-                sweep_trace_i16<W, R>(P, T, L, wbuf, stage, first, count, lane);
+                sweep_trace_i16<W, R>(P, T, L, wbuf, stage, first, count, opaque_lane(lane));
             else
-                sweep_trace<W, R>(P, T, L, wbuf, stage, first, count, lane);
+                sweep_trace<W, R>(P, T, L, wbuf, stage, first, count, opaque_lane(lane));
         } else {
             atomicOr(&P.flags[kFlagInternal], 1);
         }
@@ -836,7 +855,7 @@ __global__ __launch_bounds__(kBlock) void sw_trace_family_kernel(KParams P, Trac
     __shared__ __attribute__((aligned(16))) uint32_t stages[kWavesPerBlock * kStageDwords];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
     load_schemes(L, P, tid);
     __syncthreads();
