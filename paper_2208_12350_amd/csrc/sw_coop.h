@@ -1,27 +1,36 @@
-// sw_coop.h -- cooperative sweep: one pair group spread over the four
+// sw_coop.h -- cooperative sweeps: one pair group spread over the four
 // wavefronts of a workgroup (gfx950).
 //
 // For long queries the critical path of a pair is its sweep on one lane
 // group: m + W - 1 steps of R rows each.  A single 64-lane wavefront needs
 // R = 32 rows per lane for a 2048-residue query; here the four wavefronts of
-// a workgroup form one group of W = 256 lanes (R <= 8 rows per lane), which
-// cuts each pair's latency by about four at the price of a longer ramp
-// (W - 1 steps) and one workgroup barrier per step.
+// a workgroup form one group of 256 lanes (R <= 8 rows per lane), which cuts
+// each pair's latency by about four.
 //
-// Arithmetic, padding, biased packed int16 values and row-pair keys are
-// those of sweep_i16 (sw_sweep.h): two pairs per group, pair A in the low
-// halves, pair B in the high halves.  What changes is the exchange at the
-// wavefront boundaries: lane 0 of wavefront w > 0 takes the H and F of lane
-// 63 of wavefront w - 1 from the previous step through LDS (double-buffered
-// by step parity) instead of the DPP fill, and every step ends with a
-// workgroup barrier, so the value a wavefront reads at step t was written at
-// step t - 1 and is overwritten no earlier than step t + 1.  All waves run
-// the same number of steps and chunks (the step count depends only on the
-// pair lengths, which every lane loads), so every barrier is reached by the
-// whole workgroup.
+// Two forms:
+//   * Drifted sweeps (column words and the pair table): each wavefront runs
+//     sweep_drift on its 64 R rows, and the wavefronts follow one another as a
+//     pipeline.  The last lane of a wavefront writes its last row's values
+//     into an LDS ring from which the next wavefront's first lane takes them;
+//     the next wavefront runs `lag` blocks of 32 steps behind (63 of those 96
+//     steps are the diagonal's own), so one workgroup barrier per 32 steps
+//     orders the ring.  With a barrier in every step, as below, the four
+//     wavefronts waited for the slowest each time and every scheme took the
+//     table lookups: 1,000,000 mixed pairs took 178.3 ms, now 122.1;
+//     2,500 mixed pairs 7.4 ms, now 5.4.
+//   * Table lookups (any scheme): arithmetic, padding, biased packed int16
+//     values and row-pair keys are those of sweep_i16 (sw_sweep.h), and all
+//     four wavefronts are in step.  Lane 0 of wavefront w > 0 takes the H and F of lane 63 of wavefront w - 1 from the previous
+//     step through LDS (double-buffered by step parity) instead of the DPP
+//     fill, and every step ends with a workgroup barrier, so the value a
+//     wavefront reads at step t was written at step t - 1 and is overwritten
+//     no earlier than step t + 1.
+// All waves run the same number of steps and barriers (they depend only on
+// the pair lengths, which every lane loads), so every barrier is reached by
+// the whole workgroup.
 #pragma once
 
-#include "sw_sweep.h"
+#include "sw_queue.h"
 
 namespace sw {
 
@@ -247,34 +256,17 @@ __device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S,
     }
 }
 
-// Work-queue kernel of the cooperative shapes: every workgroup claims one
-// two-pair item at a time (wave 0 fetches, LDS broadcasts) until the bin's
-// range is exhausted.
-template <int R, bool REV>
-__global__ __launch_bounds__(kBlock) void sw_coop_kernel(KParams P) {
-    __shared__ __attribute__((aligned(16))) SchemeLds L;
-    __shared__ __attribute__((aligned(16))) CoopLds C;
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int lo = __atomic_load_n(&P.meta[P.lo_idx], __ATOMIC_RELAXED);
-    int hi = __atomic_load_n(&P.meta[P.hi_idx], __ATOMIC_RELAXED);
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    hi = __builtin_amdgcn_readfirstlane(hi);
-    if (lo == hi) return;
-    if (lo < 0 || hi > P.max_items || lo > hi) {
-        if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);
-        return;
-    }
-    const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
-    load_schemes(L, P, tid);
-    __syncthreads();
+// The work-queue loop of a cooperative workgroup: it claims one two-pair item
+// of [lo, hi) at a time (wave 0 fetches, LDS broadcasts) until the range is
+// exhausted, and sweeps each with `sweep(first, count)`.
+template <class Sweep>
+__device__ __forceinline__ void coop_loop(const KParams& P, int32_t& item, int wave, int lo, int hi, int head_idx,
+                                          int n_pairs, Sweep&& sweep) {
     for (;;) {
-        // wave 0 claims the next item; every lane of it writes the same value
-        if (wave == 0) {
-            C.item = next_item(&P.meta[P.head_idx]);
-        }
+        // every lane of wave 0 writes the same value
+        if (wave == 0) item = next_item(&P.meta[head_idx]);
         __syncthreads();
-        const int it = __builtin_amdgcn_readfirstlane(C.item);
+        const int it = __builtin_amdgcn_readfirstlane(item);
         __syncthreads();
         if (it >= hi - lo) break;
         const WorkItem* wp = P.items + lo + it;
@@ -282,11 +274,109 @@ __global__ __launch_bounds__(kBlock) void sw_coop_kernel(KParams P) {
         const int count = __builtin_amdgcn_readfirstlane((int)__atomic_load_n(&wp->count, __ATOMIC_RELAXED));
         const bool valid = first >= 0 && count >= 1 && count <= 2 && first + count <= n_pairs;
         if (valid) {
-            sweep_coop<R, REV>(P, L, C, first, count, tid);
+            sweep(first, count);
         } else {
             atomicOr(&P.flags[kFlagInternal], 1);
         }
     }
+}
+
+// LDS and sweep of one cooperative workgroup for a score source.
+template <int VAR, int RMAX>
+struct CoopWork {
+    using Src = typename std::conditional<VAR == kVarPtab, PtabScores<64, RMAX, kChunk>,
+                                          ColScores<64, RMAX, kChunk>>::type;
+    typename Src::Lds L;
+    CoopX X;
+    __attribute__((aligned(16))) typename Src::Entry wbufs[kWavesPerBlock][2 * RefStager<64>::kBuf];
+    __device__ __forceinline__ void load(const KParams& P, int tid) {
+        if constexpr (VAR == kVarPtab) load_ptab(L, P, tid);
+        else load_schemes(L, P, tid);
+    }
+    __device__ __forceinline__ int32_t& item() { return X.item; }
+    template <int R, bool REV>
+    __device__ __forceinline__ void sweep(const KParams& P, int first, int count, int tid, int wave) {
+        using S = typename std::conditional<VAR == kVarPtab, PtabScores<64, R, kChunk>, ColScores<64, R, kChunk>>::type;
+        sweep_drift<S, 64, R, REV, kChunk, true>(P, L, reinterpret_cast<uint16_t*>(wbufs[wave]), first, count,
+                                                 opaque_lane(tid & 63), &X, wave);
+    }
+};
+template <int RMAX>
+struct CoopWork<kVarTable, RMAX> {
+    SchemeLds L;
+    CoopLds C;
+    __device__ __forceinline__ void load(const KParams& P, int tid) { load_schemes(L, P, tid); }
+    __device__ __forceinline__ int32_t& item() { return C.item; }
+    template <int R, bool REV>
+    __device__ __forceinline__ void sweep(const KParams& P, int first, int count, int tid, int) {
+        sweep_coop<R, REV>(P, L, C, first, count, tid);
+    }
+};
+
+// Set-up shared by the kernels below; false when the launch cannot run.
+template <int VAR, class Work>
+__device__ __forceinline__ bool coop_begin(const KParams& P, Work& K, int tid) {
+    if constexpr (VAR == kVarPtab)
+        if (P.ptab_sid < 0 || P.ptab_sid >= SW_MAX_SCHEMES || P.ptab_dim < 2 || P.ptab_dim > kPtabMaxDim) {
+            if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);
+            return false;
+        }
+    K.load(P, tid);
+    __syncthreads();
+    return true;
+}
+
+// Work-queue kernel of one cooperative shape.
+template <int R, bool REV, int VAR>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void sw_coop_kernel(KParams P) {
+    __shared__ __attribute__((aligned(16))) CoopWork<VAR, R> K;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int lo, hi;
+    if (!launch_range(P, tid, lo, hi)) return;
+    const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
+    if (!coop_begin<VAR>(P, K, tid)) return;
+    coop_loop(P, K.item(), wave, lo, hi, P.head_idx, n_pairs,
+              [&](int first, int count) { K.template sweep<R, REV>(P, first, count, tid, wave); });
+}
+
+// Family kernel of the cooperative shapes (see sw_family_kernel): drains the
+// queue of member k's bin, then member k + 1's.
+template <int VAR, bool REV, int R, class Work>
+__device__ __forceinline__ void coop_member(const KParams& P, Work& K, int bin, int n_pairs, int tid, int wave) {
+    if (bin < 0) return;
+    const int lo_i = VAR == kVarCol ? kMetaItemFirst + bin : kMetaItemSplit + bin;
+    const int hi_i = VAR == kVarCol ? kMetaItemSplit + bin : kMetaItemFirst + bin + 1;
+    const int lo = __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[lo_i], __ATOMIC_RELAXED));
+    const int hi = __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[hi_i], __ATOMIC_RELAXED));
+    if (lo >= hi) return;
+    if (lo < 0 || hi > P.max_items) {
+        if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);
+        return;
+    }
+    coop_loop(P, K.item(), wave, lo, hi, (VAR == kVarCol ? kMetaColHeads : kMetaHeads) + bin, n_pairs,
+              [&](int first, int count) { K.template sweep<R, REV>(P, first, count, tid, wave); });
+}
+
+template <bool REV, int VAR, int... Rs>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void sw_coop_family_kernel(KParams P) {
+    __shared__ __attribute__((aligned(16))) CoopWork<VAR, 8> K;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
+    // a launch for empty bins only costs its workgroups these loads
+    int items = 0;
+#pragma unroll
+    for (int k = 0; k < (int)sizeof...(Rs); ++k) {
+        const int bin = P.fam_bins[k];
+        if (bin >= 0)
+            items += VAR == kVarCol ? P.meta[kMetaItemSplit + bin] - P.meta[kMetaItemFirst + bin]
+                                    : P.meta[kMetaItemFirst + bin + 1] - P.meta[kMetaItemSplit + bin];
+    }
+    if (__builtin_amdgcn_readfirstlane(items) == 0) return;
+    if (!coop_begin<VAR>(P, K, tid)) return;
+    int k = 0;
+    ((coop_member<VAR, REV, Rs>(P, K, P.fam_bins[k++], n_pairs, tid, wave)), ...);
 }
 
 }  // namespace sw

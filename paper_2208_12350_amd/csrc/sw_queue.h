@@ -242,6 +242,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
     __shared__ __attribute__((aligned(16))) Lds L;
     __shared__ uint16_t wbufs[kWavesPerBlock * kWaveBuf];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // a launch for empty bins only costs its workgroups these loads
+    int items = 0;
+#pragma unroll
+    for (int m = 0; m < (int)sizeof...(Rs); ++m) {
+        const int bin = P.fam_bins[m];
+        if (bin >= 0)
+            items += VAR == kVarCol ? P.meta[kMetaItemSplit + bin] - P.meta[kMetaItemFirst + bin]
+                                    : P.meta[kMetaItemFirst + bin + 1] - P.meta[kMetaItemSplit + bin];
+    }
+    if (__builtin_amdgcn_readfirstlane(items) == 0) return;
     if constexpr (VAR == kVarPtab) {
         if (P.ptab_sid < 0 || P.ptab_sid >= SW_MAX_SCHEMES || P.ptab_dim < 2 || P.ptab_dim > kPtabMaxDim) {
             if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);

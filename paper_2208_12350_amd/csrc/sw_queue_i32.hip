@@ -17,6 +17,20 @@ static const KernelEntry kI32Kernels[] = {
 };
 #undef SW_ENTRY
 
+// Families (int32 pairs are rare: fewer launches for bins that are mostly
+// empty).  The 64-lane shapes of 6..16 rows keep a family, and so a register
+// budget, of their own.
+#define SW_FAMILY32(W, ...)                                                                                  \
+    {32, W, family_size<__VA_ARGS__>(), {__VA_ARGS__},                                                       \
+     {{&sw_family_kernel<32, W, false, kVarTable, 2, kChunk, __VA_ARGS__>,                                   \
+       &sw_family_kernel<32, W, true, kVarTable, 2, kChunk, __VA_ARGS__>},                                   \
+      {nullptr, nullptr}, {nullptr, nullptr}},                                                               \
+     {2, 2, 2}, {kChunk, kChunk, kChunk}}
+static const FamilyEntry kI32W16Family = SW_FAMILY32(16, 16, 14, 12, 10, 8, 6, 4, 2);
+static const FamilyEntry kI32W64Family = SW_FAMILY32(64, 16, 14, 12, 10, 8, 6);
+static const FamilyEntry kI32W64LongFamily = SW_FAMILY32(64, 32, 28, 24, 20);
+#undef SW_FAMILY32
+
 extern const KernelEntry kI16W16Kernels[];
 extern const int kNumI16W16Kernels;
 extern const KernelEntry kI16W16bKernels[];
@@ -37,6 +51,7 @@ extern const FamilyEntry kI16W32Family;
 extern const FamilyEntry kI16W32bFamily;
 extern const FamilyEntry kI16W64Family;
 extern const FamilyEntry kI16W64LongFamily;
+extern const FamilyEntry kI16W256Family;
 
 namespace {
 
@@ -74,8 +89,9 @@ const ShapeDesc* compiled_shapes(int* n) {
 }
 
 const FamilyEntry* shape_family(int prec, int W, int R) {
-    const FamilyEntry* fams[] = {&kI16W16Family, &kI16W16bFamily, &kI16W32Family,
-                                 &kI16W32bFamily, &kI16W64Family, &kI16W64LongFamily};
+    const FamilyEntry* fams[] = {&kI16W16Family, &kI16W16bFamily, &kI16W32Family, &kI16W32bFamily, &kI16W64Family,
+                                 &kI16W64LongFamily, &kI16W256Family, &kI32W16Family, &kI32W64Family,
+                                 &kI32W64LongFamily};
     for (const FamilyEntry* f : fams)
         if (f->prec == prec && f->W == W)
             for (int k = 0; k < f->n; ++k)

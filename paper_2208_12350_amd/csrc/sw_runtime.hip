@@ -605,18 +605,15 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
             // no bin can hold more than cap / ppw items
             const int ipb = items_per_block(e.W);
             const int64_t need = (cap / e.ppw + 1 + ipb - 1) / ipb;
-            bool any = false;
             for (int v = e.col ? 1 : 0; v >= 0; --v) {   // column-word kernel first
                 if (v == 1 ? !any_col : (e.col && all_col)) continue;
                 if (covered[2 * b + v]) continue;
-                any = true;
                 const int var = table_var(h, e, K, v);
                 const int nw = narrow_tile(h, e, var);
                 const int blocks = (int)std::min<int64_t>(need, h->resident_blocks[nw][pass][var][b]);
                 set_range(K, b, v);
                 h->bin_launch[bin_ev_index(pass, b, v, 0) / 2] = n_launch++;
-                // a bin's kernels share a stream; bins go round-robin
-                hipStream_t ls = forks > 1 ? h->fork[launched % forks] : stream;
+                hipStream_t ls = forks > 1 ? h->fork[launched++ % forks] : stream;
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 0)], ls));
                 hipLaunchKernelGGL(shape_kernel(e.prec, e.W, e.R, pass != 0, var, nw == 1), dim3(blocks), dim3(kBlock),
                                    0, ls, K);
@@ -624,7 +621,6 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 1)], ls));
                 if (per_bin) h->bin_launched[bin_ev_index(pass, b, v, 0) / 2] = 1;
             }
-            if (any) ++launched;
         }
         for (int f = 0; forks > 1 && f < forks; ++f) {
             HIP_TRY(h, hipEventRecord(h->fork_ev[f], h->fork[f]));

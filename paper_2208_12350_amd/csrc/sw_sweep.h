@@ -490,7 +490,8 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
 //    bound of at most 0x7BFF >> k for the item's pairs (k = 3 for up to 8
 //    rows per lane, 4 for up to 16).  A pair-table lane of more than 8 rows
 //    keeps the maxima of its even and of its odd rows apart (kSets = 2), as
-//    its scores leave fewer bits.  Where the bound does not hold (queries of
+//    its scores leave fewer bits, and so do the lanes of cooperative groups
+//    (kCoopSets: their long queries leave 2 bits, or 1 for the pair table).  Where the bound does not hold (queries of
 //    more than about 660 DNA or 520 protein residues) the code is left out:
 //    then the column may be too small, when another row of the lane lower
 //    down holds the best score in an earlier column (about 0.05% of related
@@ -556,7 +557,7 @@ struct ColScores {
     using Lds = SchemeLds;
     using Entry = uint32_t;
     static constexpr int kSide = 0;   // KParams::drift_e / drift_period entry
-    static constexpr int kSets = 1;
+    static constexpr int kSets = 1, kCoopSets = R > 4 ? 2 : 1;
     uint32_t sel[R];
     uint32_t ca[2], cb[2];
 
@@ -578,7 +579,8 @@ struct ColScores {
             sel[r] = a | 0x0C00u | (b << 16) | 0x0C000000u;
         }
     }
-    // upper bounds of the two pairs' scores
+    // upper bounds of the two pairs' scores (kRowBounds: from the group's rows)
+    static constexpr bool kRowBounds = false;
     __device__ __forceinline__ void bounds(const KParams& P, const PairJob& JA, const PairJob& JB, int& a, int& b) const {
         a = (JA.n < JA.m ? JA.n : JA.m) * P.max_score[JA.sid];
         b = (JB.n < JB.m ? JB.n : JB.m) * P.max_score[JB.sid];
@@ -618,7 +620,7 @@ struct PtabScores {
     using Lds = PtabLds;
     using Entry = uint16_t;
     static constexpr int kSide = 1;
-    static constexpr int kSets = R > 8 ? 2 : 1;
+    static constexpr int kSets = R > 8 ? 2 : 1, kCoopSets = R > 4 ? 4 : R > 2 ? 2 : 1;
     static constexpr int RP = (R + 1) / 2;
     // Up to 14 rows per lane pairs A and B keep their scores in separate
     // registers (one v_perm_b32 per row reads both); above that the two
@@ -633,6 +635,7 @@ struct PtabScores {
     uint32_t xa[2], xb[2];
     const uint8_t* tab;
     int sumA, sumB;   // scores of this lane's rows at their best
+    static constexpr bool kRowBounds = true;
 
     __device__ __forceinline__ void check(const KParams& P, PairJob& J, int pair) const {
         // every pair of a pair-table item uses the table's scheme; anything
@@ -737,12 +740,13 @@ struct QprofScores {
     using Lds = QprofLds<W, R>;
     using Entry = uint16_t;
     static constexpr int kSide = 1;
-    static constexpr int kSets = R > 8 ? 2 : 1;
+    static constexpr int kSets = R > 8 ? 2 : 1, kCoopSets = 1;   // (never cooperative)
     static constexpr int RD = Lds::RD;
     uint32_t dA[RD], dB[RD];
     uint32_t xa[2], xb[2];
     const uint8_t* lprof;   // this lane's rows of residue 0
     int bound;
+    static constexpr bool kRowBounds = false;
 
     __device__ __forceinline__ void check(const KParams& P, PairJob& J, int pair) const {
         // every pair aligns the profiled query with the profile's scheme
@@ -796,16 +800,30 @@ __device__ __forceinline__ void push_redo(const KParams& P, int pair) {
     else atomicOr(&P.flags[kFlagInternal], 1);
 }
 
+// Exchange between the four wavefronts of a cooperative group (sw_coop.h).
+// ring[w][j % 128]: H - (o - e) and F of the row above wavefront w's first
+// row at column j, without drift; ring[0][0] is the matrix's top boundary.
+struct CoopX {
+    uint2 ring[kWavesPerBlock][128];
+    uint2 dump[128 + 64];                 // where the lanes that hand nothing on write
+    int32_t res[kWavesPerBlock][2][3];    // per wavefront and pair: best, row, column
+    int32_t item;
+};
+
 // One sweep of the wave item order[first .. first+count), two pairs per
-// W-lane group packed into int16 halves, scores from Src.
-template <class Src, int W, int R, bool REV, int C>
+// W-lane group packed into int16 halves, scores from Src.  With COOP the four
+// wavefronts of the workgroup sweep one item as a group of 256 lanes: this
+// wavefront is number `wave` of it (see sw_coop.h), W is 64.
+template <class Src, int W, int R, bool REV, int C, bool COOP = false>
 __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src::Lds& S, uint16_t* wbuf, int first,
-                                            int count, int lane) {
+                                            int count, int lane, CoopX* X = nullptr, int wave = 0) {
+    static_assert(!COOP || (W == 64 && C == 128), "a cooperative group is four 64-lane wavefronts");
     using Stager = RefStager<W, C>;
     using Entry = typename Src::Entry;
     constexpr uint32_t K2 = (uint32_t)kI16Bias * 0x10001u;
     const int g = lane / W;
     const int l = lane % W;
+    const int lr = COOP ? 64 * wave + l : l;   // lane within the pair's group: rows lr * R ..
 
     const int slot = g * 2;
     const int pairA = slot < count ? P.order[first + slot] : -1;
@@ -828,7 +846,7 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
     stA.load(P.refs, JA, P.order, 0, l);
     stB.load(P.refs, JB, P.order, 0, l);
     int bad = -1;
-    src.rows(P, S, JA, JB, l, bad);
+    src.rows(P, S, JA, JB, lr, bad);
     src.stage(stA, bufA, P, S, JA, 0, l, bad);
     src.stage(stB, bufB, P, S, JB, 0, l, bad);
 
@@ -856,7 +874,7 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
     // forward: v = ((H - (o - e) + x) << k) + row code, its largest per row,
     // and per pair and set of rows the key (largest v of a step << 16) |
     // (kColMax - column), largest first
-    constexpr int kSets = REV ? 1 : Src::kSets;
+    constexpr int kSets = REV ? 1 : COOP ? Src::kCoopSets : Src::kSets;
     constexpr int kQ = (R + kSets - 1) / kSets;      // rows of a set
     constexpr int kCode = kQ <= 1 ? 0 : kQ <= 2 ? 1 : kQ <= 4 ? 2 : kQ <= 8 ? 3 : kQ <= 16 ? 4 : 5;
     u16x2 best[REV ? 1 : R];
@@ -866,6 +884,17 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
     if constexpr (!REV) {
         int a, b;
         src.bounds(P, JA, JB, a, b);
+        if constexpr (COOP && Src::kRowBounds) {
+            // the bounds of the wavefronts' rows add up
+            X->res[wave][0][0] = a;
+            X->res[wave][1][0] = b;
+            __syncthreads();
+            a = b = 0;
+            for (int w = 0; w < kWavesPerBlock; ++w) {
+                a += X->res[w][0][0];
+                b += X->res[w][1][0];
+            }
+        }
         a = imax(a + x - (int)(goA - e), b + x - (int)(goB - e));
         k = __builtin_amdgcn_ballot_w64(((a + 1) << kCode) > 0x7C00) == 0 ? kCode : 0;
     }
@@ -891,21 +920,57 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
     const Entry* rB = bufB + W - l;
     uint32_t jc = (uint32_t)(kColMax + l);   // kColMax - j with j = t - l
 
+    // cooperative groups: blocks of `block` steps between workgroup barriers.
+    // Wavefront w starts `lag` blocks after the one above it, whose last lane
+    // is 63 columns behind its first: what a block reads was written in
+    // earlier ones.
+    const int block = COOP && period > 32 ? 32 : period;
+    const int lag = 63 / block + 2;
+    const int ring_mask = wave > 0 ? 127 : 0;
+    const int cols = __builtin_amdgcn_readfirstlane(mmax);
+    uint2 above = make_uint2(0, 0);
+    uint2* below = nullptr;
+    if constexpr (COOP) {
+        below = l == 63 && wave + 1 < kWavesPerBlock ? X->ring[wave + 1] : X->dump + l;
+        if (wave == 0) {
+            const uint32_t none = u32(pk(0) - c2);
+            X->ring[0][0] = make_uint2(none, none);
+            wave_lds_sync();
+        }
+        // (the barriers also show the top boundary to the wavefronts below)
+        for (int q = 0; q < lag * wave; ++q) __syncthreads();
+        above = X->ring[wave][0];
+    }
+
+    uint32_t zs[R + 2];   // z(r, t) of the even step t, for it and the odd step after it
     // Step tt of the chunk; zt = z(0, t).  Odd steps (PH = 1) also track the
     // even step before them (forward); at is that step's undrifting term.
-    auto step = [&](auto phase, int tt, uint32_t zt, uint32_t at) {
+    auto step = [&](auto phase, int t0, int tt, uint32_t zt, uint32_t at) {
         constexpr int PH = decltype(phase)::value;
         src.template step_begin<PH>(rA, rB, tt);
         // the row above the lane's block; above the group it is the matrix's
         // top boundary, H = 0 (z of row -1) and no F
         const uint32_t zup = s_sub(zt, e2);
-        const u16x2 top = pk(zup) - c2;
-        const u16x2 Hup = pk((uint32_t)shift_in_group<W>((int)u32(Hlast - lift), (int)u32(top)));
-        u16x2 F = pk((uint32_t)shift_in_group_zero<W>((int)u32(Flast - lift)));
+        u16x2 Hup, F;
+        if constexpr (COOP) {
+            // from the wavefront above, or the top boundary
+            Hup = pk((uint32_t)shift_in_group<W>((int)u32(Hlast - lift), (int)u32(pk(above.x) + pk(zup))));
+            F = pk((uint32_t)shift_in_group<W>((int)u32(Flast - lift), (int)u32(pk(above.y) + pk(zup))));
+            // (columns past the reference are not handed on)
+            above = t0 + tt + 1 < cols ? X->ring[wave][(tt + 1) & ring_mask] : X->ring[0][0];
+        } else {
+            const u16x2 top = pk(zup) - c2;
+            Hup = pk((uint32_t)shift_in_group<W>((int)u32(Hlast - lift), (int)u32(top)));
+            F = pk((uint32_t)shift_in_group_zero<W>((int)u32(Flast - lift)));
+        }
         u16x2 diag = Hup_prev;
         Hup_prev = Hup;
         u16x2 Hmu = Hup;
-        uint32_t z = zt;                    // becomes z(r, t + 1)
+        if constexpr (PH == 0 || R > 16) {   // (more rows would not leave enough scalar registers)
+            zs[0] = PH == 0 ? zt : zup;
+#pragma unroll
+            for (int r = 1; r < R + 2; ++r) zs[r] = s_add(zs[r - 1], e2);
+        }
         uint32_t a = at;
         u16x2 me[kSets], mo[kSets], pe[kSets], po[kSets], f = pk(0), pn = pk(0);
 #pragma unroll
@@ -917,8 +982,7 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
             diag = old;
             Hm[r] = hm;
             Hmu = hm;
-            z = s_add(z, e2);
-            E[r] = pk_max3(E[r], hm, pk(z));
+            E[r] = pk_max3(E[r], hm, pk(zs[r + 1 + PH]));
             if constexpr (REV) {
                 if (r % 8 == 0 && r > 0) f = f + pk(e8);
                 if (r == 0) f = hm;
@@ -950,6 +1014,11 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
         Hlast = Hm[R - 1];
         Flast = F;
         src.template step_end<PH>(rA, rB, tt);
+        if constexpr (COOP) {
+            // the last lane hands its last row on: column t - 63, drift off
+            const u16x2 zl = pk(zs[R - 1 + PH]);
+            below[(tt + 65) & 127] = make_uint2(u32(Hlast - zl), u32(Flast - zl));
+        }
         if constexpr (REV) {
             // the last group of 8 rows starts at row 8 * ((R - 1) / 8)
             uint32_t zg = zt;
@@ -999,12 +1068,12 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
         }
         const int tn = __builtin_amdgcn_readfirstlane(steps - t0 < C ? steps - t0 : C);
         src.begin(rA, rB);
-        for (int s0 = 0; s0 < tn; s0 += period) {
-            const int s1 = tn - s0 < period ? tn : s0 + period;
+        for (int s0 = 0; s0 < tn; s0 += block) {
+            const int s1 = tn - s0 < block ? tn : s0 + block;
             uint32_t zt = z0, at = a0;
             for (int tt = s0; tt < s1; tt += 2) {
-                step(std::integral_constant<int, 0>{}, tt, zt, at);
-                step(std::integral_constant<int, 1>{}, tt + 1, zt + e2, at);
+                step(std::integral_constant<int, 0>{}, t0, tt, zt, at);
+                step(std::integral_constant<int, 1>{}, t0, tt + 1, zt + e2, at);
                 zt += 2u * e2;
                 at -= 2u * ek;
             }
@@ -1018,6 +1087,7 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
             Hlast = Hm[R - 1];
             Flast = Flast - back;
             Hup_prev = Hup_prev - back;
+            if constexpr (COOP) __syncthreads();
         }
         if (more) {
             wave_lds_sync();
@@ -1027,9 +1097,11 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
         }
     }
     set_flag(P.flags, kFlagBadResidue, (bad >= 0) & (P.validate != 0));
+    if constexpr (COOP)
+        for (int q = 0; q < lag * (kWavesPerBlock - 1 - wave); ++q) __syncthreads();
 
     if constexpr (REV) {
-        int row[2] = {rowA < R ? l * R + rowA : kNoRow, rowB < R ? l * R + rowB : kNoRow}, col[2] = {colA, colB};
+        int row[2] = {rowA < R ? lr * R + rowA : kNoRow, rowB < R ? lr * R + rowB : kNoRow}, col[2] = {colA, colB};
 #pragma unroll
         for (int p = 0; p < 2; ++p)
             for (int off = 1; off < W; off <<= 1) {
@@ -1038,7 +1110,17 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
                 col[p] = oi < row[p] ? oj : col[p];
                 row[p] = oi < row[p] ? oi : row[p];
             }
-        if (l == 0) {
+        if constexpr (COOP) {
+            // upper wavefronts hold upper rows
+#pragma unroll
+            for (int p = 0; p < 2; ++p) { X->res[wave][p][1] = row[p]; X->res[wave][p][2] = col[p]; }
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+                for (int w = kWavesPerBlock - 1; w >= 0; --w)
+                    if (X->res[w][p][1] != kNoRow) { row[p] = X->res[w][p][1]; col[p] = X->res[w][p][2]; }
+        }
+        if (lr == 0) {
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 const int pair = p == 0 ? pairA : pairB;
@@ -1072,7 +1154,7 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             lj[p] = lb[p] > 0 ? kColMax - (lj[p] & 0x7FFF) : -1;
-            li[p] = lb[p] > 0 ? l * R + li[p] : -1;
+            li[p] = lb[p] > 0 ? lr * R + li[p] : -1;
         }
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
@@ -1086,7 +1168,26 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
                 lj[p] = take ? oj : lj[p];
             }
         }
-        if (l == 0) {
+        if constexpr (COOP) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                X->res[wave][p][0] = lb[p];
+                X->res[wave][p][1] = li[p];
+                X->res[wave][p][2] = lj[p];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                lb[p] = 0;
+                for (int w = 0; w < kWavesPerBlock; ++w)
+                    if (X->res[w][p][0] > lb[p]) {
+                        lb[p] = X->res[w][p][0];
+                        li[p] = X->res[w][p][1];
+                        lj[p] = X->res[w][p][2];
+                    }
+            }
+        }
+        if (lr == 0) {
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 const int pair = p == 0 ? pairA : pairB;
