@@ -208,6 +208,12 @@ struct ClassifyArgs {
 
 #include <hip/hip_runtime_api.h>
 
+struct sw_handle;
+// Fix the built-in int16 routing to the one for calls of `pairs` pairs (for a
+// server's handles, whose one captured graph serves calls of every size).
+// A handle with a routing table of its own keeps it.
+void pin_routing(sw_handle* h, int64_t pairs);
+
 namespace sw {
 
 // A compiled queue kernel: it aligns the work items [meta[lo_idx],

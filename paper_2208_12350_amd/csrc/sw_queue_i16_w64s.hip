@@ -1,6 +1,7 @@
 // sw_queue_i16_w64s.hip -- queue kernels of the packed int16 sweep shapes with
-// 64-lane groups, 4, 6 and 8 rows per lane (queries up to 512 residues, in small batches): table-lookup, column-word, pair-table and (forward only) query-profile
-// kernels, forward and reverse.
+// 64-lane groups, 4, 6 and 8 rows per lane (queries up to 512 residues in
+// small batches): table-lookup, column-word, pair-table and (forward only)
+// query-profile kernels, forward and reverse.
 #include "sw_queue.h"
 
 namespace sw {

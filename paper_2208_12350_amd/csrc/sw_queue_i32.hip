@@ -41,6 +41,8 @@ extern const KernelEntry kI16W32bKernels[];
 extern const int kNumI16W32bKernels;
 extern const KernelEntry kI16W64Kernels[];
 extern const int kNumI16W64Kernels;
+extern const KernelEntry kI16W64sKernels[];
+extern const int kNumI16W64sKernels;
 extern const KernelEntry kI16W64LongKernels[];
 extern const int kNumI16W64LongKernels;
 extern const KernelEntry kI16W256Kernels[];
@@ -51,6 +53,7 @@ extern const FamilyEntry kI16W32Family;
 extern const FamilyEntry kI16W32bFamily;
 extern const FamilyEntry kI16W64Family;
 extern const FamilyEntry kI16W64LongFamily;
+extern const FamilyEntry kI16W64sFamily;
 extern const FamilyEntry kI16W256Family;
 
 namespace {
@@ -66,11 +69,12 @@ Table table(int k) {
         case 4: return {kI16W64Kernels, kNumI16W64Kernels};
         case 5: return {kI16W64LongKernels, kNumI16W64LongKernels};
         case 6: return {kI16W256Kernels, kNumI16W256Kernels};
+        case 7: return {kI16W64sKernels, kNumI16W64sKernels};
         default: return {kI32Kernels, (int)(sizeof(kI32Kernels) / sizeof(kI32Kernels[0]))};
     }
 }
 
-constexpr int kTables = 8;
+constexpr int kTables = 9;
 ShapeDesc g_shapes[kMaxBins];
 int g_nshapes = 0;
 
@@ -89,9 +93,9 @@ const ShapeDesc* compiled_shapes(int* n) {
 }
 
 const FamilyEntry* shape_family(int prec, int W, int R) {
-    const FamilyEntry* fams[] = {&kI16W16Family, &kI16W16bFamily, &kI16W32Family, &kI16W32bFamily, &kI16W64Family,
-                                 &kI16W64LongFamily, &kI16W256Family, &kI32W16Family, &kI32W64Family,
-                                 &kI32W64LongFamily};
+    const FamilyEntry* fams[] = {&kI16W16Family, &kI16W16bFamily, &kI16W32Family, &kI16W32bFamily, &kI16W64sFamily,
+                                 &kI16W64Family, &kI16W64LongFamily, &kI16W256Family, &kI32W16Family,
+                                 &kI32W64Family, &kI32W64LongFamily};
     for (const FamilyEntry* f : fams)
         if (f->prec == prec && f->W == W)
             for (int k = 0; k < f->n; ++k)

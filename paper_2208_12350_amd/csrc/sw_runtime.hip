@@ -75,7 +75,12 @@ struct Workspace {
     int64_t cap;
 };
 
-constexpr int kLutEntries = 2 * kLutRows;
+constexpr int kLutEntries = 2 * kLutRows;   // per size class
+
+// Size classes of a call, by its pairs: the built-in int16 routing differs
+// between them (see class_bin).
+constexpr int kRouteClasses = 4;
+int route_class(int64_t pairs) { return pairs <= 4096 ? 0 : pairs <= 8192 ? 1 : pairs <= 262144 ? 2 : 3; }
 constexpr int kCtrBase = 16;     // int index of the first 64-bit counter
 constexpr int kSmallInts = kCtrBase + 2 * kNumCounters;   // flags [0, kNumFlags) | counters
 
@@ -103,6 +108,7 @@ struct GraphKey {
     int32_t qprof_n;       // a profile is built for this query length (a kernel argument)
     int32_t search_n;      // every pair's query length (a search: one forward bin), or -1
     int32_t max_query;     // the max_query option (bins above it are not launched)
+    int32_t route_class;   // size class of the built-in routing
 };
 
 }  // namespace
@@ -118,13 +124,15 @@ struct sw_handle {
     int64_t opt_timing = 0;
     int64_t opt_streams = 4;
     int64_t opt_max_query = 0;          // 0, or the caller's bound on query lengths
-    std::vector<int> bin_min_query;     // per bin: the shortest query any route sends to it
+    std::vector<int> bin_min_query[kRouteClasses];   // per bin: the shortest query any route sends to it
     int64_t opt_colpath = 1;
 
     std::vector<BinInfo> bins;
     std::vector<int> route[2];          // per precision (int16, int32) and 16-row bucket: bin
-    std::vector<int8_t> lut;            // device copy of route
-    std::vector<char> bin_used;         // bins some route points at
+    bool builtin16 = true;              // int16 routing is the built-in one (by batch size, see class_bin)
+    std::vector<int> class_route[kRouteClasses][2];   // the routing that calls of a size class use
+    std::vector<int8_t> lut;            // device copy of class_route
+    std::vector<char> bin_used[kRouteClasses];   // bins some route points at
     bool lut_dirty = true;
     std::vector<int> resident_blocks[2][2][kNumVars];   // per tile, pass, score source and bin: workgroups the device holds at once
     std::vector<std::pair<QueueFn, int>> fam_resident;  // per family kernel: workgroups the device holds at once
@@ -335,19 +343,55 @@ static void default_routing(sw_handle* h, int sel) {
     }
 }
 
+// Bin of the built-in int16 routing for queries of up to `rows` residues (a
+// multiple of 16) in calls of one size class.  The device runs 1024
+// wavefronts at once, one on each SIMD, before they share SIMDs, so with few
+// pairs the time is that of one sweep and not of the cells:
+//   * 129..512 rows: up to 4096 pairs 64-lane groups of 4..8 rows (two pairs
+//     a wavefront and short steps: 250 DNA residues, 1000 pairs 421 us
+//     against 456 in 32 lanes and 520 in 16; 500 residues 649 against 735),
+//     up to 8192 pairs 32-lane groups (250 protein residues 686 us against
+//     814 in 16 lanes and 699 in 64), above that the shape with the fewest
+//     lane-row slots (default_routing; 250 DNA residues, 16384 pairs 886 us
+//     against 947 and 1016).  Up to 128 rows that shape is as good in calls
+//     of every size (100 residues: 240 us against 262 in 64 lanes);
+//   * long queries take cooperative groups, whose sweep of a pair is about
+//     four times shorter, until there are enough of them to fill the device
+//     with 64-lane groups, which need fewer instructions per cell: above 512
+//     rows up to 8192 pairs (1000 DNA residues 4.05 ms against 4.38; 16384
+//     pairs 7.36 against 6.68), above 1024 rows up to 262144 pairs (2000
+//     residues, 16384 pairs: 22.0 against 22.8).  Batches of more pairs have
+//     enough of every length.
+static int class_bin(const sw_handle* h, int cls, int rows) {
+    const int base = h->route[0][rows / 16 - 1];
+    int W = 0, step = 1;
+    if (rows > 512) W = cls <= 1 || (cls == 2 && rows > 1024) ? 256 : 64;
+    else if (rows > 128 && cls == 0) { W = 64; step = 2; }
+    else if (rows > 128 && cls == 1) { W = 32; step = 2; }
+    if (W == 0) return base;
+    const int R = ((rows + W - 1) / W + step - 1) / step * step;
+    const int b = find_bin(h, 16, W, R);
+    return b >= 0 ? b : base;
+}
+
 static void rebuild_lut(sw_handle* h) {
-    h->lut.assign(kLutEntries, -1);
-    h->bin_used.assign(h->bins.size(), 0);
-    h->bin_min_query.assign(h->bins.size(), SW_MAX_QUERY + 1);
-    for (int sel = 0; sel < 2; ++sel)
-        for (int k = 0; k < kLutRows; ++k) {
-            const int b = h->route[sel][k];
-            h->lut[sel * kLutRows + k] = (int8_t)b;
-            if (b >= 0) {
-                h->bin_used[b] = 1;
-                h->bin_min_query[b] = std::min(h->bin_min_query[b], 16 * k + 1);
+    h->lut.assign(kRouteClasses * kLutEntries, -1);
+    for (int c = 0; c < kRouteClasses; ++c) {
+        h->bin_used[c].assign(h->bins.size(), 0);
+        h->bin_min_query[c].assign(h->bins.size(), SW_MAX_QUERY + 1);
+        for (int sel = 0; sel < 2; ++sel) {
+            h->class_route[c][sel].assign(kLutRows, -1);
+            for (int k = 0; k < kLutRows; ++k) {
+                const int b = sel == 0 && h->builtin16 ? class_bin(h, c, 16 * (k + 1)) : h->route[sel][k];
+                h->class_route[c][sel][k] = b;
+                h->lut[c * kLutEntries + sel * kLutRows + k] = (int8_t)b;
+                if (b >= 0) {
+                    h->bin_used[c][b] = 1;
+                    h->bin_min_query[c][b] = std::min(h->bin_min_query[c][b], 16 * k + 1);
+                }
             }
         }
+    }
     h->lut_dirty = true;
 }
 
@@ -359,6 +403,7 @@ static int set_routing(sw_handle* h, int sel, const int32_t* rows_max, const int
     const int prec = sel == 0 ? 16 : 32;
     if (n == 0) {
         default_routing(h, sel);
+        if (sel == 0) h->builtin16 = true;
         rebuild_lut(h);
         return SW_OK;
     }
@@ -381,6 +426,7 @@ static int set_routing(sw_handle* h, int sel, const int32_t* rows_max, const int
     }
     if (prev != SW_MAX_QUERY) return fail(h, SW_EINVAL, "routing must end at rows_max = %d", SW_MAX_QUERY);
     for (int k = 0; k < kLutRows; ++k) h->route[sel][k] = r[k];
+    if (sel == 0) h->builtin16 = false;
     rebuild_lut(h);
     return SW_OK;
 }
@@ -482,12 +528,13 @@ static int narrow_tile(const sw_handle* h, const BinInfo& e, int var) {
 // Enqueue one pass (planning + sweeps).  Plain mode synchronises `stream`
 // once to read the per-bin item counts.
 static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Workspace& ws, int pass,
-                        hipStream_t stream, bool timing, int64_t search_n) {
+                        hipStream_t stream, bool timing, int64_t search_n, int cls) {
     K.reverse = pass;
+    const int8_t* lut = h->d_lut + cls * kLutEntries;
     const int64_t cap = ws.cap;
     const int n_bins = (int)h->bins.size();
     HIP_TRY(h, launch_reset(h->d_hist, kHistSize, stream));
-    HIP_TRY(h, launch_classify(K, C, h->d_lut, h->d_bins, cap, ws.keys, h->d_hist, counters(h->d_small), stream));
+    HIP_TRY(h, launch_classify(K, C, lut, h->d_bins, cap, ws.keys, h->d_hist, counters(h->d_small), stream));
     HIP_TRY(h, launch_plan_bins(h->d_bins, n_bins, h->d_hist, h->d_meta, counters(h->d_small), pass, stream));
     HIP_TRY(h, launch_scatter(ws.keys, h->d_n, cap, h->d_hist, ws.order, stream));
     HIP_TRY(h, launch_items(h->d_meta, h->d_bins, n_bins, h->d_n, cap, ws.items, stream));
@@ -534,13 +581,13 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         int only16 = -1, only32 = -1;
         const bool one_length = pass == 0 && search_n >= 1 && search_n <= SW_MAX_QUERY;
         if (one_length) {
-            only16 = h->route[0][(search_n - 1) / 16];
-            only32 = h->route[1][(search_n - 1) / 16];
+            only16 = h->class_route[cls][0][(search_n - 1) / 16];
+            only32 = h->class_route[cls][1][(search_n - 1) / 16];
         }
         std::vector<char> launchable(n_bins, 0);
         for (int b = 0; b < n_bins; ++b)
-            launchable[b] = h->bin_used[b] && !(one_length && b != only16 && b != only32) &&
-                            !(h->opt_max_query > 0 && h->bin_min_query[b] > h->opt_max_query);
+            launchable[b] = h->bin_used[cls][b] && !(one_length && b != only16 && b != only32) &&
+                            !(h->opt_max_query > 0 && h->bin_min_query[cls][b] > h->opt_max_query);
         // Family launches (default tile): one kernel per family, score
         // source and pass takes the items of all its launchable member bins;
         // the bins it covers get no launch of their own below.
@@ -651,7 +698,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
     }
     // pairs whose drifted forward sweep left the end column open
     if (pass == 1 && K.redo)
-        HIP_TRY(h, launch_redo(K, h->d_lut, h->d_bins, counters(h->d_small), 2 * std::max(1, h->n_cu), stream));
+        HIP_TRY(h, launch_redo(K, lut, h->d_bins, counters(h->d_small), 2 * std::max(1, h->n_cu), stream));
     if (timing) HIP_TRY(h, hipEventRecord(h->ev[pass == 0 ? 2 : 4], stream));
     return SW_OK;
 }
@@ -728,6 +775,13 @@ static bool init_paths(sw_handle* h) {
     return ok;
 }
 
+void pin_routing(sw_handle* h, int64_t pairs) {
+    if (!h->builtin16) return;
+    h->route[0] = h->class_route[route_class(pairs)][0];
+    h->builtin16 = false;
+    rebuild_lut(h);
+}
+
 extern "C" {
 
 sw_handle* sw_create(int device, const char* tuning) {
@@ -752,11 +806,11 @@ sw_handle* sw_create(int device, const char* tuning) {
     rebuild_lut(h);
     ok = ok && h->bins.size() <= (size_t)kMaxBins &&
          hipMalloc(&h->d_mats, kSchemeBytes) == hipSuccess &&
-         hipMalloc(&h->d_lut, kLutEntries) == hipSuccess &&
+         hipMalloc(&h->d_lut, kRouteClasses * kLutEntries) == hipSuccess &&
          hipMalloc(&h->d_bins, kMaxBins * sizeof(BinInfo)) == hipSuccess &&
          hipMalloc(&h->d_small, kSmallInts * 4) == hipSuccess &&
          hipMalloc(&h->d_n, 16) == hipSuccess &&
-         hipHostMalloc(&h->h_lut, kLutEntries, hipHostMallocDefault) == hipSuccess &&
+         hipHostMalloc(&h->h_lut, kRouteClasses * kLutEntries, hipHostMallocDefault) == hipSuccess &&
          hipMalloc(&h->d_hist, kHistSize * 4) == hipSuccess &&
          hipMalloc(&h->d_meta, kMetaSize * 4) == hipSuccess &&
          hipHostMalloc(&h->h_small, kSmallInts * 4, hipHostMallocDefault) == hipSuccess &&
@@ -1130,15 +1184,15 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
         // marked dirty: the next graph-capable call must still drop its
         // graphs (which launch the bins of the old table) and upload it again
         if (h->lut_dirty) {
-            memcpy(h->h_lut, h->lut.data(), kLutEntries);
-            HIP_TRY(h, hipMemcpyAsync(h->d_lut, h->h_lut, kLutEntries, hipMemcpyHostToDevice, stream));
+            memcpy(h->h_lut, h->lut.data(), h->lut.size());
+            HIP_TRY(h, hipMemcpyAsync(h->d_lut, h->h_lut, h->lut.size(), hipMemcpyHostToDevice, stream));
         }
     } else {
         int rc = ensure_pairs(h, P);
         if (rc != SW_OK) return rc;
         if (h->lut_dirty) {
             drop_graph(h);
-            HIP_TRY(h, hipMemcpy(h->d_lut, h->lut.data(), kLutEntries, hipMemcpyHostToDevice));
+            HIP_TRY(h, hipMemcpy(h->d_lut, h->lut.data(), h->lut.size(), hipMemcpyHostToDevice));
             h->lut_dirty = false;
         }
         ws.keys = h->d_keys;
@@ -1278,6 +1332,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
         h->last_col_ok[s] = K.col_ok[s];
     }
 
+    const int cls = route_class(P);
     const bool use_graph = h->opt_mode == 1 && h->opt_graph != 0 && !timing && !no_alloc;
     GraphKey key;
     memset(&key, 0, sizeof(key));
@@ -1295,6 +1350,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     key.qprof_n = K.qprof_n;
     key.search_n = (int32_t)std::max<int64_t>(-1, std::min<int64_t>(search_n, SW_MAX_QUERY + 1));
     key.max_query = C.max_query;
+    key.route_class = h->builtin16 ? cls : 0;
 
     // Start of the call, in stream order and outside any graph: the scheme
     // tables when they differ from what the device holds (from this call's
@@ -1312,9 +1368,9 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     HIP_TRY(h, launch_call_start(h->d_small, kSmallInts, h->d_n, (int32_t)P, stream));
 
     auto enqueue_all = [&](hipStream_t es) -> int {
-        const int rc0 = enqueue_pass(h, K, C, ws, 0, es, timing, search_n);
+        const int rc0 = enqueue_pass(h, K, C, ws, 0, es, timing, search_n, cls);
         if (rc0 != SW_OK) return rc0;
-        return enqueue_pass(h, K, C, ws, 1, es, timing, search_n);
+        return enqueue_pass(h, K, C, ws, 1, es, timing, search_n, cls);
     };
     if (timing) h->bin_launched.assign(2 * kMaxBins * 2, 0);
     int gi = -1;

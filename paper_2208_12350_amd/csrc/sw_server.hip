@@ -73,16 +73,14 @@ __global__ void gather_spans_kernel(const Seg* segs, const uint8_t* pool, int64_
 }
 
 // Batches of at most kLatencyPairs pairs (a request or a few, at low load)
-// run on a slot's latency handle, whose routing has few bins: 16x16 up to
-// 256 rows, 32x16 up to 512, and one cooperative 256-lane shape (8 rows per
-// lane) above.  The sweeps of a pass run bin by bin on each of a handle's
-// streams, so a small batch waits for the sum of its bins' longest pairs;
-// with three bins that sum is about half of the default routing's (single
-// mixed requests: 6.4 ms against 13 ms at the median).  Larger merged
-// batches run on the throughput handle, with the routing of the server's
-// tuning string (or the built-in one).
+// run on a slot's latency handle, whose routing has few bins with short
+// sweeps: 64-lane groups of few rows up to 512 rows and cooperative 256-lane
+// groups above.  Its graph is captured once for every batch size.  Larger
+// merged batches run on the throughput handle, with the routing of the
+// server's tuning string (or the built-in one).
 constexpr int64_t kLatencyPairs = 8192;
-constexpr const char* kLatencyRoute = "route16=16x16@256/32x16@512/256x8@2048";
+constexpr const char* kLatencyRoute =
+    "route16=16x8@128/64x4@256/64x6@384/64x8@512/256x3@768/256x4@1024/256x6@1536/256x8@2048";
 
 struct Slot {
     sw_handle* h = nullptr;       // throughput handle
@@ -317,6 +315,7 @@ sw_server* sw_server_create(int device, const sw_scheme* schemes, int n_schemes,
         std::unique_ptr<Slot> sl(new Slot());
         sl->h = sw_create(device, tuning);
         sl->hl = sw_create(device, lat_tuning.c_str());
+        if (sl->h) pin_routing(sl->h, std::min<int64_t>(max_batch_pairs, 262144));
         ok = sl->h && sl->hl && sw_set_option(sl->h, "capacity", max_batch_pairs) == SW_OK &&
              sw_set_option(sl->hl, "capacity", std::min<int64_t>(max_batch_pairs, kLatencyPairs)) == SW_OK &&
              hipStreamCreateWithFlags(&sl->stream, hipStreamNonBlocking) == hipSuccess &&
