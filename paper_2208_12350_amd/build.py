@@ -14,8 +14,8 @@ PROBE_LIB = os.path.join(HERE, "libswprobe.so")
 STENCIL_LIB = os.path.join(HERE, "libswstencil.so")
 SOURCES = ["sw_plan.hip", "sw_queue_i16_w16.hip", "sw_queue_i16_w16b.hip", "sw_queue_i16_w32.hip",
            "sw_queue_i16_w32b.hip", "sw_queue_i16_w64.hip", "sw_queue_i16_w64s.hip", "sw_queue_i16_w64_long.hip",
-           "sw_queue_i16_w256.hip", "sw_queue_i32.hip", "sw_queue_redo.hip", "sw_trace.hip", "sw_runtime.hip",
-           "sw_server.hip"]
+           "sw_queue_i16_w256.hip", "sw_queue_i32.hip", "sw_queue_i32_all.hip", "sw_queue_redo.hip", "sw_trace.hip",
+           "sw_runtime.hip", "sw_server.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950",

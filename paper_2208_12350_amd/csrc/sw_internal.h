@@ -46,7 +46,10 @@ constexpr int kWavesPerBlock = kBlock / 64;
 constexpr int kMaxBins = 80;
 constexpr int kMBuckets = 1024;                        // length buckets per bin
 constexpr int kTrivialKey = kMaxBins * kMBuckets;      // empty / invalid pairs
-constexpr int kHistSize = kTrivialKey + 1;
+// the key histogram, followed by every bin's pairs and column-path pairs
+constexpr int kHistPairs = kTrivialKey;
+constexpr int kHistCol = kHistPairs + kMaxBins;
+constexpr int kHistSize = kHistCol + kMaxBins;
 
 // Reference length -> bucket within one half of a bin's key range,
 // monotone: exact below 256, then 32 buckets per octave (width <= 1/32 of
@@ -60,9 +63,11 @@ __host__ __device__ inline int m_bucket(int m) {
     return b < kMHalf ? b : kMHalf - 1;
 }
 
-// Most shapes one family kernel serves (one lane width, a run of rows per
-// lane).
-constexpr int kFamilyMax = 12;
+// Most shapes one family kernel serves.
+constexpr int kFamilyMax = 18;
+
+// A classified pair: its key and its rank among the pairs of that key.
+struct PairKey { int32_t key, rank; };
 
 struct BinInfo {
     uint8_t prec;     // 16 = two pairs per lane group packed in int16 halves, 32 = int32
@@ -234,35 +239,41 @@ QueueFn shape_kernel(int prec, int W, int R, bool reverse, int var = kVarTable, 
 // `rows[0..n)` are its members' rows per lane, largest first (the order of
 // KParams::fam_bins), and k[var][reverse] its kernels (kVarTable, kVarCol,
 // kVarPtab; null where there is none).
-struct FamilyEntry { int prec, W, n; int rows[kFamilyMax]; QueueFn k[3][2]; int waves[3]; int tile[3]; };
-const FamilyEntry* shape_family(int prec, int W, int R);
+// (W: lanes of its shapes, or 0 where they differ: lanes_of)
+struct FamilyEntry {
+    int prec, W, n;
+    int rows[kFamilyMax];
+    QueueFn k[3][2];
+    int waves[3];
+    int tile[3];
+    int lanes[kFamilyMax];
+    int lanes_of(int k_) const { return W ? W : lanes[k_]; }
+};
+// (only32: every pair of the call is int32)
+const FamilyEntry* shape_family(int prec, int W, int R, bool only32);
 const ShapeDesc* compiled_shapes(int* n);
 
 hipError_t launch_reset(int32_t* p, int n, hipStream_t s);
 // Pairs on the redo list, after the reverse sweeps (sw_queue_redo.hip).
 hipError_t launch_redo(const KParams& P, const int8_t* lut, const BinInfo* bins, unsigned long long* counters,
                        int blocks, hipStream_t s);
-// Start of an alignment call: small[0..n_small) = 0 (flags and counters) and
+// Start of an alignment call: small[0..n_small) = 0 (flags and counters),
+// hist[0..n_hist) = 0 (n_hist >= n_small; a histogram per pass) and
 // *n_dev = n_pairs.
-hipError_t launch_call_start(int32_t* small, int n_small, int32_t* n_dev, int32_t n_pairs, hipStream_t s);
+hipError_t launch_call_start(int32_t* small, int n_small, int32_t* hist, int n_hist, int32_t* n_dev, int32_t n_pairs,
+                             hipStream_t s);
 // beg[0..n) = 0, end[0..n) = len (the query spans of a database search)
 hipError_t launch_fill_span(int64_t* beg, int64_t* end, int64_t n, int64_t len, hipStream_t s);
 // The planning launches are sized for `cap` pairs; the kernels take the
 // batch size from device memory (P.n_dev / n_dev), so a captured graph can be
 // replayed for any batch of at most `cap` pairs.
 hipError_t launch_classify(const KParams& P, const ClassifyArgs& C, const int8_t* lut, const BinInfo* bins,
-                           int64_t cap, int32_t* keys, int32_t* hist,
+                           int64_t cap, PairKey* keys, int32_t* hist,
                            unsigned long long* counters, hipStream_t s);
-hipError_t launch_plan(const BinInfo* bins, int n_bins, int32_t* hist, int32_t* meta,
-                       hipStream_t s);
-// The same plan for a score pass, one workgroup per bin, from the pass's
-// per-bin pair counters that launch_classify accumulates.
-hipError_t launch_plan_bins(const BinInfo* bins, int n_bins, int32_t* hist, int32_t* meta,
-                            const unsigned long long* counters, int reverse, hipStream_t s);
-hipError_t launch_scatter(const int32_t* keys, const int32_t* n_dev, int64_t cap, int32_t* hist,
-                          int32_t* order, hipStream_t s);
-hipError_t launch_items(const int32_t* meta, const BinInfo* bins, int n_bins, const int32_t* n_dev,
-                        int64_t cap, WorkItem* items, hipStream_t s);
+hipError_t launch_plan_bins(const BinInfo* bins, int n_bins, int32_t* hist, int32_t* meta, hipStream_t s);
+hipError_t launch_scatter(const PairKey* keys, const int32_t* meta, const BinInfo* bins, int n_bins,
+                          const int32_t* n_dev, int64_t cap, const int32_t* hist, int32_t* order, WorkItem* items,
+                          hipStream_t s);
 
 // ---- alignment paths (sw_trace.hip) ----------------------------------------
 // The path of a pair is recovered in its result box a[q_start..q_end] x
@@ -309,7 +320,7 @@ hipError_t launch_trace_sizes(const KParams& P, const TraceArgs& T, int64_t cap,
                               int64_t* block_sums, unsigned long long* counters, hipStream_t s);
 // Planning of one chunk; in chunk 0 it also sets path_len = 0 for pairs
 // without an alignment.
-hipError_t launch_trace_classify(const KParams& P, const TraceArgs& T, int64_t cap, int32_t* keys,
+hipError_t launch_trace_classify(const KParams& P, const TraceArgs& T, int64_t cap, PairKey* keys,
                                  int32_t* hist, unsigned long long* counters, int32_t* path_len, hipStream_t s);
 // Walks of the pairs of one path-sweep bin (after the bin's sweep).
 hipError_t launch_trace_walk(const KParams& P, const TraceArgs& T, int bin, int blocks, int active,

@@ -41,7 +41,7 @@ std::mutex g_capture_mu;   // one graph capture at a time in the process
 // device when the first handle on that device is created.
 constexpr int64_t kStaticPairs = SW_NOALLOC_MAX_PAIRS;
 constexpr int64_t kStaticKeys = 0;
-constexpr int64_t kStaticOrder = kStaticKeys + 4 * kStaticPairs;
+constexpr int64_t kStaticOrder = kStaticKeys + (int64_t)sizeof(PairKey) * kStaticPairs;
 constexpr int64_t kStaticItems = kStaticOrder + 4 * kStaticPairs;
 constexpr int64_t kStaticBytes = kStaticItems + (kStaticPairs + kMaxBins) * (int64_t)sizeof(WorkItem);
 static __device__ __align__(256) uint8_t scratch[kStaticBytes];
@@ -69,7 +69,7 @@ static uint8_t* scratch_address(int device) {
 // or the static array of sw_align_batch_noalloc.  Launch grids are sized for
 // `cap` pairs.
 struct Workspace {
-    int32_t* keys;
+    PairKey* keys;
     int32_t* order;
     WorkItem* items;
     int64_t cap;
@@ -150,7 +150,7 @@ struct sw_handle {
     int32_t* d_n = nullptr;       // batch size, written by the call-start kernel of each call
     int32_t* d_hist = nullptr;
     int32_t* d_meta = nullptr;
-    int32_t* d_keys = nullptr;
+    PairKey* d_keys = nullptr;
     int32_t* d_order = nullptr;
     WorkItem* d_items = nullptr;
     int64_t cap_pairs = 0;
@@ -481,10 +481,10 @@ static int ensure_pairs(sw_handle* h, int64_t n) {
     if (n <= h->cap_pairs) return SW_OK;
     drop_graph(h);
     free_dev(h->d_keys); free_dev(h->d_order); free_dev(h->d_items);
-    h->d_keys = h->d_order = nullptr; h->d_items = nullptr;
+    h->d_keys = nullptr; h->d_order = nullptr; h->d_items = nullptr;
     h->cap_pairs = 0;
     const int64_t cap = std::max<int64_t>(n, 4096);
-    if (hipMalloc(&h->d_keys, cap * 4) != hipSuccess || hipMalloc(&h->d_order, cap * 4) != hipSuccess ||
+    if (hipMalloc(&h->d_keys, cap * sizeof(PairKey)) != hipSuccess || hipMalloc(&h->d_order, cap * 4) != hipSuccess ||
         hipMalloc(&h->d_items, (cap + kMaxBins) * sizeof(WorkItem)) != hipSuccess)
         return fail(h, SW_ENOMEM, "device allocation of %lld pair slots failed", (long long)cap);
     h->cap_pairs = cap;
@@ -533,11 +533,10 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
     const int8_t* lut = h->d_lut + cls * kLutEntries;
     const int64_t cap = ws.cap;
     const int n_bins = (int)h->bins.size();
-    HIP_TRY(h, launch_reset(h->d_hist, kHistSize, stream));
-    HIP_TRY(h, launch_classify(K, C, lut, h->d_bins, cap, ws.keys, h->d_hist, counters(h->d_small), stream));
-    HIP_TRY(h, launch_plan_bins(h->d_bins, n_bins, h->d_hist, h->d_meta, counters(h->d_small), pass, stream));
-    HIP_TRY(h, launch_scatter(ws.keys, h->d_n, cap, h->d_hist, ws.order, stream));
-    HIP_TRY(h, launch_items(h->d_meta, h->d_bins, n_bins, h->d_n, cap, ws.items, stream));
+    int32_t* hist = h->d_hist + pass * kHistSize;   // cleared at the start of the call
+    HIP_TRY(h, launch_classify(K, C, lut, h->d_bins, cap, ws.keys, hist, counters(h->d_small), stream));
+    HIP_TRY(h, launch_plan_bins(h->d_bins, n_bins, hist, h->d_meta, stream));
+    HIP_TRY(h, launch_scatter(ws.keys, h->d_meta, h->d_bins, n_bins, h->d_n, cap, hist, ws.order, ws.items, stream));
     const bool per_bin = timing && h->opt_timing == 2;
     if (h->bin_launch.size() != (size_t)(2 * kMaxBins * 2)) {
         h->bin_launch.assign(2 * kMaxBins * 2, -1);
@@ -587,6 +586,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         std::vector<char> launchable(n_bins, 0);
         for (int b = 0; b < n_bins; ++b)
             launchable[b] = h->bin_used[cls][b] && !(one_length && b != only16 && b != only32) &&
+                            !(C.i16_limit < 0 && h->bins[b].prec == 16) &&   // (max_score is at least 1)
                             !(h->opt_max_query > 0 && h->bin_min_query[cls][b] > h->opt_max_query);
         // Family launches (default tile): one kernel per family, score
         // source and pass takes the items of all its launchable member bins;
@@ -595,16 +595,21 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         int fam_slot = 0;
         if (h->opt_families && h->opt_chunk == kChunk) {
             std::vector<const FamilyEntry*> seen;
-            for (int b = 0; b < n_bins; ++b) {
+            for (int b1 = 0; b1 < n_bins; ++b1) {
+                // the launch with most of the pairs first: the narrow shapes
+                // when every pair is int32 (10,007 protein pairs 1.97 ms,
+                // 2.16 with the wide ones first)
+                const int b = C.i16_limit < 0 ? n_bins - 1 - b1 : b1;
                 if (!launchable[b]) continue;
-                const FamilyEntry* f = shape_family(h->bins[b].prec, h->bins[b].W, h->bins[b].R);
+                const FamilyEntry* f = shape_family(h->bins[b].prec, h->bins[b].W, h->bins[b].R,
+                                                    C.i16_limit < 0);
                 if (!f || std::find(seen.begin(), seen.end(), f) != seen.end()) continue;
                 seen.push_back(f);
                 for (int v = 1; v >= 0; --v) {
                     int var = -1, members = 0;
                     for (int k = 0; k < kFamilyMax; ++k) K.fam_bins[k] = -1;
                     for (int k = 0; k < f->n; ++k) {
-                        const int mb = find_bin(h, f->prec, f->W, f->rows[k]);
+                        const int mb = find_bin(h, f->prec, f->lanes_of(k), f->rows[k]);
                         if (mb < 0 || !launchable[mb]) continue;
                         const BinInfo& m = h->bins[mb];
                         if (v == 1 ? !(any_col && m.col) : (m.col && all_col)) continue;
@@ -631,7 +636,8 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                         h->bin_fam_tile[i2] = f->tile[var];
                     }
                     const QueueFn fn = f->k[var][pass];
-                    const int ppw = pairs_per_item(f->prec, f->W), ipb = items_per_block(f->W);
+                    // (lanes_of(0): the widest, so the fewest pairs an item)
+                    const int ppw = pairs_per_item(f->prec, f->lanes_of(0)), ipb = items_per_block(f->lanes_of(0));
                     const int64_t need = (cap / ppw + 1 + ipb - 1) / ipb;
                     const int blocks = (int)std::min<int64_t>(need, std::max(1, family_resident(h, fn)));
                     hipStream_t ls = forks > 1 ? h->fork[launched % forks] : stream;
@@ -811,7 +817,7 @@ sw_handle* sw_create(int device, const char* tuning) {
          hipMalloc(&h->d_small, kSmallInts * 4) == hipSuccess &&
          hipMalloc(&h->d_n, 16) == hipSuccess &&
          hipHostMalloc(&h->h_lut, kRouteClasses * kLutEntries, hipHostMallocDefault) == hipSuccess &&
-         hipMalloc(&h->d_hist, kHistSize * 4) == hipSuccess &&
+         hipMalloc(&h->d_hist, 2 * kHistSize * 4) == hipSuccess &&
          hipMalloc(&h->d_meta, kMetaSize * 4) == hipSuccess &&
          hipHostMalloc(&h->h_small, kSmallInts * 4, hipHostMallocDefault) == hipSuccess &&
          hipHostMalloc(&h->h_meta, kMetaSize * 4, hipHostMallocDefault) == hipSuccess;
@@ -846,8 +852,9 @@ sw_handle* sw_create(int device, const char* tuning) {
                     h->resident_blocks[nw][pass][v][b] = std::max(1, per_cu) * std::max(1, h->n_cu);
                 }
             }
-    for (size_t b = 0; ok && b < h->bins.size(); ++b) {
-        const FamilyEntry* f = shape_family(h->bins[b].prec, h->bins[b].W, h->bins[b].R);
+    for (size_t q = 0; ok && q < 2 * h->bins.size(); ++q) {
+        const size_t b = q / 2;
+        const FamilyEntry* f = shape_family(h->bins[b].prec, h->bins[b].W, h->bins[b].R, q % 2 != 0);
         for (int var = 0; f && ok && var <= kVarPtab; ++var)
             for (int pass = 0; pass < 2; ++pass) {
                 const QueueFn fn = f->k[var][pass];
@@ -1176,7 +1183,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     Workspace ws;
     if (no_alloc) {
         if (!h->d_scratch) return fail(h, SW_EDEVICE, "the static workspace has no address on device %d", h->device);
-        ws.keys = reinterpret_cast<int32_t*>(h->d_scratch + kStaticKeys);
+        ws.keys = reinterpret_cast<PairKey*>(h->d_scratch + kStaticKeys);
         ws.order = reinterpret_cast<int32_t*>(h->d_scratch + kStaticOrder);
         ws.items = reinterpret_cast<WorkItem*>(h->d_scratch + kStaticItems);
         ws.cap = P;
@@ -1303,7 +1310,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     K.max_items = (int32_t)(ws.cap + kMaxBins);
     K.ptab_sid = ptab_sid;
     K.ptab_dim = D;
-    K.redo = ws.keys;   // the keys of the reverse pass are not read any more when its sweeps run
+    K.redo = reinterpret_cast<int32_t*>(ws.keys);   // the keys of the reverse pass are not read any more when its sweeps run
     K.drift_sid[0] = std::max(0, col_sid);
     K.drift_e[0] = col_sid >= 0 ? schemes[col_sid].gap_extend : 0;
     K.drift_period[0] = col_sid >= 0 ? col_period : kChunk;
@@ -1365,7 +1372,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
         HIP_TRY(h, hipMemcpyAsync(h->d_mats, sl.h_mats, kSchemeBytes, hipMemcpyHostToDevice, stream));
         h->dev_mats = h->tables;
     }
-    HIP_TRY(h, launch_call_start(h->d_small, kSmallInts, h->d_n, (int32_t)P, stream));
+    HIP_TRY(h, launch_call_start(h->d_small, kSmallInts, h->d_hist, 2 * kHistSize, h->d_n, (int32_t)P, stream));
 
     auto enqueue_all = [&](hipStream_t es) -> int {
         const int rc0 = enqueue_pass(h, K, C, ws, 0, es, timing, search_n, cls);
@@ -1771,9 +1778,9 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
         T.chunk = c;
         HIP_TRY(h, launch_reset(h->d_hist, kHistSize, stream));
         HIP_TRY(h, launch_trace_classify(K, T, cap, h->d_keys, h->d_hist, counters(h->d_small), path_len, stream));
-        HIP_TRY(h, launch_plan(h->d_tbins, n_tb, h->d_hist, h->d_meta, stream));
-        HIP_TRY(h, launch_scatter(h->d_keys, h->d_n, cap, h->d_hist, h->d_order, stream));
-        HIP_TRY(h, launch_items(h->d_meta, h->d_tbins, n_tb, h->d_n, cap, h->d_items, stream));
+        HIP_TRY(h, launch_plan_bins(h->d_tbins, n_tb, h->d_hist, h->d_meta, stream));
+        HIP_TRY(h, launch_scatter(h->d_keys, h->d_meta, h->d_tbins, n_tb, h->d_n, cap, h->d_hist, h->d_order,
+                                  h->d_items, stream));
         // longest boxes first: each bin's sweep (sized to fill the device),
         // then its walks, on one stream; bins go round-robin to the forked
         // streams (joined back at the end of the chunk), so that walks and

@@ -1033,55 +1033,72 @@ hipError_t launch_trace_sizes(const KParams& P, const TraceArgs& T, int64_t cap,
 // Keys as in the score passes' classification: (bin, reference-length
 // bucket, longest first); pairs outside the chunk or without an alignment
 // get the trivial key.
-__global__ void sw_trace_classify_kernel(KParams P, TraceArgs T, int32_t* keys, int32_t* hist,
-                                         unsigned long long* counters, int32_t* path_len) {
+template <int THREADS, int PER>
+__global__ __launch_bounds__(THREADS) void sw_trace_classify_kernel(KParams P, TraceArgs T, PairKey* keys,
+                                                                    int32_t* hist, unsigned long long* counters,
+                                                                    int32_t* path_len) {
+    __shared__ KeyCount<THREADS, PER> KC;
     __shared__ unsigned long long s_cells[kMaxBins];
-    __shared__ uint32_t s_pairs[kMaxBins];
-    __shared__ int32_t s_trivial;
-    if (threadIdx.x < kMaxBins) { s_cells[threadIdx.x] = 0; s_pairs[threadIdx.x] = 0; }
-    if (threadIdx.x == 0) s_trivial = 0;
+    __shared__ uint32_t s_pairs[kMaxBins], s_col[kMaxBins];
+    KC.clear();
+    if (threadIdx.x < kMaxBins) { s_cells[threadIdx.x] = 0; s_pairs[threadIdx.x] = s_col[threadIdx.x] = 0; }
     __syncthreads();
     const int64_t n = *P.n_dev;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        int key = kTrivialKey;
-        const sw_result r = P.out[i];
-        if (r.score <= 0 && T.chunk == 0) path_len[i] = 0;   // no alignment, no path
-        if (r.score > 0 && T.rec_off[i] / T.chunk_bytes == T.chunk) {
-            const int rows = r.q_end - r.q_start + 1, cols = r.r_end - r.r_start + 1;
-            // sizes were validated when the records were laid out
-            if (rows >= 1 && rows <= SW_MAX_QUERY && cols >= 1 && cols <= SW_MAX_REF) {
-                const int b = trace_bin(T, r.score, rows);
-                if (b >= 0 && b < T.n_bins) {
-                    // pairs of column-path schemes first (the bin's
-                    // column-word kernel takes them; the host enables the
-                    // column path only when every scheme of the call has it)
-                    const int sid = P.scheme_id ? (int)P.scheme_id[i] : 0;
-                    const int col = (T.bins[b].col && sid < SW_MAX_SCHEMES && P.col_ok[sid]) ? 1 : 0;
-                    key = b * kMBuckets + (col ? 0 : kMHalf) + (kMHalf - 1 - m_bucket(cols));
-                    atomicAdd(&s_cells[b], (unsigned long long)rows * (unsigned long long)cols);
-                    atomicAdd(&s_pairs[b], 1u);
+    const int64_t i0 = (int64_t)blockIdx.x * (THREADS * PER) + threadIdx.x;
+    int key[PER], slot[PER], rank[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t i = i0 + u * THREADS;
+        key[u] = kTrivialKey;
+        if (i < n) {
+            const sw_result r = P.out[i];
+            if (r.score <= 0 && T.chunk == 0) path_len[i] = 0;   // no alignment, no path
+            if (r.score > 0 && T.rec_off[i] / T.chunk_bytes == T.chunk) {
+                const int rows = r.q_end - r.q_start + 1, cols = r.r_end - r.r_start + 1;
+                // sizes were validated when the records were laid out
+                if (rows >= 1 && rows <= SW_MAX_QUERY && cols >= 1 && cols <= SW_MAX_REF) {
+                    const int b = trace_bin(T, r.score, rows);
+                    if (b >= 0 && b < T.n_bins) {
+                        // pairs of column-path schemes first (the bin's
+                        // column-word kernel takes them; the host enables the
+                        // column path only when every scheme of the call has it)
+                        const int sid = P.scheme_id ? (int)P.scheme_id[i] : 0;
+                        const int col = (T.bins[b].col && sid < SW_MAX_SCHEMES && P.col_ok[sid]) ? 1 : 0;
+                        key[u] = b * kMBuckets + (col ? 0 : kMHalf) + (kMHalf - 1 - m_bucket(cols));
+                        atomicAdd(&s_cells[b], (unsigned long long)rows * (unsigned long long)cols);
+                        atomicAdd(&s_pairs[b], 1u);
+                        if (col) atomicAdd(&s_col[b], 1u);
+                    }
                 }
             }
         }
-        if (key == kTrivialKey) atomicAdd(&s_trivial, 1);
-        else atomicAdd(&hist[key], 1);
-        keys[i] = key;
+        KC.insert(key[u], slot[u], rank[u]);
     }
     __syncthreads();
-    if (threadIdx.x == 0 && s_trivial) atomicAdd(&hist[kTrivialKey], s_trivial);
+    KC.reserve(hist);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t i = i0 + u * THREADS;
+        if (i < n) keys[i] = KC.place(key[u], slot[u], rank[u]);
+    }
     if (threadIdx.x < kMaxBins && s_pairs[threadIdx.x]) {
+        atomicAdd(&hist[kHistPairs + threadIdx.x], (int32_t)s_pairs[threadIdx.x]);
+        if (s_col[threadIdx.x]) atomicAdd(&hist[kHistCol + threadIdx.x], (int32_t)s_col[threadIdx.x]);
         atomicAdd(&counters[kCtrTraceBinCells + threadIdx.x], s_cells[threadIdx.x]);
         atomicAdd(&counters[kCtrTraceBinPairs + threadIdx.x], (unsigned long long)s_pairs[threadIdx.x]);
     }
 }
 
-hipError_t launch_trace_classify(const KParams& P, const TraceArgs& T, int64_t cap, int32_t* keys,
+hipError_t launch_trace_classify(const KParams& P, const TraceArgs& T, int64_t cap, PairKey* keys,
                                  int32_t* hist, unsigned long long* counters, int32_t* path_len, hipStream_t s) {
     if (cap <= 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((cap + 255) / 256);
-    hipLaunchKernelGGL(sw_trace_classify_kernel, dim3(blocks), dim3(256), 0, s, P, T, keys, hist, counters,
-                       path_len);
+    if (cap <= kClassifySmall)
+        hipLaunchKernelGGL((sw_trace_classify_kernel<256, 1>), dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s,
+                           P, T, keys, hist, counters, path_len);
+    else
+        hipLaunchKernelGGL((sw_trace_classify_kernel<1024, 2>), dim3((unsigned)((cap + 2047) / 2048)), dim3(1024), 0,
+                           s, P, T, keys, hist, counters, path_len);
     return hipGetLastError();
 }
 
