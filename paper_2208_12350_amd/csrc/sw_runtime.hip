@@ -1781,33 +1781,36 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
         HIP_TRY(h, launch_plan_bins(h->d_tbins, n_tb, h->d_hist, h->d_meta, stream));
         HIP_TRY(h, launch_scatter(h->d_keys, h->d_meta, h->d_tbins, n_tb, h->d_n, cap, h->d_hist, h->d_order,
                                   h->d_items, stream));
-        // longest boxes first: each bin's sweep (sized to fill the device),
-        // then its walks, on one stream; bins go round-robin to the forked
+        // longest boxes first: sweeps sized to fill the device, on the forked
         // streams (joined back at the end of the chunk), so that walks and
         // launch tails overlap other bins' sweeps.  Timing serialises
         // everything on the caller's stream.
         const int forks = timing ? 0 : (int)h->opt_streams;
-        const int walk_blocks = (int)std::min<int64_t>((cap + 255) / 256, 4 * std::max(1, h->n_cu));
         if (forks > 1) {
             HIP_TRY(h, hipEventRecord(h->fork_ev[sw_handle::kForks], stream));
             for (int f = 0; f < forks; ++f)
                 HIP_TRY(h, hipStreamWaitEvent(h->fork[f], h->fork_ev[sw_handle::kForks], 0));
         }
-        int launched = 0;
-        // walks per wavefront: fewer for longer boxes (a wavefront waits
-        // for every miss of any of its walks)
-        auto walk = [&](int b, hipStream_t ls) -> hipError_t {
-            const int rows = h->tbins[b].W * h->tbins[b].R;
-            const int active = rows >= 1024 ? 8 : rows >= 768 ? 16 : rows >= 96 ? 32 : 64;
-            const int wblocks = active == 64 ? walk_blocks
-                                             : (int)std::min<int64_t>((cap + 4 * active - 1) / (4 * active),
-                                                                      4 * std::max(1, h->n_cu));
-            return launch_trace_walk(K, T, b, wblocks, active, path_off, path, path_len, ls);
+        // the forked stream with the fewest launches
+        int queued[sw_handle::kForks] = {};
+        auto next_fork = [&]() -> int {
+            int best = 0;
+            for (int f = 1; f < forks; ++f)
+                if (queued[f] < queued[best]) best = f;
+            ++queued[best];
+            return best;
+        };
+        // walks of up to kFamilyMax bins
+        auto walk = [&](const int* bins, int nb, hipStream_t ls) -> hipError_t {
+            KParams KW = K;
+            for (int k = 0; k < kFamilyMax; ++k) KW.fam_bins[k] = (int8_t)(k < nb ? bins[k] : -1);
+            return launch_trace_walk(KW, T, cap, std::max(1, h->n_cu), h->tbins[bins[0]].W == 64, path_off, path,
+                                     path_len, ls);
         };
         // Family launches (option "families"): per lane width and variant, one
         // box-sweep kernel takes the items of all its bins, largest rows
-        // first.  The two variants of a width run on different streams; a
-        // member's walks start once both have swept it.
+        // first.  The two variants of a width run on different streams; the
+        // members' walks, one launch, start once both are done.
         h->tfam_first.assign(n_tb, -1);
         int n_fam = 0;
         for (int b = n_tb - 1; h->opt_families && b >= 0; --b) {
@@ -1845,13 +1848,14 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
             for (int k = 0; k < nm; ++k) h->tfam_first[members[k]] = b0;
             for (int k = 0; k < kFamilyMax; ++k) K.fam_bins[k] = fam_bins[k];
             const int64_t need = (cap / e.ppw + 1 + kWavesPerBlock - 1) / kWavesPerBlock;
-            hipStream_t ls = forks > 1 ? h->fork[launched++ % forks] : stream;
+            const int lf = forks > 1 ? next_fork() : 0;
+            hipStream_t ls = forks > 1 ? h->fork[lf] : stream;
             if (timing) HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * b0], ls));
             hipEvent_t swept[2];
             int n_swept = 0;
             for (int v = 1; v >= 0; --v) {
                 if (!fns[v]) continue;
-                hipStream_t vs = n_swept == 0 || forks <= 1 ? ls : h->fork[launched++ % forks];
+                hipStream_t vs = n_swept == 0 || forks <= 1 ? ls : h->fork[next_fork()];
                 hipLaunchKernelGGL(fns[v], dim3((int)std::min<int64_t>(need, res[v])), dim3(kBlock), 0, vs, K, T);
                 HIP_TRY(h, hipGetLastError());
                 swept[n_swept] = h->tfam_ev[n_fam++];
@@ -1859,26 +1863,29 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
                 ++n_swept;
             }
             if (timing) HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * b0 + 1], ls));
-            // the members' walks, once the sweeps have written their records:
-            // spread over the forked streams so that they overlap other
-            // sweeps (timing keeps everything on the caller's stream)
-            for (int k = 0; k < nm; ++k) {
-                const int mb = members[k];
-                hipStream_t ws = ls;
+            // the members' walks, once the sweeps have written their records
+            // (timing launches and times each bin's)
+            if (!timing) {
                 if (forks > 1) {
-                    if (k > 0) ws = h->fork[launched++ % forks];
-                    for (int q = 0; q < n_swept; ++q) HIP_TRY(h, hipStreamWaitEvent(ws, swept[q], 0));
+                    for (int q = 0; q < n_swept; ++q) HIP_TRY(h, hipStreamWaitEvent(ls, swept[q], 0));
+                    ++queued[lf];
                 }
-                if (timing && mb != b0) HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * mb + 1], ws));
-                HIP_TRY(h, walk(mb, ws));
-                if (timing) HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * mb + 2], ws));
+                HIP_TRY(h, walk(members, nm, ls));
+            }
+            for (int k = 0; timing && k < nm; ++k) {
+                const int mb = members[k];
+                if (mb != b0) HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * mb + 1], ls));
+                HIP_TRY(h, walk(&mb, 1, ls));
+                HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * mb + 2], ls));
             }
         }
+        // the other bins: their sweeps one by one, then one launch walks them
+        std::vector<int> rest;
         for (int b = n_tb - 1; b >= 0; --b) {
             if (h->tfam_first[b] >= 0 || !reachable(b)) continue;
             const BinInfo& e = h->tbins[b];
             const int64_t need = (cap / e.ppw + 1 + kWavesPerBlock - 1) / kWavesPerBlock;
-            hipStream_t ls = forks > 1 ? h->fork[launched++ % forks] : stream;
+            hipStream_t ls = forks > 1 ? h->fork[next_fork()] : stream;
             if (timing) HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * b], ls));
             // the column-word kernel takes the bin's small-alphabet items,
             // the table kernel the rest, one after the other on the bin's
@@ -1891,14 +1898,20 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
                                    T);
                 HIP_TRY(h, hipGetLastError());
             }
-            if (timing) HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * b + 1], ls));
-            HIP_TRY(h, walk(b, ls));
-            if (timing) HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * b + 2], ls));
+            if (timing) {
+                HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * b + 1], ls));
+                HIP_TRY(h, walk(&b, 1, ls));
+                HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * b + 2], ls));
+            } else {
+                rest.push_back(b);
+            }
         }
         for (int f = 0; forks > 1 && f < forks; ++f) {
             HIP_TRY(h, hipEventRecord(h->fork_ev[f], h->fork[f]));
             HIP_TRY(h, hipStreamWaitEvent(stream, h->fork_ev[f], 0));
         }
+        for (size_t q = 0; q < rest.size(); q += kFamilyMax)
+            HIP_TRY(h, walk(&rest[q], (int)std::min<size_t>(kFamilyMax, rest.size() - q), stream));
         if (timing) {
             HIP_TRY(h, hipStreamSynchronize(stream));
             for (int b = 0; b < n_tb; ++b) {

@@ -36,7 +36,7 @@
 //      bytes of two such differences (four flags, one per byte, in bit 7),
 //      and a shift and a bitfield insert push them into the row's bit of
 //      four byte-wide flag streams.  The int32 sweep takes min(x ^ y, 1).
-//   2. Walk: one thread per pair follows the bits back from the box's last
+//   2. Walk: a few lanes per pair follow the bits back from the box's last
 //      cell, taking as H's source the diagonal, else F, else E (the first
 //      that equals H) and opening a gap over extending it, and writes the path as
 //      runs (length << 4) | op with the SAM codes 7 '=', 8 'X', 1 'I', 2 'D'.
@@ -46,6 +46,8 @@
 // prefix of an optimal path scores above 0).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "sw_device.h"
 #include "sw_internal.h"
@@ -1103,204 +1105,292 @@ hipError_t launch_trace_classify(const KParams& P, const TraceArgs& T, int64_t c
 }
 
 // ---- walk ------------------------------------------------------------------------
-// One thread per pair of the chunk.  Runs are written from the end of the
-// pair's output room backwards while the path is followed back, then moved
-// to its start.  A path that leaves its box or does not end at the box's
-// first cell is an internal error; one that needs more runs than its room
-// sets kFlagPathRoom.  Either way the pair's run count becomes -1.
-// dwords per thread: two record blocks of up to 32 dwords, padded against
-// bank conflicts
-constexpr int kWalkSlot = 65;
+// A few lanes per pair.  All of them follow the path with the same state, which
+// makes every read of the staged record a broadcast, and share the loads.
+// Runs are written from the end of the pair's output room backwards while the
+// path is followed back, then moved to its start.  A path that leaves its box
+// or does not end at the box's first cell is an internal error; one that
+// needs more runs than its room sets kFlagPathRoom.  Either way the pair's run
+// count becomes -1.
+//
+// Bound by latency, one dependent step after another.  A path moves to the
+// same or earlier lanes and steps, about one row per column, so the walk
+// stages a square tile of its record and the residues beside it, and follows
+// the path in LDS until it leaves the tile.  The walks of a wavefront stage
+// their tiles at the same time, so it waits for memory about once per tile.
+// Staged by each thread alone, 16 steps of one lane's rows at a time, a
+// wavefront waited for the misses of its 8 to 64 walks one by one, and moved
+// the runs of a pair one load after another.  50,000 mixed pairs: 2.0 ms of
+// walks, 9 before; 100,000 pairs of 250 DNA residues: 0.31 ms.
+//   Boxes above 512 rows: eight walks a wavefront with tiles of 64 (18 KB, 9
+// wavefronts on a CU) have the fewest waits.  Smaller boxes, of which there
+// are more: sixteen with tiles of 32 (10 KB, 16 wavefronts) share a step's
+// instructions between more walks; 100,000 pairs of 250 DNA residues took
+// 4.37 ms with the larger tiles and 3.76 with these.
+//
+// WALKS pairs per wavefront, tiles of TILE rows by TILE steps.
+template <int WALKS, int TILE>
+struct WalkShape {
+    static constexpr int kLanes = 64 / WALKS;                   // per pair
+    static constexpr int kBlocks = TILE / kStage;               // record blocks of a tile
+    static constexpr int kDwords = kBlocks * TILE;              // a block's rows take one dword each
+    static constexpr int kChunks = (TILE / 4 + kLanes - 1) / kLanes;       // of 16 bytes, per lane and block
+    static constexpr int kResidues = TILE + 16;                 // bytes: TILE residues from any alignment to 16
+    static constexpr int kResChunks = (kResidues / 16 + kLanes - 1) / kLanes;   // per lane
+    // dwords per walk: an odd number of 16-byte units, so that the walks of a
+    // wavefront start in banks of their own
+    static constexpr int kUsed = kDwords + 2 * kResidues / 4;
+    static constexpr int kSlot = kUsed + (kUsed / 4 % 2 == 0 ? 4 : 0);
+    static_assert(kStage == 8 && TILE % 16 == 0 && TILE >= 32, "whole lanes of up to 32 rows, whole chunks");
+};
 
-// The 16 residues around a position, read as one aligned 16-byte load (an
-// aligned 16-byte block never crosses a page, so it is readable whenever
-// the residue itself is); a walk moves backwards through each sequence, so
-// one load serves up to 16 of its steps.
-__device__ __forceinline__ uint32_t window_at(const uint8_t* seq, int x, uintptr_t& base, uint32_t& w0, uint32_t& w1,
-                                              uint32_t& w2, uint32_t& w3) {
-    const uintptr_t a = reinterpret_cast<uintptr_t>(seq + x);
-    const uintptr_t b = a & ~(uintptr_t)15;
-    if (b != base) {
-        const uint4 v = *reinterpret_cast<const uint4*>(b);
-        w0 = v.x; w1 = v.y; w2 = v.z; w3 = v.w;
-        base = b;
-    }
-    const uint32_t o = (uint32_t)(a - b);
-    const uint32_t w = o < 8 ? (o < 4 ? w0 : w1) : (o < 12 ? w2 : w3);
-    return (w >> (8 * (o & 3))) & 0xFFu;
-}
+// The pair at one lane group of a wavefront, and where its walk stands.
+struct Walk {
+    const uint32_t* rec;
+    const uint8_t* qa;
+    const uint8_t* rb;
+    int64_t beg, end, room;
+    int W, R, x, y, lane, rr;   // cell (x, y); x = lane * R + rr
+    int state;                  // 0 = H, 1 = F (query gap), 2 = E (reference gap), 3 = E moved, choice pending
+    int err;                    // 1 internal, 2 room
+    int64_t k;                  // runs written
+    uint32_t op, len;
+    int pair;                   // -1: none
+    bool done;                  // the walk is over (reached the first cell, or failed)
+};
 
-// Walk of pair i (whose record is in the current chunk).
-__device__ __forceinline__ void walk_pair(const KParams& P, const TraceArgs& T, int i, const int64_t* path_off,
-                                          uint32_t* path, int32_t* path_len, uint32_t* slot) {
+__device__ __forceinline__ void walk_begin(const KParams& P, const TraceArgs& T, int i, const int64_t* path_off, Walk& w) {
+    w.pair = i;
+    w.done = true;
+    w.err = 0;
+    w.rec = nullptr;
+    w.qa = w.rb = nullptr;
+    w.beg = w.end = w.room = w.k = 0;
+    w.W = w.R = 4;
+    w.x = w.y = w.lane = w.rr = w.state = 0;
+    w.op = w.len = 0;
+    if (i < 0) return;
     const sw_result r = P.out[i];
     const int64_t off = T.rec_off[i];
     const int rows = r.q_end - r.q_start + 1, cols = r.r_end - r.r_start + 1;
     const int b = (r.score > 0 && rows >= 1 && rows <= SW_MAX_QUERY) ? trace_bin(T, r.score, rows) : -1;
-    const int64_t beg = path_off[i], end = path_off[i + 1];
-    if (b < 0 || b >= T.n_bins || cols < 1 || end < beg) {
-        atomicOr(&P.flags[end < beg ? kFlagPathRoom : kFlagInternal], 1);
-        path_len[i] = -1;
+    w.beg = path_off[i];
+    w.end = path_off[i + 1];
+    if (b < 0 || b >= T.n_bins || cols < 1 || w.end < w.beg) {
+        w.err = w.end < w.beg ? 2 : 1;
         return;
     }
-    const int W = T.bins[b].W, R = T.bins[b].R;
+    w.W = T.bins[b].W;
+    w.R = T.bins[b].R;
     const int64_t rel = off - (int64_t)T.chunk * T.chunk_bytes;
-    if (W * R < rows || R > 32 || (R & 3) != 0 || rel < 0 || rel + trace_record_bytes(W, R, cols) > T.ws_bytes) {
-        atomicOr(&P.flags[kFlagInternal], 1);
-        path_len[i] = -1;
+    if (w.W * w.R < rows || w.R > 32 || (w.R & 3) != 0 || rel < 0 ||
+        rel + trace_record_bytes(w.W, w.R, cols) > T.ws_bytes) {
+        w.err = 1;
         return;
     }
-    const uint32_t* rec = reinterpret_cast<const uint32_t*>(T.ws + rel);
-    // `slot` (this thread's LDS copy) holds the record blocks of steps
-    // [8 c_tb, 8 c_tb + 8) and, when c_tb >= 1, [8 c_tb - 8, 8 c_tb) of lane
-    // c_lane: a walk only moves to the same or earlier steps, so the second
-    // block is the next one it needs in that lane.  Both are fetched in one
-    // round trip, every 16-byte load issued before the first is waited for.
-    int c_lane = -1, c_tb = -1;
-    const uint8_t* qa = P.queries + P.q_beg[i] + r.q_start;
-    const uint8_t* rb = P.refs + P.r_beg[i] + r.r_start;
-    uintptr_t qbase = ~(uintptr_t)0, rbase = ~(uintptr_t)0;
-    uint32_t q0 = 0, q1 = 0, q2 = 0, q3 = 0, r0 = 0, r1 = 0, r2 = 0, r3 = 0;
-    const int64_t room = end - beg;
-    int x = rows - 1, y = cols - 1;
-    int state = 0;   // 0 = H, 1 = F (query gap), 2 = E (reference gap), 3 = E moved, choice pending
-    int64_t k = 0;   // runs written
-    uint32_t op = 0, len = 0;
-    int err = 0;     // 1 internal, 2 room
-    const int64_t limit = 2 * ((int64_t)rows + cols) + 2;
-    bool done = false;
-    for (int64_t it = 0; it < limit && !err; ++it) {
-        const int lane = x / R, rr = x - lane * R;
-        const int t = y + lane;
-        const int tb = t / kStage;
-        if (lane != c_lane || tb > c_tb || tb < c_tb - 1) {
-            const int nq = R / 4;   // 16-byte pieces per block (R <= 32)
-            const uint4* src0 = reinterpret_cast<const uint4*>(rec + ((int64_t)tb * W + lane) * R);
-            const uint4* src1 = reinterpret_cast<const uint4*>(rec + ((int64_t)(tb - 1) * W + lane) * R);
-            const bool two = tb >= 1;
-            uint4 v0[8], v1[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                if (q < nq) v0[q] = src0[q];
-                if (q < nq && two) v1[q] = src1[q];
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                if (q < nq) {
-                    slot[4 * q] = v0[q].x; slot[4 * q + 1] = v0[q].y;
-                    slot[4 * q + 2] = v0[q].z; slot[4 * q + 3] = v0[q].w;
-                }
-                if (q < nq && two) {
-                    slot[R + 4 * q] = v1[q].x; slot[R + 4 * q + 1] = v1[q].y;
-                    slot[R + 4 * q + 2] = v1[q].z; slot[R + 4 * q + 3] = v1[q].w;
-                }
-            }
-            c_lane = lane;
-            c_tb = tb;
-        }
-        // the step's R/2 bytes: a dword of D, N, FX, EX bytes per 8 rows,
-        // then for R % 8 == 4 the 16-bit tail (FX, D, EX, N nibbles)
-        const uint16_t* st = reinterpret_cast<const uint16_t*>(slot + (c_tb - tb) * R) + (t % kStage) * (R / 4);
-        const int j = rr >> 3, kk = rr & 7;
-        uint32_t fd, fn, ffx, fex;
-        if (j < (R >> 3)) {
-            const uint32_t v = ((uint32_t)st[2 * j] | ((uint32_t)st[2 * j + 1] << 16)) >> kk;
-            fd = v & 1u; fn = (v >> 8) & 1u; ffx = (v >> 16) & 1u; fex = (v >> 24) & 1u;
-        } else {
-            const uint32_t v = (uint32_t)st[2 * j] >> kk;
-            ffx = v & 1u; fd = (v >> 4) & 1u; fex = (v >> 8) & 1u; fn = (v >> 12) & 1u;
-        }
-        // a gap move from (x, y+1) left E's choice there open: this cell's
-        // record holds whether E(x, y+1) extends E(x, y)
-        if (state == 3) state = fex ? 2 : 0;
-        uint32_t o;
-        if (state == 0) {
-            if (fd) { state = fn ? 2 : 1; continue; }
-            o = window_at(qa, x, qbase, q0, q1, q2, q3) == window_at(rb, y, rbase, r0, r1, r2, r3) ? 7u : 8u;
-            --x; --y;
-        } else if (state == 1) {
-            o = 1u;
-            state = ffx ? 1 : 0;
-            --x;
-        } else {
-            o = 2u;
-            state = 3;
-            --y;
-        }
-        if (o == op) {
-            ++len;
-        } else {
-            if (len) {
-                if (k >= room) { err = 2; break; }
-                path[end - 1 - k] = (len << 4) | op;
-                ++k;
-            }
-            op = o;
-            len = 1;
-        }
-        if (x < 0 || y < 0) {
-            // the first column of the path must be the box's first cell
-            done = x == -1 && y == -1 && state == 0 && (o == 7u || o == 8u);
-            if (!done) err = 1;
-            break;
-        }
-    }
-    if (!err && !done) err = 1;
-    if (!err) {
-        if (k >= room) err = 2;
-        else {
-            path[end - 1 - k] = (len << 4) | op;
-            ++k;
-        }
-    }
-    if (err) {
-        atomicOr(&P.flags[err == 2 ? kFlagPathRoom : kFlagInternal], 1);
-        path_len[i] = -1;
-        return;
-    }
-    // runs sit at path[end-k .. end) in order; move them to the room's start
-    for (int64_t q = 0; q < k; ++q) path[beg + q] = path[end - k + q];
-    path_len[i] = (int32_t)k;
+    w.rec = reinterpret_cast<const uint32_t*>(T.ws + rel);
+    w.qa = P.queries + P.q_beg[i] + r.q_start;
+    w.rb = P.refs + P.r_beg[i] + r.r_start;
+    w.room = w.end - w.beg;
+    w.x = rows - 1;
+    w.y = cols - 1;
+    w.lane = w.x / w.R;
+    w.rr = w.x - w.lane * w.R;
+    w.done = false;
 }
 
-// One bin's walks: its pairs are order[meta[bin first] .. meta[next bin first]).
-// A of each wavefront's lanes walk a pair each (the others return at once):
-// a wavefront waits for every record block any of its walks misses, so long
-// walks run few to a wavefront.
-template <int A>
-__global__ __launch_bounds__(256) void sw_trace_walk_kernel(KParams P, TraceArgs T, int bin, const int64_t* path_off,
-                                                            uint32_t* path, int32_t* path_len) {
-    __shared__ uint32_t cache[4 * A * kWalkSlot];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int lo = P.meta[kMetaBinFirst + bin], hi = P.meta[kMetaBinFirst + bin + 1];
-    if (lo < 0 || lo > hi || hi > P.n_pairs) {
-        if (threadIdx.x == 0) atomicOr(&P.flags[kFlagInternal], 1);
-        return;
+// Stage the residues of positions max(x - TILE + 1, 0) .. x of a sequence;
+// returns the offset that turns a position into its byte of the staged copy.
+// (An aligned 16-byte block never crosses a page, so it is readable whenever
+// one of its residues is.)
+template <class Sh, int TILE>
+__device__ __forceinline__ int load_residues(const uint8_t* seq, int x, int sub, bool live, uint4 (&v)[Sh::kResChunks]) {
+    const uintptr_t top = reinterpret_cast<uintptr_t>(seq) + (uintptr_t)x;
+    const uintptr_t low = reinterpret_cast<uintptr_t>(seq) + (uintptr_t)(x > TILE - 1 ? x - (TILE - 1) : 0);
+    const uintptr_t base = low & ~(uintptr_t)15;
+#pragma unroll
+    for (int c = 0; c < Sh::kResChunks; ++c) {
+        const uintptr_t at = base + 16 * (uintptr_t)(sub + Sh::kLanes * c);
+        v[c] = make_uint4(0, 0, 0, 0);
+        if (live && at <= top) v[c] = *reinterpret_cast<const uint4*>(at);
     }
-    if (lane >= A) return;
-    uint32_t* slot = cache + (wave * A + lane) * kWalkSlot;
+    return (int)((intptr_t)reinterpret_cast<uintptr_t>(seq) - (intptr_t)base);
+}
+
+// The walks of a run of bins' pairs: the pairs of bin P.fam_bins[k], then of
+// P.fam_bins[k + 1] (each longest boxes first), WALKS to a wavefront, whose
+// lane groups start on their next pairs together.
+template <int WALKS, int TILE>
+__global__ __launch_bounds__(64) void sw_trace_walk_kernel(KParams P, TraceArgs T, const int64_t* path_off,
+                                                           uint32_t* path, int32_t* path_len) {
+    using Sh = WalkShape<WALKS, TILE>;
+    __shared__ __attribute__((aligned(16))) uint32_t slots[WALKS * Sh::kSlot];
+    __shared__ int32_t s_first[kFamilyMax], s_end[kFamilyMax];   // first pair in P.order, end of the run's count
+    const int lane64 = threadIdx.x, g = lane64 / Sh::kLanes, sub = lane64 % Sh::kLanes;
+    uint32_t* slot = slots + g * Sh::kSlot;
     const int n = *P.n_dev;
-    const int stride = (int)gridDim.x * 4 * A;
-    for (int k = lo + ((int)blockIdx.x * 4 + wave) * A + lane; k < hi; k += stride) {
-        const int i = P.order[k];
-        if (i < 0 || i >= n) {
-            atomicOr(&P.flags[kFlagInternal], 1);
+    int total = 0;
+    for (int q = 0; q < kFamilyMax; ++q) {
+        const int bin = P.fam_bins[q];
+        int lo = 0, hi = 0;
+        if (bin >= 0) {
+            lo = P.meta[kMetaBinFirst + bin];
+            hi = P.meta[kMetaBinFirst + bin + 1];
+            if (lo < 0 || lo > hi || hi > P.n_pairs) {
+                if (threadIdx.x == 0) atomicOr(&P.flags[kFlagInternal], 1);
+                lo = hi = 0;
+            }
+        }
+        total += hi - lo;
+        if (threadIdx.x == 0) { s_first[q] = lo; s_end[q] = total; }
+    }
+    __syncthreads();
+    const int stride = (int)gridDim.x * WALKS;
+    for (int k0 = (int)blockIdx.x * WALKS; k0 < total; k0 += stride) {
+        int i = -1;
+        if (k0 + g < total) {
+            int q = 0;
+            while (q < kFamilyMax - 1 && k0 + g >= s_end[q]) ++q;
+            i = P.order[s_first[q] + (k0 + g - (q > 0 ? s_end[q - 1] : 0))];
+            if (i < 0 || i >= n) {
+                if (sub == 0) atomicOr(&P.flags[kFlagInternal], 1);
+                i = -1;
+            }
+        }
+        Walk w;
+        walk_begin(P, T, i, path_off, w);
+        while (__builtin_amdgcn_ballot_w64(!w.done) != 0) {
+            // ---- stage the tile that ends at the walk's lane and block
+            const int nl_max = TILE / w.R;                         // whole lanes of a tile
+            const int lane0 = w.lane - nl_max + 1 > 0 ? w.lane - nl_max + 1 : 0;
+            const int tb = (w.y + w.lane) / kStage;
+            const int b0 = tb - Sh::kBlocks + 1 > 0 ? tb - Sh::kBlocks + 1 : 0;
+            const int chunks = (w.lane - lane0 + 1) * w.R / 4;     // 16-byte chunks of a block
+            uint4 v[Sh::kBlocks][Sh::kChunks], vq[Sh::kResChunks], vr[Sh::kResChunks];
+#pragma unroll
+            for (int q = 0; q < Sh::kBlocks; ++q) {
+                const uint4* src = reinterpret_cast<const uint4*>(w.rec + ((int64_t)(b0 + q) * w.W + lane0) * w.R);
+#pragma unroll
+                for (int c = 0; c < Sh::kChunks; ++c) {
+                    const int u = sub + Sh::kLanes * c;
+                    v[q][c] = make_uint4(0, 0, 0, 0);
+                    if (!w.done && b0 + q <= tb && u < chunks) v[q][c] = src[u];
+                }
+            }
+            const int qoff = load_residues<Sh, TILE>(w.qa, w.x, sub, !w.done, vq);
+            const int roff = load_residues<Sh, TILE>(w.rb, w.y, sub, !w.done, vr);
+#pragma unroll
+            for (int q = 0; q < Sh::kBlocks; ++q)
+#pragma unroll
+                for (int c = 0; c < Sh::kChunks; ++c) {
+                    const int u = sub + Sh::kLanes * c;
+                    if (u < TILE / 4) *reinterpret_cast<uint4*>(slot + q * TILE + 4 * u) = v[q][c];
+                }
+#pragma unroll
+            for (int c = 0; c < Sh::kResChunks; ++c) {
+                const int u = sub + Sh::kLanes * c;
+                if (u < Sh::kResidues / 16) {
+                    *reinterpret_cast<uint4*>(slot + Sh::kDwords + 4 * u) = vq[c];
+                    *reinterpret_cast<uint4*>(slot + Sh::kDwords + Sh::kResidues / 4 + 4 * u) = vr[c];
+                }
+            }
+            wave_lds_sync();
+            // ---- follow the path inside it
+            const uint16_t* tile = reinterpret_cast<const uint16_t*>(slot);
+            const uint8_t* qres = reinterpret_cast<const uint8_t*>(slot + Sh::kDwords) + qoff;
+            const uint8_t* rres = reinterpret_cast<const uint8_t*>(slot + Sh::kDwords + Sh::kResidues / 4) + roff;
+            const int x0 = w.x > TILE - 1 ? w.x - (TILE - 1) : 0, y0 = w.y > TILE - 1 ? w.y - (TILE - 1) : 0;
+            const int whole = w.R >> 3;   // row groups of 8 with a whole dword a step
+            bool inside = !w.done;
+            while (inside) {
+                const int t = w.y + w.lane;
+                // the step's R/2 bytes: a dword of D, N, FX, EX bytes per 8 rows,
+                // then for R % 8 == 4 the 16-bit tail (FX, D, EX, N nibbles)
+                const int j = w.rr >> 3, kk = w.rr & 7;
+                const uint16_t* st = tile + 2 * ((t / kStage - b0) * TILE + (w.lane - lane0) * w.R) +
+                                     (t % kStage) * (w.R / 4) + 2 * j;
+                const bool tail = j >= whole;
+                const uint32_t lo = st[0], hi = st[tail ? 0 : 1];
+                const uint32_t same = qres[w.x] == rres[w.y] ? 7u : 8u;
+                const uint32_t f = (lo | (hi << 16)) >> kk;
+                const uint32_t fd = (tail ? f >> 4 : f) & 1u, fn = (tail ? f >> 12 : f >> 8) & 1u;
+                const uint32_t ffx = (tail ? f : f >> 16) & 1u, fex = (tail ? f >> 8 : f >> 24) & 1u;
+                // a gap move from (x, y+1) left E's choice there open: this cell's
+                // record holds whether E(x, y+1) extends E(x, y)
+                int s = w.state == 3 ? (fex ? 2 : 0) : w.state;
+                if (s == 0 && fd) s = fn ? 2 : 1;
+                const uint32_t o = s == 0 ? same : (uint32_t)s;   // 1 = I, 2 = D
+                const bool up = s != 2, left = s != 1;
+                w.state = s == 1 ? (int)ffx : s == 2 ? 3 : 0;
+                w.x -= up ? 1 : 0;
+                w.y -= left ? 1 : 0;
+                const bool next_lane = up && w.rr == 0;
+                w.rr = next_lane ? w.R - 1 : w.rr - (up ? 1 : 0);
+                w.lane -= next_lane ? 1 : 0;
+                if (o != w.op && w.len != 0) {
+                    // (a full room ends the walk)
+                    if (w.k < w.room) {
+                        if (sub == 0) path[w.end - 1 - w.k] = (w.len << 4) | w.op;
+                        ++w.k;
+                    } else {
+                        w.err = 2;
+                    }
+                }
+                w.len = o == w.op ? w.len + 1 : 1;
+                w.op = o;
+                // the first column of the path must be the box's first cell
+                const bool out = w.x < 0 || w.y < 0;
+                if (out && !w.err && !(w.x == -1 && w.y == -1 && w.state == 0 && s == 0)) w.err = 1;
+                w.done = out || w.err != 0;
+                inside = !w.done && w.lane >= lane0 && (w.y + w.lane) / kStage >= b0 && w.x >= x0 && w.y >= y0;
+            }
+            wave_lds_sync();
+        }
+        if (w.pair < 0) continue;
+        if (!w.err) {
+            if (w.k >= w.room) {
+                w.err = 2;
+            } else {
+                if (sub == 0) path[w.end - 1 - w.k] = (w.len << 4) | w.op;
+                ++w.k;
+            }
+        }
+        if (w.err) {
+            if (sub == 0) {
+                atomicOr(&P.flags[w.err == 2 ? kFlagPathRoom : kFlagInternal], 1);
+                path_len[w.pair] = -1;
+            }
             continue;
         }
-        walk_pair(P, T, i, path_off, path, path_len, slot);
+        // runs sit at path[end-k .. end) in order; move them to the room's
+        // start, 4 a lane at a time: each batch is read before it is written, and
+        // what it overwrites was read before
+        __threadfence_block();
+        for (int64_t q = sub; q - sub < w.k && w.k < w.room; q += 4 * Sh::kLanes) {
+            uint32_t m[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m[u] = q + u * Sh::kLanes < w.k ? path[w.end - w.k + q + u * Sh::kLanes] : 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (q + u * Sh::kLanes < w.k) path[w.beg + q + u * Sh::kLanes] = m[u];
+        }
+        if (sub == 0) path_len[w.pair] = (int32_t)w.k;
     }
 }
 
-hipError_t launch_trace_walk(const KParams& P, const TraceArgs& T, int bin, int blocks, int active,
+hipError_t launch_trace_walk(const KParams& P, const TraceArgs& T, int64_t cap, int n_cu, bool tall,
                              const int64_t* path_off, uint32_t* path, int32_t* path_len, hipStream_t s) {
-    const dim3 grid(blocks > 0 ? blocks : 1);
-    switch (active) {
-        case 4: hipLaunchKernelGGL(sw_trace_walk_kernel<4>, grid, dim3(256), 0, s, P, T, bin, path_off, path, path_len); break;
-        case 8: hipLaunchKernelGGL(sw_trace_walk_kernel<8>, grid, dim3(256), 0, s, P, T, bin, path_off, path, path_len); break;
-        case 16: hipLaunchKernelGGL(sw_trace_walk_kernel<16>, grid, dim3(256), 0, s, P, T, bin, path_off, path, path_len); break;
-        case 32: hipLaunchKernelGGL(sw_trace_walk_kernel<32>, grid, dim3(256), 0, s, P, T, bin, path_off, path, path_len); break;
-        default: hipLaunchKernelGGL(sw_trace_walk_kernel<64>, grid, dim3(256), 0, s, P, T, bin, path_off, path, path_len);
-    }
+    // as many wavefronts as are resident by their LDS
+    auto blocks = [&](int walks, int slot) {
+        const int64_t per_cu = (160 * 1024) / (walks * slot * 4 + 512);
+        return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((cap + walks - 1) / walks, per_cu * n_cu)));
+    };
+    if (tall)
+        hipLaunchKernelGGL((sw_trace_walk_kernel<8, 64>), blocks(8, WalkShape<8, 64>::kSlot), dim3(64), 0, s, P, T,
+                           path_off, path, path_len);
+    else
+        hipLaunchKernelGGL((sw_trace_walk_kernel<16, 32>), blocks(16, WalkShape<16, 32>::kSlot), dim3(64), 0, s, P, T,
+                           path_off, path, path_len);
     return hipGetLastError();
 }
 
