@@ -44,12 +44,13 @@ struct CoopLds {
     int32_t item;
 };
 
-template <int R, bool REV>
-__device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S, CoopLds& C, int first,
-                                           int count, int tid) {
+// Row-major-first cell of the best score of two jobs (pair A low): score, row
+// and column, the same in every lane of the workgroup.
+template <int R>
+__device__ __forceinline__ void coop_best(const KParams& P, const SchemeLds& S, CoopLds& C, const PairJob& JA,
+                                          const PairJob& JB, int tid, int (&best)[2], int (&row)[2], int (&col)[2]) {
     constexpr int W = kCoopW;
     using Stager = RefStager<W>;
-    constexpr int reverse = REV ? 1 : 0;
     constexpr int RP = (R + 1) / 2;
     constexpr uint32_t K = kI16Bias;
     constexpr uint32_t K2 = K | (K << 16);
@@ -57,10 +58,6 @@ __device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S,
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    const int pairA = count > 0 ? P.order[first] : -1;
-    const int pairB = count > 1 ? P.order[first + 1] : -1;
-    const PairJob JA = load_job(P, pairA, reverse);
-    const PairJob JB = load_job(P, pairB, reverse);
     const int mmax = imax(JA.m, JB.m);
     const int steps = __builtin_amdgcn_readfirstlane(mmax > 0 ? mmax + W - 1 : 0);
 
@@ -227,30 +224,44 @@ __device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S,
         C.res[wave][p][2] = lj[p];
     }
     __syncthreads();
-    // wave 0 combines; all its lanes compute and store the same values
-    if (wave == 0) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            int b = 0, bi = -1, bj = -1;
-            for (int w = 0; w < kWavesPerBlock; ++w) {
-                const int ob = C.res[w][p][0], oi = C.res[w][p][1], oj = C.res[w][p][2];
-                if (ob > b || (ob == b && ob > 0 && oi < bi)) { b = ob; bi = oi; bj = oj; }
+    for (int p = 0; p < 2; ++p) {
+        int b = 0, bi = -1, bj = -1;
+        for (int w = 0; w < kWavesPerBlock; ++w) {
+            const int ob = C.res[w][p][0], oi = C.res[w][p][1], oj = C.res[w][p][2];
+            if (ob > b) { b = ob; bi = oi; bj = oj; }   // (lower waves hold lower rows)
+        }
+        best[p] = b; row[p] = bi; col[p] = bj;
+    }
+}
+
+template <int R, bool REV>
+__device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S, CoopLds& C, int first,
+                                           int count, int tid) {
+    const int pairs[2] = {count > 0 ? P.order[first] : -1, count > 1 ? P.order[first + 1] : -1};
+    const PairJob J[2] = {load_job(P, pairs[0], REV), load_job(P, pairs[1], REV)};
+    int best[2], row[2], col[2];
+    coop_best<R>(P, S, C, J[0], J[1], tid, best, row, col);
+    // wave 0 writes; all its lanes store the same values
+    if (__builtin_amdgcn_readfirstlane(tid >> 6) != 0) return;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int pair = pairs[p];
+        if (pair < 0) continue;
+        if (!REV) {
+            sw_result res;
+            if (best[p] > 0) {
+                res.score = best[p]; res.q_start = -1; res.q_end = row[p]; res.r_start = -1; res.r_end = col[p];
+            } else {
+                res.score = 0; res.q_start = res.q_end = res.r_start = res.r_end = -1;
             }
-            const int pair = p == 0 ? pairA : pairB;
-            const PairJob& J = p == 0 ? JA : JB;
-            if (pair < 0) continue;
-            if (!reverse) {
-                sw_result res;
-                if (b > 0) { res.score = b; res.q_start = -1; res.q_end = bi; res.r_start = -1; res.r_end = bj; }
-                else { res.score = 0; res.q_start = res.q_end = res.r_start = res.r_end = -1; }
-                P.out[pair] = res;
-            } else if (J.fwd_score > 0) {
-                if (b != J.fwd_score) {
-                    if (tid == 0) push_redo(P, pair);
-                } else {
-                    P.out[pair].q_start = J.fwd_qe - bi;
-                    P.out[pair].r_start = J.fwd_re - bj;
-                }
+            P.out[pair] = res;
+        } else if (J[p].fwd_score > 0) {
+            if (best[p] != J[p].fwd_score) {
+                if (tid == 0) push_redo(P, pair);
+            } else {
+                P.out[pair].q_start = J[p].fwd_qe - row[p];
+                P.out[pair].r_start = J[p].fwd_re - col[p];
             }
         }
     }

@@ -6,12 +6,15 @@
 // For each listed pair the kernel finds the end column (the first column of
 // the end row that holds the score), then the start as the reverse sweep
 // does.  Both are the same search for the row-major-first cell that holds a
-// known score, one pair of pairs per wavefront (64-lane groups), with scores
-// read from the byte tables, so one kernel serves every scheme.  Few pairs
-// are listed, so what counts is the time of one pair: the forward search
-// sweeps only the columns and rows an alignment that ends past the column
-// found can use, and ends at the first hit.  A launch without listed pairs
-// costs its workgroups one load.
+// known score, with scores read from the byte tables, so one kernel serves
+// every scheme: two pairs per wavefront (64-lane groups) up to 512 rows, per
+// workgroup (the cooperative sweep) above.  Few pairs are listed, so what
+// counts is the time of one: the forward search sweeps only the columns and
+// rows an alignment that ends past the column found can use, and in a
+// wavefront ends at the first hit.  A pair of 2000 x 6000 took 7.6 ms in one
+// wavefront, at the end of 1,000,000 mixed pairs, and takes 3.3 in
+// four.  A launch without listed pairs costs its workgroups one load.
+#include "sw_coop.h"
 #include "sw_queue.h"
 
 namespace sw {
@@ -207,10 +210,13 @@ __device__ __forceinline__ PairJob start_job(const KParams& P, const Listed& x) 
     return J;
 }
 
-template <int R>
-__device__ __forceinline__ void redo_pairs(const KParams& P, const SchemeLds& S, uint16_t* wbuf, int pairA, int pairB,
-                                           int lane, const int8_t* lut, const BinInfo* bins,
-                                           unsigned long long* counters) {
+// Redo of two pairs.  search(J, first_hit, row, col) finds the cells of their
+// jobs; max_rows is the most rows it can take, and the thread with `writes`
+// set writes.
+template <class Search>
+__device__ __forceinline__ void redo_pairs(const KParams& P, int pairA, int pairB, int max_rows, bool writes,
+                                           const int8_t* lut, const BinInfo* bins, unsigned long long* counters,
+                                           Search&& search) {
     Listed x[2] = {listed(P, pairA), listed(P, pairB)};
     long long was[2] = {0, 0};
     int bin[2] = {-1, -1};
@@ -220,7 +226,7 @@ __device__ __forceinline__ void redo_pairs(const KParams& P, const SchemeLds& S,
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             J[p] = round == 0 ? end_job(P, x[p]) : start_job(P, x[p]);
-            if (J[p].n > 64 * R) {   // cannot happen: R was chosen for the pair's rows
+            if (J[p].n > max_rows) {   // cannot happen: R was chosen for the pair's rows
                 atomicOr(&P.flags[kFlagInternal], 1);
                 J[p] = no_job();
                 x[p].pair = -1;
@@ -232,7 +238,7 @@ __device__ __forceinline__ void redo_pairs(const KParams& P, const SchemeLds& S,
             }
         }
         int row[2], col[2];
-        find_score<R>(P, S, wbuf, J[0], J[1], round == 0, lane, row, col);
+        search(J, round == 0, row, col);
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             if (x[p].pair < 0) continue;
@@ -246,7 +252,7 @@ __device__ __forceinline__ void redo_pairs(const KParams& P, const SchemeLds& S,
                 x[p].re = J[p].fwd_re + col[p];
                 continue;
             }
-            if (lane == 0) {
+            if (writes) {
                 sw_result* o = P.out + x[p].pair;
                 o->q_start = x[p].qe - row[p];
                 o->r_start = x[p].re - col[p];
@@ -264,35 +270,77 @@ __device__ __forceinline__ void redo_pairs(const KParams& P, const SchemeLds& S,
     }
 }
 
-// (one wavefront per SIMD: the 32-row search then keeps its rows in registers)
+// The entries k and k + 1 of the list, and their rows (the larger).
+__device__ __forceinline__ int listed_rows(const KParams& P, int k, int n, int n_pairs, int (&id)[2]) {
+    int rows = 0;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        id[p] = k + p < n ? __builtin_amdgcn_readfirstlane(P.redo[k + p]) : -1;
+        if (id[p] >= n_pairs) {
+            atomicOr(&P.flags[kFlagInternal], 1);
+            id[p] = -1;
+        }
+        if (id[p] >= 0) rows = imax(rows, (int)(P.q_end[id[p]] - P.q_beg[id[p]]));
+    }
+    return __builtin_amdgcn_readfirstlane(rows);
+}
+
+template <int R>
+__device__ __forceinline__ void redo_wave(const KParams& P, const SchemeLds& S, uint16_t* wbuf, const int (&id)[2],
+                                          int lane, const int8_t* lut, const BinInfo* bins,
+                                          unsigned long long* counters) {
+    redo_pairs(P, id[0], id[1], 64 * R, lane == 0, lut, bins, counters,
+               [&](const PairJob (&J)[2], bool first_hit, int (&row)[2], int (&col)[2]) {
+                   find_score<R>(P, S, wbuf, J[0], J[1], first_hit, lane, row, col);
+               });
+}
+
+template <int R>
+__device__ __forceinline__ void redo_coop(const KParams& P, const SchemeLds& S, CoopLds& C, const int (&id)[2],
+                                          int tid, const int8_t* lut, const BinInfo* bins,
+                                          unsigned long long* counters) {
+    redo_pairs(P, id[0], id[1], kCoopW * R, tid == 0, lut, bins, counters,
+               [&](const PairJob (&J)[2], bool, int (&row)[2], int (&col)[2]) {
+                   int best[2];
+                   __syncthreads();   // the last search's LDS is free
+                   coop_best<R>(P, S, C, J[0], J[1], tid, best, row, col);
+#pragma unroll
+                   for (int p = 0; p < 2; ++p)
+                       if (best[p] != J[p].fwd_score || best[p] == 0) row[p] = kNoRow;
+               });
+}
+
+// (one wavefront per SIMD: few are in flight)
+constexpr int kRedoTall = 512;   // rows above which a workgroup searches together
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1))) void sw_redo_kernel(
     KParams P, const int8_t* lut, const BinInfo* bins, unsigned long long* counters) {
     __shared__ __attribute__((aligned(16))) SchemeLds L;
     __shared__ uint16_t wbufs[kWavesPerBlock * 2 * RefStager<64>::kBuf];
+    __shared__ CoopLds C;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
     int n = __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[kMetaRedo], __ATOMIC_RELAXED));
     n = n < n_pairs ? n : n_pairs;
-    if (2 * kWavesPerBlock * (int)blockIdx.x >= n) return;
+    if (2 * (int)blockIdx.x >= n) return;
     load_schemes(L, P, tid);
     __syncthreads();
     uint16_t* wbuf = wbufs + wave * 2 * RefStager<64>::kBuf;
-    for (int k = 2 * (kWavesPerBlock * (int)blockIdx.x + wave); k < n; k += 2 * kWavesPerBlock * (int)gridDim.x) {
-        int id[2], rows = 0;
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            id[p] = k + p < n ? __builtin_amdgcn_readfirstlane(P.redo[k + p]) : -1;
-            if (id[p] >= n_pairs) {
-                atomicOr(&P.flags[kFlagInternal], 1);
-                id[p] = -1;
-            }
-            if (id[p] >= 0) rows = imax(rows, (int)(P.q_end[id[p]] - P.q_beg[id[p]]));
-        }
-        rows = __builtin_amdgcn_readfirstlane(rows);
-        if (rows <= 256) redo_pairs<4>(P, L, wbuf, id[0], id[1], lane, lut, bins, counters);
-        else if (rows <= 512) redo_pairs<8>(P, L, wbuf, id[0], id[1], lane, lut, bins, counters);
-        else if (rows <= 1024) redo_pairs<16>(P, L, wbuf, id[0], id[1], lane, lut, bins, counters);
-        else redo_pairs<32>(P, L, wbuf, id[0], id[1], lane, lut, bins, counters);
+    int id[2];
+    // the tall pairs first: the same entries in every wavefront, so every
+    // barrier is reached by the whole workgroup
+    for (int k = 2 * (int)blockIdx.x; k < n; k += 2 * (int)gridDim.x) {
+        const int rows = listed_rows(P, k, n, n_pairs, id);
+        if (rows <= kRedoTall) continue;
+        if (rows <= 768) redo_coop<3>(P, L, C, id, tid, lut, bins, counters);
+        else if (rows <= 1024) redo_coop<4>(P, L, C, id, tid, lut, bins, counters);
+        else if (rows <= 1536) redo_coop<6>(P, L, C, id, tid, lut, bins, counters);
+        else redo_coop<8>(P, L, C, id, tid, lut, bins, counters);
+    }
+    for (int k = 2 * ((int)blockIdx.x + (int)gridDim.x * wave); k < n; k += 2 * kWavesPerBlock * (int)gridDim.x) {
+        const int rows = listed_rows(P, k, n, n_pairs, id);
+        if (rows > kRedoTall) continue;
+        if (rows <= 256) redo_wave<4>(P, L, wbuf, id, lane, lut, bins, counters);
+        else redo_wave<8>(P, L, wbuf, id, lane, lut, bins, counters);
     }
 }
 
