@@ -250,8 +250,11 @@ TILES = (128, 64)
 
 
 def tuning_string(table: Table, tile: int = DEFAULT_TILE) -> str:
-    """The sw_create tuning string of a routing table and tile width."""
+    """The sw_create tuning string of a routing table and tile width; an empty
+    table leaves the library's own routing, which depends on a call's size."""
     from .binding import routing_string
+    if not table:
+        return "chunk=%d" % tile
     s = routing_string(16, table)
     return s if tile == DEFAULT_TILE else s + ";chunk=%d" % tile
 
@@ -290,7 +293,8 @@ def tune_batch(batch, dbatch, device: int = 0, sample: int = 50000, repeats: int
                options: str = ""):
     """The routing a batch is timed with: shape rates measured on the batch's
     dominant scheme at its median reference length, the candidate tables of
-    a seeded sample of its pairs, the fastest of them on the batch itself
+    a seeded sample of its pairs and the built-in routing by the size of the
+    call (an empty table), the fastest of them on the batch itself
     (median of `repeats` graph-replayed calls each), then the faster tile
     width for it; the calls are timed with the tuning-string `options`.
     Returns (name, table, candidates, tile)."""
@@ -306,6 +310,7 @@ def tune_batch(batch, dbatch, device: int = 0, sample: int = 50000, repeats: int
     finally:
         probe.close()
     cands = candidate_tables(ql, rl, rates, list(rates), builtin=builtin)
+    cands["by size"] = []   # the built-in routing as calls without a table use it
     name, table, ms = pick_by_timing(dbatch, cands, device, repeats=repeats, log=log, options=options)
     tile = DEFAULT_TILE
     for t in TILES:
