@@ -220,7 +220,7 @@ int sw_poll(sw_handle* h, uint64_t ticket, int wait);
  * sw_align_batch, with the same arguments, results and errors, except that
  * it allocates and frees nothing.  Its planning workspace (sort keys, pair
  * order and work items; 16 bytes per pair) is one static device array of
- * 16 MiB that each GPU the library runs on holds until the process ends;
+ * 20 MiB that each GPU the library runs on holds until the process ends;
  * the handle (created beforehand with sw_create, which does allocate) gives
  * everything else.  The call never captures or replays a graph; its kernels
  * are launched on `stream` and it returns after they have completed.
@@ -342,11 +342,14 @@ int sw_shapes(sw_handle* h, int32_t* precision, int32_t* lanes, int32_t* rows, i
  * shape (lanes[k], rows[k]).  rows_max must increase in steps that are
  * multiples of 16 and end at SW_MAX_QUERY; each shape must be compiled and
  * cover its rows (lanes * rows >= rows_max).  n == 0 restores the built-in
- * routing.  HOST arrays; SW_EINVAL on a malformed table (the routing is then
+ * routing.  An installed table is used for calls of every size; the built-in
+ * int16 routing also depends on the pairs of a call (up to 4096, 8192, 262144
+ * or more).  HOST arrays; SW_EINVAL on a malformed table (the routing is then
  * unchanged).  Results never depend on the routing, only speed does. */
 int sw_set_routing(sw_handle* h, int precision, const int32_t* rows_max, const int32_t* lanes, const int32_t* rows,
                    int n);
-/* The current routing of one precision, in the same form (merged runs). */
+/* The current routing of one precision, in the same form (merged runs): the
+ * installed table, or the one the built-in routing starts from. */
 int sw_get_routing(sw_handle* h, int precision, int32_t* rows_max, int32_t* lanes, int32_t* rows, int capacity,
                    int* n_out);
 
@@ -404,9 +407,9 @@ int sw_last_bin_stats(sw_handle* h, sw_bin_stat* out, int capacity, int* n_out);
  * next batch of the first slot to free up, so work from different requests
  * overlaps on the device.  Results are identical to aligning each request
  * alone.  Each slot holds two handles: merged batches of up to 8192 pairs
- * run with a routing of few bins (16x16 up to 256 rows, 32x16 up to 512,
- * cooperative 256x8 above), which shortens the critical path of small
- * batches; larger ones use the routing of `tuning` (or the built-in one).
+ * run with a routing of few bins and short sweeps (64-lane groups of few rows
+ * up to 512 rows, cooperative groups above), which shortens the critical path
+ * of small batches; larger ones use the routing of `tuning` (or the built-in one).
  * Each handle's call is captured into a graph once, when the server is
  * created, and replayed for every batch.  A server may be driven from
  * several host threads. */

@@ -272,9 +272,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
 // for its column-word kernel, PW and the reference tile PC for its
 // pair-table kernel (the table-lookup kernel keeps 2 and kChunk).
 // Measured: the 9..16-row 16-lane and 11..16-row 32-lane column-word
-// families run dna_large 2.5% faster at 3 (a few spilled registers).  Their
-// pair-table families ran protein 4% slower at 3, and the 32-lane one no
-// faster at 3 with tiles of 64 steps (168 registers, 3 spilled).
+// families gain 2.5% at 3 (a few spilled registers).  At 4 the 1..8-row
+// 16-lane and 5..10-row 32-lane ones made 200,000 DNA pairs 1.6% slower; at 3
+// the 9..16-row pair-table families (174 and 179 registers at 2) gave protein
+// 0.8% and a search nothing.
 #define SW_FAMILY16(W, CW, PW, PC, ...)                                                                       \
     {16, W, family_size<__VA_ARGS__>(), {__VA_ARGS__},                                                        \
      {{&sw_family_kernel<16, W, false, kVarTable, 2, kChunk, __VA_ARGS__>,                                    \

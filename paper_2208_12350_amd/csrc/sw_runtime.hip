@@ -308,6 +308,7 @@ static int find_bin(const sw_handle* h, int prec, int W, int R) {
 // rows go to cooperative 256-lane groups when they are compiled: their
 // per-pair latency is about four times shorter than a 64-lane group's, and
 // that latency bounds small batches and the tails of large ones.
+// (class_bin refines the int16 table by the size of a call.)
 // The int32 routing uses six shapes of 64 to 2048 rows (doubling): int32
 // pairs are rare unless a call forces the precision (references above
 // kI16MaxRef, or scores past the packed range), and every bin a route uses

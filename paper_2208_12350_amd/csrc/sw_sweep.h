@@ -491,11 +491,11 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
 //    rows per lane, 4 for up to 16).  A pair-table lane of more than 8 rows
 //    keeps the maxima of its even and of its odd rows apart (kSets = 2), as
 //    its scores leave fewer bits, and so do the lanes of cooperative groups
-//    (kCoopSets: their long queries leave 2 bits, or 1 for the pair table).  Where the bound does not hold (queries of
-//    more than about 660 DNA or 520 protein residues) the code is left out:
-//    then the column may be too small, when another row of the lane lower
-//    down holds the best score in an earlier column (about 0.05% of related
-//    pairs).  The reverse sweep decides: the prefix box of a column that is
+//    (kCoopSets: their long queries leave 2 bits, or 1 for the pair table).
+//    Where the bound does not hold (queries of more than about 660 DNA or 520
+//    protein residues) the code is left out: then the column may be too
+//    small, when another row of the lane lower down holds the best score in
+//    an earlier column (about 0.05% of related pairs).  The reverse sweep decides: the prefix box of a column that is
 //    too small holds no cell of the best score, so no start is found, the
 //    pair goes to the redo list and sw_redo_kernel looks for its end again.
 //    Reverse: the score S is known, so a cell is looked at only when it can
