@@ -106,7 +106,8 @@ const char* sw_last_error(sw_handle* h);
  *               over a device work queue (default 1)
  *   "graph"     1 = capture the call into a hipGraph and replay it while
  *               the buffers, schemes and options stay the same (the batch
- *               size may change up to the capacity); default 1
+ *               size may change up to the capacity, within a size class of
+ *               the built-in routing: see sw_set_routing); default 1
  *   "validate"  1 = check residue codes (default 1); invalid residues make
  *               the call return SW_EINVAL (results of those pairs undefined)
  *   "precision" 0 = automatic routing (default): a pair runs on the packed
@@ -123,7 +124,9 @@ const char* sw_last_error(sw_handle* h);
  *               grows to the largest batch seen).  Launch grids and captured
  *               graphs are sized for the capacity and read the batch size
  *               from device memory, so one graph serves every batch with the
- *               same buffers and at most that many pairs
+ *               same buffers and at most that many pairs that is of the same
+ *               size class (up to 4096, 8192, 262144 or more pairs; with an
+ *               installed routing table, every batch)
  *   "colpath"   1 = pairs whose scheme has at most 4 residues (and whose
  *               scores plus gap_open and gap_extend fit a byte) read their
  *               substitution scores from per-column words instead of table
@@ -199,7 +202,7 @@ int sw_align_batch(sw_handle* h, const sw_batch* batch, const sw_scheme* schemes
  * oldest (whose status sw_poll still reports).  A submit may also wait for
  * the calls in flight when it must replace what they use: a larger
  * workspace, a new routing table, or a captured graph evicted from the
- * handle's cache of 4.  Errors returned by sw_submit itself (nothing is
+ * handle's cache of 16.  Errors returned by sw_submit itself (nothing is
  * then enqueued and no ticket issued): SW_EINVAL for bad arguments that
  * the host can see (null pointers, bad schemes, the "timing" option set),
  * SW_ENOMEM, SW_EDEVICE. */

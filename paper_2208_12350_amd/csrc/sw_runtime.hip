@@ -205,13 +205,16 @@ struct sw_handle {
     static constexpr int kForks = 8;    // persistent mode spreads bins over up to this many streams
     hipStream_t fork[kForks] = {};
     hipEvent_t fork_ev[kForks + 1] = {};
-    // captured calls, most recently used last (at most kGraphs)
+    // captured calls, most recently used last (at most kGraphs: four for each
+    // size class, as a set of buffers has a graph for every class its calls
+    // fall into; with four in all, two sets of buffers used in three classes
+    // captured again on every call, 4.2 ms for six small calls against 3.4)
     struct GraphEntry {
         GraphKey key;
         hipGraph_t graph;
         hipGraphExec_t exec;
     };
-    static constexpr int kGraphs = 4;
+    static constexpr int kGraphs = 4 * kRouteClasses;
     std::vector<GraphEntry> graphs;
     int64_t n_captures = 0;
     int64_t n_capture_refusals = 0;
