@@ -170,9 +170,10 @@ const char* sw_last_error(sw_handle* h);
  *               smallest accepted value is about 123 MB)
  * Returns SW_OK or SW_EINVAL for an unknown key / bad value. */
 int sw_set_option(sw_handle* h, const char* key, int64_t value);
-/* Read an option, or the read-only "captures" (graphs captured so far) and
+/* Read an option, or the read-only "captures" (graphs captured so far),
  * "capture_refusals" (captures the runtime refused; those calls ran their
- * kernels without a graph). */
+ * kernels without a graph) and "redo_pairs" (pairs of the last finished call
+ * whose end column tied scores left open, so that it was looked for again). */
 int sw_get_option(sw_handle* h, const char* key, int64_t* value);
 
 /* Align every pair of `batch` and write out[i] (a DEVICE pointer to

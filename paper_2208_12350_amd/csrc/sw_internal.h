@@ -123,7 +123,8 @@ enum : int {
     kCtrBinColPairs = kCtrBinColCells + 2 * kMaxBins,   // [2 * kMaxBins] column-path pairs
     kCtrTraceBinCells = kCtrBinColPairs + 2 * kMaxBins,   // [kMaxBins] box cells per path-sweep bin
     kCtrTraceBinPairs = kCtrTraceBinCells + kMaxBins,      // [kMaxBins] pairs per path-sweep bin
-    kNumCounters = kCtrTraceBinPairs + kMaxBins,
+    kCtrRedoPairs = kCtrTraceBinPairs + kMaxBins,          // pairs on the redo list
+    kNumCounters = kCtrRedoPairs + 1,
 };
 
 // Arguments shared by every sweep launch.

@@ -322,6 +322,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     int n = __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[kMetaRedo], __ATOMIC_RELAXED));
     n = n < n_pairs ? n : n_pairs;
     if (2 * (int)blockIdx.x >= n) return;
+    if (blockIdx.x == 0 && tid == 0) counters[kCtrRedoPairs] = (unsigned long long)n;
     load_schemes(L, P, tid);
     __syncthreads();
     uint16_t* wbuf = wbufs + wave * 2 * RefStager<64>::kBuf;

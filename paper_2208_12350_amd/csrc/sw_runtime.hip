@@ -219,7 +219,7 @@ struct sw_handle {
     int64_t n_captures = 0;
     int64_t n_capture_refusals = 0;
 
-    int64_t last_fwd = 0, last_rev = 0, last_i32 = 0;
+    int64_t last_fwd = 0, last_rev = 0, last_i32 = 0, last_redo = 0;
 
     // alignment paths (sw_align_cigar)
     std::vector<BinInfo> tbins;          // path-sweep shapes
@@ -1018,6 +1018,7 @@ int sw_get_option(sw_handle* h, const char* key, int64_t* value) {
     else if (k == "qprofile_used") *value = h->last_qprof;
     else if (k == "pairtable_used") *value = h->last_ptab;
     else if (k == "cigar_workspace") *value = h->opt_path_ws;
+    else if (k == "redo_pairs") *value = h->last_redo;
     else if (k == "captures") *value = h->n_captures;
     else if (k == "capture_refusals") *value = h->n_capture_refusals;
     else return fail(h, SW_EINVAL, "unknown option '%s'", key);
@@ -1039,6 +1040,7 @@ static int complete_slot(sw_handle* h, int k) {
     h->last_fwd = (int64_t)cnt[kCtrFwdCells];
     h->last_rev = (int64_t)cnt[kCtrRevCells];
     h->last_i32 = (int64_t)cnt[kCtrI32Pairs];
+    h->last_redo = (int64_t)cnt[kCtrRedoPairs];
     h->bin_stats.clear();
     h->last_ptab = sl.ptab ? 1 : 0;
     h->last_qprof = sl.qprof ? 1 : 0;
@@ -1112,7 +1114,7 @@ static int complete_slot(sw_handle* h, int k) {
 static uint64_t finish_now(sw_handle* h) {
     const uint64_t t = h->next_ticket++;
     h->finished[t] = sw_handle::Finished{SW_OK, std::string()};
-    h->last_fwd = h->last_rev = h->last_i32 = 0;
+    h->last_fwd = h->last_rev = h->last_i32 = h->last_redo = 0;
     h->bin_stats.clear();
     h->t_plan = h->t_fwd = h->t_rev = 0.f;
     return t;
