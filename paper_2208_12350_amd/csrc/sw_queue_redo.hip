@@ -210,6 +210,18 @@ __device__ __forceinline__ PairJob start_job(const KParams& P, const Listed& x) 
     return J;
 }
 
+// Whether the pair holds a residue outside its scheme's alphabet (a call that
+// does not check them, option validate = 0).  The sweeps and the searches
+// here score such a residue differently, so a search may then fail.
+__device__ __forceinline__ bool has_invalid(const KParams& P, const Listed& x) {
+    const int A = P.alphabet[x.sid], lane = (int)__lane_id();
+    const int n = (int)(P.q_end[x.pair] - x.q0);
+    bool bad = false;
+    for (int i = lane; i < n; i += 64) bad |= P.queries[x.q0 + i] >= A;
+    for (int j = lane; j < x.m0; j += 64) bad |= P.refs[x.r0 + j] >= A;
+    return __builtin_amdgcn_ballot_w64(bad) != 0;
+}
+
 // Redo of two pairs.  search(J, first_hit, row, col) finds the cells of their
 // jobs; max_rows is the most rows it can take, and the thread with `writes`
 // set writes.
@@ -244,7 +256,14 @@ __device__ __forceinline__ void redo_pairs(const KParams& P, int pairA, int pair
             if (x[p].pair < 0) continue;
             // the end row is exact, so a hit elsewhere is an error too
             if (row[p] == kNoRow || (round == 0 && row[p] != J[p].n - 1)) {
-                atomicOr(&P.flags[kFlagReverseMismatch], 1);
+                if (P.validate || !has_invalid(P, x[p])) {
+                    atomicOr(&P.flags[kFlagReverseMismatch], 1);
+                } else if (writes) {
+                    // no result is defined for the pair: it starts where it ends
+                    sw_result* o = P.out + x[p].pair;
+                    o->q_start = x[p].qe;
+                    o->r_start = o->r_end = x[p].re;
+                }
                 x[p].pair = -1;
                 continue;
             }
