@@ -363,7 +363,9 @@ int sw_get_routing(sw_handle* h, int precision, int32_t* rows_max, int32_t* lane
  * with the kernel launch that swept them.  A family launch (option
  * "families") sweeps several bins of one lane width with one kernel: those
  * bins share `launch` and `ms`, so per-launch figures group the entries by
- * (pass, launch). */
+ * (pass, launch).  lanes and rows are the shape the routing chose; with few
+ * queries above 512 residues in a pass the built-in routing's 64-lane bins of
+ * such queries are swept by the launch of the cooperative (256-lane) family. */
 typedef struct sw_bin_stat {
     int32_t pass;        /* 0 forward, 1 reverse, 2 path boxes (sw_align_cigar) */
     int32_t precision;   /* 16 (two pairs packed per register) or 32 */

@@ -352,21 +352,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 }
 
 // Family kernel of the cooperative shapes (see sw_family_kernel): drains the
-// queue of member k's bin, then member k + 1's.
+// queue of member k's bin and of the `more` long bins after it, then
+// member k + 1's.
 template <int VAR, bool REV, int R, class Work>
-__device__ __forceinline__ void coop_member(const KParams& P, Work& K, int bin, int n_pairs, int tid, int wave) {
-    if (bin < 0) return;
-    const int lo_i = VAR == kVarCol ? kMetaItemFirst + bin : kMetaItemSplit + bin;
-    const int hi_i = VAR == kVarCol ? kMetaItemSplit + bin : kMetaItemFirst + bin + 1;
-    const int lo = __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[lo_i], __ATOMIC_RELAXED));
-    const int hi = __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[hi_i], __ATOMIC_RELAXED));
-    if (lo >= hi) return;
-    if (lo < 0 || hi > P.max_items) {
-        if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);
-        return;
+__device__ __forceinline__ void coop_member(const KParams& P, Work& K, int own, int more, int n_pairs, int tid,
+                                            int wave) {
+    if (own < 0) return;
+    for (int bin = own; bin <= own + more; ++bin) {
+        const int lo_i = VAR == kVarCol ? kMetaItemFirst + bin : kMetaItemSplit + bin;
+        const int hi_i = VAR == kVarCol ? kMetaItemSplit + bin : kMetaItemFirst + bin + 1;
+        const int lo = __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[lo_i], __ATOMIC_RELAXED));
+        const int hi = __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[hi_i], __ATOMIC_RELAXED));
+        if (lo >= hi) continue;
+        if (lo < 0 || hi > P.max_items) {
+            if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);
+            continue;
+        }
+        coop_loop(P, K.item(), wave, lo, hi, (VAR == kVarCol ? kMetaColHeads : kMetaHeads) + bin, n_pairs,
+                  [&](int first, int count) { K.template sweep<R, REV>(P, first, count, tid, wave); });
     }
-    coop_loop(P, K.item(), wave, lo, hi, (VAR == kVarCol ? kMetaColHeads : kMetaHeads) + bin, n_pairs,
-              [&](int first, int count) { K.template sweep<R, REV>(P, first, count, tid, wave); });
 }
 
 template <bool REV, int VAR, int... Rs>
@@ -376,7 +380,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
     // a launch for empty bins only costs its workgroups these loads
-    int items = 0;
+    const bool few = P.few_run > 0 && few_long_pairs(P);
+    int items = few ? P.meta[kMetaLong] : 0;
 #pragma unroll
     for (int k = 0; k < (int)sizeof...(Rs); ++k) {
         const int bin = P.fam_bins[k];
@@ -387,7 +392,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     if (__builtin_amdgcn_readfirstlane(items) == 0) return;
     if (!coop_begin<VAR>(P, K, tid)) return;
     int k = 0;
-    ((coop_member<VAR, REV, Rs>(P, K, P.fam_bins[k++], n_pairs, tid, wave)), ...);
+    ((coop_member<VAR, REV, Rs>(P, K, P.fam_bins[k], few ? P.fam_more[k] : 0, n_pairs, tid, wave), ++k), ...);
 }
 
 }  // namespace sw

@@ -86,6 +86,12 @@ __host__ __device__ inline int pairs_per_item(int prec, int W) {
 }
 __host__ __device__ inline int items_per_block(int W) { return W <= 64 ? kWavesPerBlock : 1; }
 
+// Bins of 64-lane int16 shapes above 512 rows.  Their work items have two
+// pairs, as those of a cooperative group, so either kind of kernel can sweep
+// them: cooperative groups of R' = ceil(R / 4) rows per lane when the pass has
+// few pairs above 512 rows (KParams::few_run), the bin's own kernel otherwise.
+__host__ __device__ inline bool long_bin(const BinInfo& b) { return b.prec == 16 && b.W == 64 && b.R > 8; }
+
 // One work item: pairs order[first .. first+count) of one bin.
 struct WorkItem {
     int32_t first;
@@ -108,7 +114,8 @@ enum : int {
     kMetaColHeads = kMetaHeads + kMaxBins,            // [kMaxBins] and of its column-word items
     kMetaBinCol = kMetaColHeads + kMaxBins,           // [kMaxBins] column-path pairs of each bin
     kMetaRedo = kMetaBinCol + kMaxBins,               // pairs on the redo list (reverse pass)
-    kMetaSize = kMetaRedo + 1,
+    kMetaLong = kMetaRedo + 1,                        // int16 pairs in bins above 512 rows
+    kMetaSize = kMetaLong + 1,
 };
 
 // Layout of the 64-bit statistics counters of a call (cleared at its start).
@@ -166,6 +173,13 @@ struct KParams {
     int32_t drift_period[2];
     int32_t drift_sid[2];
     int32_t drift_x[2];          // the largest o - e of their schemes
+    // Launches over the long bins run only when meta[kMetaLong] is at most
+    // few_long (few_run = 1) or only when it is above (-1); other launches have
+    // few_run = 0.  A family launch of cooperative groups always takes its own
+    // bins, and with few_run = 1 also the fam_more[k] long bins that follow
+    // member k's when there are few.
+    int32_t few_long, few_run;
+    int8_t fam_more[kFamilyMax];
     int32_t* redo;               // redo list of the reverse pass (meta[kMetaRedo] pairs; room for n_pairs)
 };
 

@@ -45,6 +45,15 @@ __device__ __forceinline__ void queue_loop(const KParams& P, int lane, int lo, i
     }
 }
 
+// Launches over the long bins (KParams::few_run): whether the pass has few long
+// pairs, and whether the launch leaves them to the other kind of kernel.
+__device__ __forceinline__ bool few_long_pairs(const KParams& P) {
+    return __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[kMetaLong], __ATOMIC_RELAXED)) <= P.few_long;
+}
+__device__ __forceinline__ bool left_to_others(const KParams& P) {
+    return P.few_run != 0 && few_long_pairs(P) != (P.few_run > 0);
+}
+
 // The item range of the launch, read first: a launch for an empty bin (the
 // host does not know which bins are empty) costs its workgroups two loads
 // and an exit.  Returns false when there is nothing to do.
@@ -53,7 +62,7 @@ __device__ __forceinline__ bool launch_range(const KParams& P, int tid, int& lo,
     hi = __atomic_load_n(&P.meta[P.hi_idx], __ATOMIC_RELAXED);
     lo = __builtin_amdgcn_readfirstlane(lo);
     hi = __builtin_amdgcn_readfirstlane(hi);
-    if (lo == hi) return false;
+    if (lo == hi || left_to_others(P)) return false;
     if (lo < 0 || hi > P.max_items || lo > hi) {
         if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);
         return false;
@@ -251,7 +260,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
             items += VAR == kVarCol ? P.meta[kMetaItemSplit + bin] - P.meta[kMetaItemFirst + bin]
                                     : P.meta[kMetaItemFirst + bin + 1] - P.meta[kMetaItemSplit + bin];
     }
-    if (__builtin_amdgcn_readfirstlane(items) == 0) return;
+    if (__builtin_amdgcn_readfirstlane(items) == 0 || left_to_others(P)) return;
     if constexpr (VAR == kVarPtab) {
         if (P.ptab_sid < 0 || P.ptab_sid >= SW_MAX_SCHEMES || P.ptab_dim < 2 || P.ptab_dim > kPtabMaxDim) {
             if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);

@@ -130,6 +130,13 @@ struct sw_handle {
     std::vector<BinInfo> bins;
     std::vector<int> route[2];          // per precision (int16, int32) and 16-row bucket: bin
     bool builtin16 = true;              // int16 routing is the built-in one (by batch size, see class_bin)
+    int pin_class = -1;                 // size class of every call (pin_routing), or -1
+    const FamilyEntry* coop = nullptr;  // the cooperative family, its members' bins and the long
+    int8_t coop_bin[kFamilyMax] = {}, coop_more[kFamilyMax] = {};   // bins after each (long_bin)
+    // per pass and score range (0 table, 1 column) of the last enqueued call:
+    // launch and event slot of the cooperative kernel that takes the long
+    // bins' items when there are few (-1: none)
+    int32_t few_launch[2][2] = {{-1, -1}, {-1, -1}}, few_slot[2][2] = {{-1, -1}, {-1, -1}};
     std::vector<int> class_route[kRouteClasses][2];   // the routing that calls of a size class use
     std::vector<int8_t> lut;            // device copy of class_route
     std::vector<char> bin_used[kRouteClasses];   // bins some route points at
@@ -196,7 +203,7 @@ struct sw_handle {
     // swept the bin (index within its pass, or -1), the family of a family
     // launch (rows per lane of its first and last shape, else 0) and its
     // event slot ("timing" = 2)
-    static constexpr int kFamLaunches = 16;
+    static constexpr int kFamLaunches = 2 * 10;   // families times score ranges, at most
     std::vector<int32_t> bin_launch, bin_fam_hi, bin_fam_lo, bin_fam_slot, bin_fam_waves, bin_fam_tile;
     std::vector<hipEvent_t> fam_ev;     // [pass][kFamLaunches][start, end]
     std::vector<sw_bin_stat> bin_stats;
@@ -366,6 +373,10 @@ static void default_routing(sw_handle* h, int sel) {
 //     pairs 7.36 against 6.68), above 1024 rows up to 262144 pairs (2000
 //     residues, 16384 pairs: 22.0 against 22.8).  Batches of more pairs have
 //     enough of every length.
+// A call of many pairs may still have few long ones, which then take as long
+// as one of them: the kernels themselves choose between the two forms for the
+// queries above 512 rows that go to 64-lane groups, by their number in the
+// pass (kFewLong).
 static int class_bin(const sw_handle* h, int cls, int rows) {
     const int base = h->route[0][rows / 16 - 1];
     int W = 0, step = 1;
@@ -376,6 +387,36 @@ static int class_bin(const sw_handle* h, int cls, int rows) {
     const int R = ((rows + W - 1) / W + step - 1) / step * step;
     const int b = find_bin(h, 16, W, R);
     return b >= 0 ? b : base;
+}
+
+// Passes of up to this many int16 pairs above 512 rows sweep those of the long
+// bins by cooperative groups: two pairs for every SIMD of the device, so that
+// with fewer the 64-lane sweeps would leave SIMDs idle and the time is that of
+// one sweep.  Measured, 64-lane against cooperative: 300,000 pairs of 100-150
+// residues and 10 of 2000, DNA 6.2 ms against 2.9 and protein 8.4 against 3.4;
+// and 2000 of 2000, 12.7 against 6.3 and 15.9 against 7.9; 100,000 and 2000 of
+// 1000, 4.4 against 2.4 and 4.2 against 2.9.  Above the limit: 300,000 and 4000
+// of 1000, 5.7 against 5.1 and 5.6 against 6.4; 8000 of 700, 5.3 against 5.8 and
+// 6.1 against 7.1; 50,000 mixed pairs (about 5400 long) 9.9 against 10.7.
+constexpr int kFewLong = 2048;
+
+// Rows per lane of the cooperative shape that sweeps long bin e.
+static int coop_rows(const BinInfo& e) { return (e.R + 3) / 4; }
+
+// The cooperative family's bins, and the long bins between each and the next:
+// the bins are in order of their rows, and shapes above 512 rows have 64 or
+// 256 lanes.
+static void init_coop(sw_handle* h) {
+    h->coop = shape_family(16, 256, 8, false);
+    for (int k = 0; h->coop && k < h->coop->n; ++k) {
+        const int b = find_bin(h, 16, 256, h->coop->rows[k]);
+        int n = 0;
+        while (b >= 0 && b + n + 1 < (int)h->bins.size() && long_bin(h->bins[b + n + 1]) &&
+               coop_rows(h->bins[b + n + 1]) == h->coop->rows[k])
+            ++n;
+        h->coop_bin[k] = (int8_t)b;
+        h->coop_more[k] = (int8_t)n;
+    }
 }
 
 static void rebuild_lut(sw_handle* h) {
@@ -556,6 +597,8 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         h->bin_fam_slot[i] = -1;
     }
     int n_launch = 0;   // launches of this pass
+    for (int v = 0; v < 2; ++v) h->few_launch[pass][v] = h->few_slot[pass][v] = -1;
+    K.few_long = kFewLong;
     if (timing && h->opt_mode == 1) HIP_TRY(h, hipEventRecord(h->ev[pass == 0 ? 1 : 3], stream));
     if (h->opt_mode == 1) {
         // Bins go round-robin, longest first, to the forked streams, which
@@ -592,29 +635,41 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
             launchable[b] = h->bin_used[cls][b] && !(one_length && b != only16 && b != only32) &&
                             !(C.i16_limit < 0 && h->bins[b].prec == 16) &&   // (max_score is at least 1)
                             !(h->opt_max_query > 0 && h->bin_min_query[cls][b] > h->opt_max_query);
+        // score ranges (1 column words, 0 the others) whose launchable long
+        // bins cooperative groups take when there are few (an installed
+        // routing table holds as it is)
+        bool few[2] = {false, false};
+        for (int b = 0; b < n_bins; ++b) {
+            const BinInfo& e = h->bins[b];
+            if (!launchable[b] || !long_bin(e) || !h->builtin16 || !h->coop) continue;
+            few[1] |= any_col && e.col;
+            few[0] |= !(e.col && all_col) && table_var(h, e, K, 0) != kVarQprof;
+        }
         // Family launches (default tile): one kernel per family, score
         // source and pass takes the items of all its launchable member bins;
         // the bins it covers get no launch of their own below.
         std::vector<char> covered(2 * n_bins, 0);
         int fam_slot = 0;
-        if (h->opt_families && h->opt_chunk == kChunk) {
+        const bool families = h->opt_families && h->opt_chunk == kChunk;
+        if (families) {
             std::vector<const FamilyEntry*> seen;
             for (int b1 = 0; b1 < n_bins; ++b1) {
                 // the launch with most of the pairs first: the narrow shapes
                 // when every pair is int32 (10,007 protein pairs 1.97 ms,
                 // 2.16 with the wide ones first)
                 const int b = C.i16_limit < 0 ? n_bins - 1 - b1 : b1;
-                if (!launchable[b]) continue;
+                if (!launchable[b] && !((few[0] || few[1]) && h->bins[b].W > 64)) continue;
                 const FamilyEntry* f = shape_family(h->bins[b].prec, h->bins[b].W, h->bins[b].R,
                                                     C.i16_limit < 0);
                 if (!f || std::find(seen.begin(), seen.end(), f) != seen.end()) continue;
                 seen.push_back(f);
                 for (int v = 1; v >= 0; --v) {
                     int var = -1, members = 0;
+                    const bool take_long = f == h->coop && few[v];
                     for (int k = 0; k < kFamilyMax; ++k) K.fam_bins[k] = -1;
                     for (int k = 0; k < f->n; ++k) {
                         const int mb = find_bin(h, f->prec, f->lanes_of(k), f->rows[k]);
-                        if (mb < 0 || !launchable[mb]) continue;
+                        if (mb < 0 || !(launchable[mb] || take_long)) continue;
                         const BinInfo& m = h->bins[mb];
                         if (v == 1 ? !(any_col && m.col) : (m.col && all_col)) continue;
                         const int mv = table_var(h, m, K, v);
@@ -627,9 +682,19 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                     // shape's own kernel (measured: small batches on three
                     // bins of different widths ran 15% slower)
                     if (members < 2 || !f->k[var][pass] || fam_slot >= sw_handle::kFamLaunches) continue;
+                    if (take_long) {
+                        memcpy(K.fam_more, h->coop_more, sizeof(K.fam_more));
+                        K.few_run = 1;
+                        h->few_launch[pass][v] = n_launch;
+                        h->few_slot[pass][v] = fam_slot;
+                    } else if (few[v] && f->prec == 16 && long_bin(h->bins[find_bin(h, 16, f->W, f->rows[0])])) {
+                        K.few_run = -1;
+                    } else {
+                        K.few_run = 0;
+                    }
                     for (int k = 0; k < f->n; ++k) {
                         const int mb = K.fam_bins[k];
-                        if (mb < 0) continue;
+                        if (mb < 0 || !launchable[mb]) continue;
                         covered[2 * mb + v] = 1;
                         const int i2 = bin_ev_index(pass, mb, v, 0) / 2;
                         h->bin_launch[i2] = n_launch;
@@ -672,6 +737,18 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                 h->bin_launch[bin_ev_index(pass, b, v, 0) / 2] = n_launch++;
                 hipStream_t ls = forks > 1 ? h->fork[launched++ % forks] : stream;
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 0)], ls));
+                const int cb = find_bin(h, 16, 256, coop_rows(e));
+                K.few_run = 0;
+                if (few[v] && long_bin(e) && var != kVarQprof && cb >= 0) {
+                    if (!families) {   // (a family launch takes them otherwise)
+                        K.few_run = 1;
+                        const int64_t most = std::min<int64_t>(cap / e.ppw + 1, h->resident_blocks[0][pass][var][cb]);
+                        hipLaunchKernelGGL(shape_kernel(16, 256, coop_rows(e), pass != 0, var), dim3((int)most),
+                                           dim3(kBlock), 0, ls, K);
+                        HIP_TRY(h, hipGetLastError());
+                    }
+                    K.few_run = -1;
+                }
                 hipLaunchKernelGGL(shape_kernel(e.prec, e.W, e.R, pass != 0, var, nw == 1), dim3(blocks), dim3(kBlock),
                                    0, ls, K);
                 HIP_TRY(h, hipGetLastError());
@@ -693,12 +770,15 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                 set_range(K, b, v);
                 const int items = h->h_meta[K.hi_idx] - h->h_meta[K.lo_idx];
                 if (items <= 0) continue;
-                const int blocks = (items + items_per_block(e.W) - 1) / items_per_block(e.W);
                 const int var = table_var(h, e, K, v);
                 const int nw = narrow_tile(h, e, var);
+                const bool coop = long_bin(e) && h->builtin16 && h->coop && var != kVarQprof &&
+                                  h->h_meta[kMetaLong] <= kFewLong;
+                const int W = coop ? 256 : e.W, R = coop ? coop_rows(e) : e.R;
+                const int blocks = (items + items_per_block(W) - 1) / items_per_block(W);
                 h->bin_launch[bin_ev_index(pass, b, v, 0) / 2] = n_launch++;
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 0)], stream));
-                hipLaunchKernelGGL(shape_kernel(e.prec, e.W, e.R, pass != 0, var, nw == 1), dim3(blocks), dim3(kBlock),
+                hipLaunchKernelGGL(shape_kernel(e.prec, W, R, pass != 0, var, nw == 1), dim3(blocks), dim3(kBlock),
                                    0, stream, K);
                 HIP_TRY(h, hipGetLastError());
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 1)], stream));
@@ -785,12 +865,7 @@ static bool init_paths(sw_handle* h) {
     return ok;
 }
 
-void pin_routing(sw_handle* h, int64_t pairs) {
-    if (!h->builtin16) return;
-    h->route[0] = h->class_route[route_class(pairs)][0];
-    h->builtin16 = false;
-    rebuild_lut(h);
-}
+void pin_routing(sw_handle* h, int64_t pairs) { h->pin_class = route_class(pairs); }
 
 extern "C" {
 
@@ -809,6 +884,7 @@ sw_handle* sw_create(int device, const char* tuning) {
     // chunk costs its own planning and walk tails
     if (ok && prop.totalGlobalMem / 2 > (size_t)h->opt_path_ws) h->opt_path_ws = (int64_t)(prop.totalGlobalMem / 2);
     build_bins(h);
+    init_coop(h);
     for (int sel = 0; sel < 2; ++sel) {
         h->route[sel].assign(kLutRows, -1);
         default_routing(h, sel);
@@ -1042,6 +1118,15 @@ static int complete_slot(sw_handle* h, int k) {
     h->last_i32 = (int64_t)cnt[kCtrI32Pairs];
     h->last_redo = (int64_t)cnt[kCtrRedoPairs];
     h->bin_stats.clear();
+    // whether cooperative groups swept long bin b's items (there were few)
+    auto few_swept = [&](int pass, int b, int v) -> bool {
+        if (h->few_launch[pass][v] < 0 || !long_bin(h->bins[b])) return false;
+        uint64_t n = 0;
+        for (int q = 0; q < (int)h->bins.size(); ++q) {
+            if (h->bins[q].prec == 16 && h->bins[q].W * h->bins[q].R > 512) n += cnt[kCtrBinPairs + pass * kMaxBins + q];
+        }
+        return n <= (uint64_t)kFewLong;
+    };
     h->last_ptab = sl.ptab ? 1 : 0;
     h->last_qprof = sl.qprof ? 1 : 0;
     for (int pass = 0; pass < 2; ++pass)
@@ -1072,6 +1157,12 @@ static int complete_slot(sw_handle* h, int k) {
                 st.family_lo = known ? h->bin_fam_lo[i2] : 0;
                 st.family_waves = known ? h->bin_fam_waves[i2] : 0;
                 if (known && h->bin_fam_tile[i2] > 0) st.tile = h->bin_fam_tile[i2];
+                if (few_swept(pass, b, v)) {
+                    st.launch = h->few_launch[pass][v];
+                    st.family_hi = h->coop->rows[0];
+                    st.family_lo = h->coop->rows[h->coop->n - 1];
+                    st.family_waves = h->coop->waves[kVarTable];
+                }
                 h->bin_stats.push_back(st);
             }
     h->t_plan = h->t_fwd = h->t_rev = 0.f;
@@ -1088,7 +1179,8 @@ static int complete_slot(sw_handle* h, int k) {
                 // item ranges; no mode launches a bin no route points at)
                 const int b = find_bin(h, st.precision, st.lanes, st.rows);
                 const int i = bin_ev_index(st.pass, b, st.column == 1 ? 1 : 0, 0);
-                const int slot = (size_t)(i / 2) < h->bin_fam_slot.size() ? h->bin_fam_slot[i / 2] : -1;
+                int slot = (size_t)(i / 2) < h->bin_fam_slot.size() ? h->bin_fam_slot[i / 2] : -1;
+                if (few_swept(st.pass, b, st.column == 1 ? 1 : 0)) slot = h->few_slot[st.pass][st.column == 1 ? 1 : 0];
                 if (slot >= 0) {
                     // a family launch: its time, shared by its bins
                     const hipEvent_t* fe = &h->fam_ev[(st.pass * sw_handle::kFamLaunches + slot) * 2];
@@ -1345,7 +1437,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
         h->last_col_ok[s] = K.col_ok[s];
     }
 
-    const int cls = route_class(P);
+    const int cls = h->pin_class >= 0 ? h->pin_class : route_class(P);
     const bool use_graph = h->opt_mode == 1 && h->opt_graph != 0 && !timing && !no_alloc;
     GraphKey key;
     memset(&key, 0, sizeof(key));
