@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     const int n_pairs = __builtin_amdgcn_readfirstlane(*P.n_dev);
     // a launch for empty bins only costs its workgroups these loads
     const bool few = P.few_run > 0 && few_long_pairs(P);
-    int items = few ? P.meta[kMetaLong] : 0;
+    int items = few ? P.meta[P.few_idx] : 0;
 #pragma unroll
     for (int k = 0; k < (int)sizeof...(Rs); ++k) {
         const int bin = P.fam_bins[k];

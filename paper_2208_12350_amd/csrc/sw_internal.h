@@ -114,8 +114,7 @@ enum : int {
     kMetaColHeads = kMetaHeads + kMaxBins,            // [kMaxBins] and of its column-word items
     kMetaBinCol = kMetaColHeads + kMaxBins,           // [kMaxBins] column-path pairs of each bin
     kMetaRedo = kMetaBinCol + kMaxBins,               // pairs on the redo list (reverse pass)
-    kMetaLong = kMetaRedo + 1,                        // int16 pairs in bins above 512 rows
-    kMetaSize = kMetaLong + 1,
+    kMetaSize = kMetaRedo + 1,
 };
 
 // Layout of the 64-bit statistics counters of a call (cleared at its start).
@@ -131,7 +130,7 @@ enum : int {
     kCtrTraceBinCells = kCtrBinColPairs + 2 * kMaxBins,   // [kMaxBins] box cells per path-sweep bin
     kCtrTraceBinPairs = kCtrTraceBinCells + kMaxBins,      // [kMaxBins] pairs per path-sweep bin
     kCtrRedoPairs = kCtrTraceBinPairs + kMaxBins,          // pairs on the redo list
-    kNumCounters = kCtrRedoPairs + 1,
+    kNumCounters = kCtrRedoPairs + 2,   // (even, for whole 16-byte units in the copy to the host)
 };
 
 // Arguments shared by every sweep launch.
@@ -165,7 +164,16 @@ struct KParams {
     int32_t ptab_dim;            // its D = alphabet + 1
     int32_t qprof;               // 1: the forward pass may use the query profile of queries[0 .. qprof_n)
     int32_t qprof_n;
+    // Launches over the long bins run only when meta[few_idx], the int16 pairs
+    // above 512 rows, is at most few_long (few_run = 1) or only when it is above
+    // (-1); other launches have few_run = 0.  A family launch of cooperative
+    // groups always takes its own bins, and with few_run = 1 also the fam_more[k]
+    // long bins that follow member k's when there are few.  (Beside fam_bins: a
+    // kernel's first read of another line of its arguments takes microseconds.)
+    int32_t few_long;
+    int16_t few_idx, few_run;
     int8_t fam_bins[kFamilyMax];   // family launch: member k's bin, or -1 (not launched)
+    int8_t fam_more[kFamilyMax];
     // Drifted sweeps (sw_sweep.h), [0] column words, [1] pair table and query
     // profile: the gap extension cost of their schemes, the steps between
     // renormalisations, one of their schemes (for empty lane groups).
@@ -173,13 +181,6 @@ struct KParams {
     int32_t drift_period[2];
     int32_t drift_sid[2];
     int32_t drift_x[2];          // the largest o - e of their schemes
-    // Launches over the long bins run only when meta[kMetaLong] is at most
-    // few_long (few_run = 1) or only when it is above (-1); other launches have
-    // few_run = 0.  A family launch of cooperative groups always takes its own
-    // bins, and with few_run = 1 also the fam_more[k] long bins that follow
-    // member k's when there are few.
-    int32_t few_long, few_run;
-    int8_t fam_more[kFamilyMax];
     int32_t* redo;               // redo list of the reverse pass (meta[kMetaRedo] pairs; room for n_pairs)
 };
 

@@ -178,7 +178,7 @@ static_assert(kMaxBins <= 128, "bin ranges are scanned by two wavefronts");
 
 __global__ __launch_bounds__(kBinScanThreads) void sw_plan_bins_kernel(const BinInfo* bins, int n_bins,
                                                                         int32_t* hist, int32_t* meta) {
-    __shared__ int32_t s_tot[2], s_base, s_long;
+    __shared__ int32_t s_tot[2], s_base;
     __shared__ int32_t wave_tot[kBinScanThreads / 64];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int b = blockIdx.x;
@@ -214,13 +214,11 @@ __global__ __launch_bounds__(kBinScanThreads) void sw_plan_bins_kernel(const Bin
     }
     const int32_t col = real && bins[t].col ? hist[kHistCol + t] : 0;
     const int32_t ppw = real ? bins[t].ppw : 1;
-    if (t == 0) s_long = 0;
     const int32_t col_items = (col + ppw - 1) / ppw;
     const int32_t items = col_items + (pairs - col + ppw - 1) / ppw;
     const int32_t ipos = wave_scan(items, lane) - items;
     __syncthreads();
     const int32_t total = s_tot[0] + s_tot[1];
-    if (real && bins[t].prec == 16 && bins[t].W * bins[t].R > 512) atomicAdd(&s_long, pairs);
     __syncthreads();
     if (lane == 63 && wave < 2) s_tot[wave] = ipos + items;
     __syncthreads();
@@ -237,7 +235,6 @@ __global__ __launch_bounds__(kBinScanThreads) void sw_plan_bins_kernel(const Bin
         meta[kMetaBinFirst + kMaxBins] = total;
         meta[kMetaItemFirst + kMaxBins] = s_tot[0] + s_tot[1];
         meta[kMetaRedo] = 0;
-        meta[kMetaLong] = s_long;
     }
 }
 

@@ -133,6 +133,7 @@ struct sw_handle {
     int pin_class = -1;                 // size class of every call (pin_routing), or -1
     const FamilyEntry* coop = nullptr;  // the cooperative family, its members' bins and the long
     int8_t coop_bin[kFamilyMax] = {}, coop_more[kFamilyMax] = {};   // bins after each (long_bin)
+    int n_long_bins = 0;                // int16 bins above 512 rows, the first of all
     // per pass and score range (0 table, 1 column) of the last enqueued call:
     // launch and event slot of the cooperative kernel that takes the long
     // bins' items when there are few (-1: none)
@@ -408,6 +409,9 @@ static int coop_rows(const BinInfo& e) { return (e.R + 3) / 4; }
 // 256 lanes.
 static void init_coop(sw_handle* h) {
     h->coop = shape_family(16, 256, 8, false);
+    h->n_long_bins = 0;
+    for (const BinInfo& e : h->bins)
+        if (e.prec == 16 && e.W * e.R > 512) ++h->n_long_bins;
     for (int k = 0; h->coop && k < h->coop->n; ++k) {
         const int b = find_bin(h, 16, 256, h->coop->rows[k]);
         int n = 0;
@@ -599,6 +603,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
     int n_launch = 0;   // launches of this pass
     for (int v = 0; v < 2; ++v) h->few_launch[pass][v] = h->few_slot[pass][v] = -1;
     K.few_long = kFewLong;
+    K.few_idx = (int16_t)(kMetaBinFirst + h->n_long_bins);
     if (timing && h->opt_mode == 1) HIP_TRY(h, hipEventRecord(h->ev[pass == 0 ? 1 : 3], stream));
     if (h->opt_mode == 1) {
         // Bins go round-robin, longest first, to the forked streams, which
@@ -773,7 +778,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                 const int var = table_var(h, e, K, v);
                 const int nw = narrow_tile(h, e, var);
                 const bool coop = long_bin(e) && h->builtin16 && h->coop && var != kVarQprof &&
-                                  h->h_meta[kMetaLong] <= kFewLong;
+                                  h->h_meta[K.few_idx] <= kFewLong;
                 const int W = coop ? 256 : e.W, R = coop ? coop_rows(e) : e.R;
                 const int blocks = (items + items_per_block(W) - 1) / items_per_block(W);
                 h->bin_launch[bin_ev_index(pass, b, v, 0) / 2] = n_launch++;
@@ -1122,9 +1127,7 @@ static int complete_slot(sw_handle* h, int k) {
     auto few_swept = [&](int pass, int b, int v) -> bool {
         if (h->few_launch[pass][v] < 0 || !long_bin(h->bins[b])) return false;
         uint64_t n = 0;
-        for (int q = 0; q < (int)h->bins.size(); ++q) {
-            if (h->bins[q].prec == 16 && h->bins[q].W * h->bins[q].R > 512) n += cnt[kCtrBinPairs + pass * kMaxBins + q];
-        }
+        for (int q = 0; q < h->n_long_bins; ++q) n += cnt[kCtrBinPairs + pass * kMaxBins + q];
         return n <= (uint64_t)kFewLong;
     };
     h->last_ptab = sl.ptab ? 1 : 0;
