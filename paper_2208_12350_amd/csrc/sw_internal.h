@@ -164,14 +164,13 @@ struct KParams {
     int32_t ptab_dim;            // its D = alphabet + 1
     int32_t qprof;               // 1: the forward pass may use the query profile of queries[0 .. qprof_n)
     int32_t qprof_n;
-    // Launches over the long bins run only when meta[few_idx], the int16 pairs
-    // above 512 rows, is at most few_long (few_run = 1) or only when it is above
-    // (-1); other launches have few_run = 0.  A family launch of cooperative
+    // Launches over the long bins run only when meta[few_idx] - meta[few_sub], the
+    // pairs of a run of bins above 512 rows, is at most few_long (few_run = 1) or
+    // only when it is above (-1); other launches have few_run = 0.  A family launch of cooperative
     // groups always takes its own bins, and with few_run = 1 also the fam_more[k]
     // long bins that follow member k's when there are few.  (Beside fam_bins: a
     // kernel's first read of another line of its arguments takes microseconds.)
-    int32_t few_long;
-    int16_t few_idx, few_run;
+    int16_t few_long, few_idx, few_sub, few_run;
     int8_t fam_bins[kFamilyMax];   // family launch: member k's bin, or -1 (not launched)
     int8_t fam_more[kFamilyMax];
     // Drifted sweeps (sw_sweep.h), [0] column words, [1] pair table and query
@@ -203,9 +202,11 @@ constexpr int kI16Limit = 0x7BFF - kI16Bias - 127;
 constexpr int kI16MaxRef = 32000;
 
 // Classification inputs: lut[sel * kLutRows + (n-1)/16] gives the bin of a
-// pair with query length n, where sel = 0 for the packed int16 path and 1
-// for int32; a pair takes int16 when min(n, m) * max_score[s] <= i16_limit.
+// pair with query length n, where sel is kLutI16Col for the packed int16 path
+// with column words, kLutI32 for int32 and kLutI16 for other int16 pairs; a
+// pair takes int16 when min(n, m) * max_score[s] <= i16_limit.
 constexpr int kLutRows = SW_MAX_QUERY / 16;
+enum : int { kLutI16Col = 0, kLutI32 = 1, kLutI16 = 2, kLutSels = 3 };
 
 // Drifted sweeps: the steps between renormalisations of a scheme with gap
 // costs o and e, or 0 when it cannot take them.  The drift of a period plus

@@ -110,7 +110,8 @@ __global__ __launch_bounds__(THREADS) void sw_classify_kernel(KParams P, Classif
                 const int64_t mn = n < m ? n : m;
                 const int sel = (mn * C.max_score[s] <= C.i16_limit && m <= kI16MaxRef) ? 0 : 1;
                 if (sel && !P.reverse) atomicAdd(&s_i32, 1);
-                const int bin = lut[sel * kLutRows + (int)((n - 1) / 16)];
+                const int lut_sel = sel ? kLutI32 : C.col_ok[s] ? kLutI16Col : kLutI16;
+                const int bin = lut[lut_sel * kLutRows + (int)((n - 1) / 16)];
                 // within a bin: pairs of column-path schemes first (the bin's
                 // column-word kernel takes them), each part by decreasing
                 // reference length; only packed-int16 pairs use column words

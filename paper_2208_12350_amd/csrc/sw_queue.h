@@ -48,7 +48,8 @@ __device__ __forceinline__ void queue_loop(const KParams& P, int lane, int lo, i
 // Launches over the long bins (KParams::few_run): whether the pass has few long
 // pairs, and whether the launch leaves them to the other kind of kernel.
 __device__ __forceinline__ bool few_long_pairs(const KParams& P) {
-    return __builtin_amdgcn_readfirstlane(__atomic_load_n(&P.meta[P.few_idx], __ATOMIC_RELAXED)) <= P.few_long;
+    const int n = __atomic_load_n(&P.meta[P.few_idx], __ATOMIC_RELAXED) - __atomic_load_n(&P.meta[P.few_sub], __ATOMIC_RELAXED);
+    return __builtin_amdgcn_readfirstlane(n) <= P.few_long;
 }
 __device__ __forceinline__ bool left_to_others(const KParams& P) {
     return P.few_run != 0 && few_long_pairs(P) != (P.few_run > 0);

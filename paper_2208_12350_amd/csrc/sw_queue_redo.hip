@@ -246,7 +246,7 @@ __device__ __forceinline__ void redo_pairs(const KParams& P, int pairA, int pair
             if (round == 0 && x[p].pair >= 0) {
                 const PairJob old = start_job(P, x[p]);   // what the statistics counted
                 was[p] = (long long)old.n * old.m;
-                bin[p] = lut[(old.n - 1) / 16];
+                bin[p] = lut[(P.col_ok[x[p].sid] ? kLutI16Col : kLutI16) * kLutRows + (old.n - 1) / 16];
             }
         }
         int row[2], col[2];

@@ -75,7 +75,7 @@ struct Workspace {
     int64_t cap;
 };
 
-constexpr int kLutEntries = 2 * kLutRows;   // per size class
+constexpr int kLutEntries = kLutSels * kLutRows;   // per size class
 
 // Size classes of a call, by its pairs: the built-in int16 routing differs
 // between them (see class_bin).
@@ -134,13 +134,14 @@ struct sw_handle {
     const FamilyEntry* coop = nullptr;  // the cooperative family, its members' bins and the long
     int8_t coop_bin[kFamilyMax] = {}, coop_more[kFamilyMax] = {};   // bins after each (long_bin)
     int n_long_bins = 0;                // int16 bins above 512 rows, the first of all
+    int few_from[2] = {0, 0};           // the first of them that the last enqueued call counts, per score range (few_first)
     // per pass and score range (0 table, 1 column) of the last enqueued call:
     // launch and event slot of the cooperative kernel that takes the long
     // bins' items when there are few (-1: none)
     int32_t few_launch[2][2] = {{-1, -1}, {-1, -1}}, few_slot[2][2] = {{-1, -1}, {-1, -1}};
-    std::vector<int> class_route[kRouteClasses][2];   // the routing that calls of a size class use
+    std::vector<int> class_route[kRouteClasses][kLutSels];   // the routing that calls of a size class use
     std::vector<int8_t> lut;            // device copy of class_route
-    std::vector<char> bin_used[kRouteClasses];   // bins some route points at
+    std::vector<char> bin_used[kRouteClasses];   // bit sel: bins that route sel points at
     bool lut_dirty = true;
     std::vector<int> resident_blocks[2][2][kNumVars];   // per tile, pass, score source and bin: workgroups the device holds at once
     std::vector<std::pair<QueueFn, int>> fam_resident;  // per family kernel: workgroups the device holds at once
@@ -355,6 +356,12 @@ static void default_routing(sw_handle* h, int sel) {
     }
 }
 
+// Above 512 rows: the most that the built-in routing sends to 64-lane groups.
+static int most_rows64(int cls, bool col) {
+    const int most[kRouteClasses] = {512, col ? 768 : 1024, 1024, SW_MAX_QUERY};
+    return most[cls];
+}
+
 // Bin of the built-in int16 routing for queries of up to `rows` residues (a
 // multiple of 16) in calls of one size class.  The device runs 1024
 // wavefronts at once, one on each SIMD, before they share SIMDs, so with few
@@ -369,19 +376,29 @@ static void default_routing(sw_handle* h, int sel) {
 //     of every size (100 residues: 240 us against 262 in 64 lanes);
 //   * long queries take cooperative groups, whose sweep of a pair is about
 //     four times shorter, until there are enough of them to fill the device
-//     with 64-lane groups, which need fewer instructions per cell: above 512
-//     rows up to 8192 pairs (1000 DNA residues 4.05 ms against 4.38; 16384
-//     pairs 7.36 against 6.68), above 1024 rows up to 262144 pairs (2000
-//     residues, 16384 pairs: 22.0 against 22.8).  Batches of more pairs have
-//     enough of every length.
+//     with 64-lane groups, which need fewer instructions per cell.  Column-word
+//     sweeps of few rows and pair-table sweeps fill it sooner.  Calls of one
+//     length, ms in 64 lanes against cooperative groups:
+//       rows             2048 pairs    4096          6144          8192          16384
+//        700 column      0.98  0.77    1.11  1.29    1.94  1.92    1.96  2.36    3.14  4.64
+//            pair table  1.00  0.89    1.18  1.59    1.53  2.28    2.38  3.00    3.54  5.82
+//       1000 column      2.29  1.12    2.85  1.99    3.27  2.75    3.81  3.87    5.82  6.99
+//            pair table  1.74  1.29    2.93  2.52    2.61  3.48    4.27  4.59    7.18  9.02
+//       1600 column      5.15  2.33    5.37  4.15    6.41  6.22    7.92  8.13    12.7  15.6
+//            pair table  4.31  2.76    6.71  5.58    8.03  7.43    7.94  9.86    16.8  19.6
+//     So up to 4096 pairs all take cooperative groups; up to 8192 pairs those
+//     above 768 rows with column words and above 1024 without; up to 262144
+//     those above 1024, of which calls of mixed lengths have too few to fill
+//     the device (35,000 mixed pairs have 1750).  (Byte-table lookups cross
+//     earlier, at about 3000 pairs of any length, and take the pair table's line.)
 // A call of many pairs may still have few long ones, which then take as long
 // as one of them: the kernels themselves choose between the two forms for the
 // queries above 512 rows that go to 64-lane groups, by their number in the
 // pass (kFewLong).
-static int class_bin(const sw_handle* h, int cls, int rows) {
+static int class_bin(const sw_handle* h, int cls, int rows, bool col) {
     const int base = h->route[0][rows / 16 - 1];
     int W = 0, step = 1;
-    if (rows > 512) W = cls <= 1 || (cls == 2 && rows > 1024) ? 256 : 64;
+    if (rows > 512) W = rows <= most_rows64(cls, col) ? 64 : 256;
     else if (rows > 128 && cls == 0) { W = 64; step = 2; }
     else if (rows > 128 && cls == 1) { W = 32; step = 2; }
     if (W == 0) return base;
@@ -400,6 +417,17 @@ static int class_bin(const sw_handle* h, int cls, int rows) {
 // of 1000, 5.7 against 5.1 and 5.6 against 6.4; 8000 of 700, 5.3 against 5.8 and
 // 6.1 against 7.1; 50,000 mixed pairs (about 5400 long) 9.9 against 10.7.
 constexpr int kFewLong = 2048;
+
+// The first bin whose pairs decide whether a pass has few: all above 512 rows
+// (in a batch of mixed lengths the cooperative groups of the longer ones keep
+// the device busy), but in calls of up to 8192 pairs, which cannot fill it with
+// both kinds, those of the 64-lane rows only (5000 DNA pairs of 765-850
+// residues, 180 of them up to 768: 2.9 ms by all, 2.0 by those).
+static int few_first(const sw_handle* h, int cls, int v) {
+    int b = 0;
+    while (cls <= 1 && b < h->n_long_bins && h->bins[b].W * h->bins[b].R > most_rows64(cls, v == 1)) ++b;
+    return b;
+}
 
 // Rows per lane of the cooperative shape that sweeps long bin e.
 static int coop_rows(const BinInfo& e) { return (e.R + 3) / 4; }
@@ -428,14 +456,16 @@ static void rebuild_lut(sw_handle* h) {
     for (int c = 0; c < kRouteClasses; ++c) {
         h->bin_used[c].assign(h->bins.size(), 0);
         h->bin_min_query[c].assign(h->bins.size(), SW_MAX_QUERY + 1);
-        for (int sel = 0; sel < 2; ++sel) {
+        for (int sel = 0; sel < kLutSels; ++sel) {
             h->class_route[c][sel].assign(kLutRows, -1);
             for (int k = 0; k < kLutRows; ++k) {
-                const int b = sel == 0 && h->builtin16 ? class_bin(h, c, 16 * (k + 1)) : h->route[sel][k];
+                const int b = sel == kLutI32   ? h->route[1][k]
+                              : h->builtin16 ? class_bin(h, c, 16 * (k + 1), sel == kLutI16Col)
+                                             : h->route[0][k];
                 h->class_route[c][sel][k] = b;
                 h->lut[c * kLutEntries + sel * kLutRows + k] = (int8_t)b;
                 if (b >= 0) {
-                    h->bin_used[c][b] = 1;
+                    h->bin_used[c][b] |= (char)(1 << sel);
                     h->bin_min_query[c][b] = std::min(h->bin_min_query[c][b], 16 * k + 1);
                 }
             }
@@ -601,7 +631,10 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         h->bin_fam_slot[i] = -1;
     }
     int n_launch = 0;   // launches of this pass
-    for (int v = 0; v < 2; ++v) h->few_launch[pass][v] = h->few_slot[pass][v] = -1;
+    for (int v = 0; v < 2; ++v) {
+        h->few_launch[pass][v] = h->few_slot[pass][v] = -1;
+        h->few_from[v] = few_first(h, cls, v);
+    }
     K.few_long = kFewLong;
     K.few_idx = (int16_t)(kMetaBinFirst + h->n_long_bins);
     if (timing && h->opt_mode == 1) HIP_TRY(h, hipEventRecord(h->ev[pass == 0 ? 1 : 3], stream));
@@ -632,12 +665,19 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         int only16 = -1, only32 = -1;
         const bool one_length = pass == 0 && search_n >= 1 && search_n <= SW_MAX_QUERY;
         if (one_length) {
-            only16 = h->class_route[cls][0][(search_n - 1) / 16];
-            only32 = h->class_route[cls][1][(search_n - 1) / 16];
+            only16 = h->class_route[cls][C.col_ok[0] ? kLutI16Col : kLutI16][(search_n - 1) / 16];   // (one scheme)
+            only32 = h->class_route[cls][kLutI32][(search_n - 1) / 16];
         }
+        // the routes that the call's pairs can take
+        const int routes = (any_col ? 1 << kLutI16Col : 0) | (all_col ? 0 : 1 << kLutI16) | 1 << kLutI32;
+        // may bin b hold items of score range v (1 column words, 0 the others)?
+        auto in_range = [&](int b, int v) {
+            const int r = h->bin_used[cls][b] & routes;
+            return v == 1 ? h->bins[b].col && (r >> kLutI16Col & 1) : (r & ~(h->bins[b].col ? 1 << kLutI16Col : 0)) != 0;
+        };
         std::vector<char> launchable(n_bins, 0);
         for (int b = 0; b < n_bins; ++b)
-            launchable[b] = h->bin_used[cls][b] && !(one_length && b != only16 && b != only32) &&
+            launchable[b] = (h->bin_used[cls][b] & routes) && !(one_length && b != only16 && b != only32) &&
                             !(C.i16_limit < 0 && h->bins[b].prec == 16) &&   // (max_score is at least 1)
                             !(h->opt_max_query > 0 && h->bin_min_query[cls][b] > h->opt_max_query);
         // score ranges (1 column words, 0 the others) whose launchable long
@@ -647,14 +687,14 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         for (int b = 0; b < n_bins; ++b) {
             const BinInfo& e = h->bins[b];
             if (!launchable[b] || !long_bin(e) || !h->builtin16 || !h->coop) continue;
-            few[1] |= any_col && e.col;
-            few[0] |= !(e.col && all_col) && table_var(h, e, K, 0) != kVarQprof;
+            few[1] |= in_range(b, 1);
+            few[0] |= in_range(b, 0) && table_var(h, e, K, 0) != kVarQprof;
         }
         // Family launches (default tile): one kernel per family, score
         // source and pass takes the items of all its launchable member bins;
         // the bins it covers get no launch of their own below.
         std::vector<char> covered(2 * n_bins, 0);
-        int fam_slot = 0;
+        int fam_slot = 0, few_fork[2] = {-1, -1};
         const bool families = h->opt_families && h->opt_chunk == kChunk;
         if (families) {
             std::vector<const FamilyEntry*> seen;
@@ -676,7 +716,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                         const int mb = find_bin(h, f->prec, f->lanes_of(k), f->rows[k]);
                         if (mb < 0 || !(launchable[mb] || take_long)) continue;
                         const BinInfo& m = h->bins[mb];
-                        if (v == 1 ? !(any_col && m.col) : (m.col && all_col)) continue;
+                        if (!take_long && !in_range(mb, v)) continue;
                         const int mv = table_var(h, m, K, v);
                         if (mv == kVarQprof || (var >= 0 && mv != var)) continue;
                         var = mv;
@@ -687,6 +727,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                     // shape's own kernel (measured: small batches on three
                     // bins of different widths ran 15% slower)
                     if (members < 2 || !f->k[var][pass] || fam_slot >= sw_handle::kFamLaunches) continue;
+                    K.few_sub = (int16_t)(kMetaBinFirst + h->few_from[v]);
                     if (take_long) {
                         memcpy(K.fam_more, h->coop_more, sizeof(K.fam_more));
                         K.few_run = 1;
@@ -699,7 +740,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                     }
                     for (int k = 0; k < f->n; ++k) {
                         const int mb = K.fam_bins[k];
-                        if (mb < 0 || !launchable[mb]) continue;
+                        if (mb < 0 || !launchable[mb] || !in_range(mb, v)) continue;
                         covered[2 * mb + v] = 1;
                         const int i2 = bin_ev_index(pass, mb, v, 0) / 2;
                         h->bin_launch[i2] = n_launch;
@@ -714,13 +755,19 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                     const int ppw = pairs_per_item(f->prec, f->lanes_of(0)), ipb = items_per_block(f->lanes_of(0));
                     const int64_t need = (cap / ppw + 1 + ipb - 1) / ipb;
                     const int blocks = (int)std::min<int64_t>(need, std::max(1, family_resident(h, fn)));
-                    hipStream_t ls = forks > 1 ? h->fork[launched % forks] : stream;
+                    // calls of up to 8192 pairs: the two kinds of launch over the
+                    // long bins share a stream, as one of them has nothing to
+                    // do, and leave the others to the shorter bins
+                    const bool shared = cls <= 1 && K.few_run < 0 && few_fork[v] >= 0;
+                    const int fork = shared ? few_fork[v] : launched;
+                    if (take_long) few_fork[v] = fork;
+                    hipStream_t ls = forks > 1 ? h->fork[fork % forks] : stream;
                     hipEvent_t* fe = per_bin ? &h->fam_ev[(pass * sw_handle::kFamLaunches + fam_slot) * 2] : nullptr;
                     if (fe) HIP_TRY(h, hipEventRecord(fe[0], ls));
                     hipLaunchKernelGGL(fn, dim3(blocks), dim3(kBlock), 0, ls, K);
                     HIP_TRY(h, hipGetLastError());
                     if (fe) HIP_TRY(h, hipEventRecord(fe[1], ls));
-                    ++launched;
+                    if (!shared) ++launched;
                     ++n_launch;
                     ++fam_slot;
                 }
@@ -733,7 +780,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
             const int ipb = items_per_block(e.W);
             const int64_t need = (cap / e.ppw + 1 + ipb - 1) / ipb;
             for (int v = e.col ? 1 : 0; v >= 0; --v) {   // column-word kernel first
-                if (v == 1 ? !any_col : (e.col && all_col)) continue;
+                if (!in_range(b, v)) continue;
                 if (covered[2 * b + v]) continue;
                 const int var = table_var(h, e, K, v);
                 const int nw = narrow_tile(h, e, var);
@@ -744,6 +791,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 0)], ls));
                 const int cb = find_bin(h, 16, 256, coop_rows(e));
                 K.few_run = 0;
+                K.few_sub = (int16_t)(kMetaBinFirst + h->few_from[v]);
                 if (few[v] && long_bin(e) && var != kVarQprof && cb >= 0) {
                     if (!families) {   // (a family launch takes them otherwise)
                         K.few_run = 1;
@@ -778,7 +826,7 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                 const int var = table_var(h, e, K, v);
                 const int nw = narrow_tile(h, e, var);
                 const bool coop = long_bin(e) && h->builtin16 && h->coop && var != kVarQprof &&
-                                  h->h_meta[K.few_idx] <= kFewLong;
+                                  h->h_meta[K.few_idx] - h->h_meta[kMetaBinFirst + h->few_from[v]] <= kFewLong;
                 const int W = coop ? 256 : e.W, R = coop ? coop_rows(e) : e.R;
                 const int blocks = (items + items_per_block(W) - 1) / items_per_block(W);
                 h->bin_launch[bin_ev_index(pass, b, v, 0) / 2] = n_launch++;
@@ -1127,7 +1175,7 @@ static int complete_slot(sw_handle* h, int k) {
     auto few_swept = [&](int pass, int b, int v) -> bool {
         if (h->few_launch[pass][v] < 0 || !long_bin(h->bins[b])) return false;
         uint64_t n = 0;
-        for (int q = 0; q < h->n_long_bins; ++q) n += cnt[kCtrBinPairs + pass * kMaxBins + q];
+        for (int q = h->few_from[v]; q < h->n_long_bins; ++q) n += cnt[kCtrBinPairs + pass * kMaxBins + q];
         return n <= (uint64_t)kFewLong;
     };
     h->last_ptab = sl.ptab ? 1 : 0;
