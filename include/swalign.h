@@ -130,10 +130,11 @@ const char* sw_last_error(sw_handle* h);
  *   "colpath"   1 = pairs whose scheme has at most 4 residues (and whose
  *               scores plus gap_open and gap_extend fit a byte) read their
  *               substitution scores from per-column words instead of table
- *               lookups (default 1; 0 = always table lookups).  Schemes of
- *               one call share the gap_extend of the first such scheme;
- *               others, and gap costs too large for the drifted sweeps
- *               (gap_open + 42 gap_extend > 1024), take table lookups
+ *               lookups (default 1; 0 = always table lookups).  Gap costs too
+ *               large for the drifted sweeps (gap_open + 42 gap_extend >
+ *               1024) take table lookups, and a scheme that is the only one
+ *               of a call not to share the first such scheme's gap_extend
+ *               takes the pair table
  *   "pairtable" 1 = when exactly one scheme of a call takes table lookups
  *               (alphabet of at most 24 residues, scores plus gap_open
  *               and gap_extend a byte, gap_open + 42 gap_extend <= 1024),

@@ -23,6 +23,9 @@ FLAGS = [
     "-std=c++17",
     "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # a family kernel reads its arguments in more than 300 places, above which
+    # the compiler copies them all to scratch memory (300 to 400 bytes a lane)
+    "-mllvm", "-instcombine-max-copied-from-constant-users=100000",
     "-I" + os.path.join(ROOT, "include"),
     "-I" + CSRC,
 ]

@@ -368,7 +368,7 @@ __device__ __forceinline__ void coop_member(const KParams& P, Work& K, int own, 
             if (tid == 0) atomicOr(&P.flags[kFlagInternal], 1);
             continue;
         }
-        coop_loop(P, K.item(), wave, lo, hi, (VAR == kVarCol ? kMetaColHeads : kMetaHeads) + bin, n_pairs,
+        coop_loop(P, K.item(), wave, lo, hi, head_of<VAR>(P, bin), n_pairs,
                   [&](int first, int count) { K.template sweep<R, REV>(P, first, count, tid, wave); });
     }
 }

@@ -124,6 +124,31 @@ __device__ __forceinline__ PairJob load_job(const KParams& P, int pair, int reve
     return J;
 }
 
+// Drift group of column-word scheme sid.
+__device__ __forceinline__ int drift_group(const KParams& P, int sid) { return (P.drift_of >> (8 * sid)) & 0xFF; }
+
+// Leaves a pair of another drift group out of a sweep.  (Without a branch for the
+// usual call of one group: it kept the loads of an item's pairs and of its
+// residues apart, and 200,000 short DNA pairs were 1.3% slower.)
+__device__ __forceinline__ void keep_group(const KParams& P, PairJob& J, int& pair) {
+    const bool in = pair >= 0 && drift_group(P, J.sid) == P.group;
+    J.n = in ? J.n : 0;
+    J.m = in ? J.m : 0;
+    J.fwd_score = in ? J.fwd_score : 0;
+    pair = in ? pair : -1;
+}
+
+// Planning key of a pair of `bin` against m reference residues: the pairs of
+// column-path schemes first, each part by decreasing length.  Drift groups follow
+// one another in the first part, with coarser length buckets, so that few
+// work items hold pairs of more than one.
+__device__ __forceinline__ int pair_key(const KParams& P, int bin, bool col, int sid, int m) {
+    const int b = kMHalf - 1 - m_bucket(m);
+    if (!col) return bin * kMBuckets + kMHalf + b;
+    const int shift = P.n_drift <= 1 ? 0 : P.n_drift == 2 ? 1 : 2;
+    return bin * kMBuckets + drift_group(P, sid) * (kMHalf >> shift) + (b >> shift);
+}
+
 // Sets an error flag from any lanes (a plain store: every writer stores 1).
 // No lane-divergent branch: see opaque_lane.
 __device__ __forceinline__ void set_flag(int32_t* flags, int which, bool raise) {

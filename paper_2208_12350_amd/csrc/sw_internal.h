@@ -111,8 +111,8 @@ enum : int {
     kMetaItemFirst = kMetaBinFirst + kMaxBins + 1,    // [kMaxBins + 1] first item of each bin
     kMetaItemSplit = kMetaItemFirst + kMaxBins + 1,   // [kMaxBins] first table-lookup item of each bin
     kMetaHeads = kMetaItemSplit + kMaxBins,           // [kMaxBins] queue head of each bin's table-lookup items
-    kMetaColHeads = kMetaHeads + kMaxBins,            // [kMaxBins] and of its column-word items
-    kMetaBinCol = kMetaColHeads + kMaxBins,           // [kMaxBins] column-path pairs of each bin
+    kMetaColHeads = kMetaHeads + kMaxBins,            // [SW_MAX_SCHEMES][kMaxBins] and of its column-word items, per drift group
+    kMetaBinCol = kMetaColHeads + SW_MAX_SCHEMES * kMaxBins,   // [kMaxBins] column-path pairs of each bin
     kMetaRedo = kMetaBinCol + kMaxBins,               // pairs on the redo list (reverse pass)
     kMetaSize = kMetaRedo + 1,
 };
@@ -131,6 +131,15 @@ enum : int {
     kCtrTraceBinPairs = kCtrTraceBinCells + kMaxBins,      // [kMaxBins] pairs per path-sweep bin
     kCtrRedoPairs = kCtrTraceBinPairs + kMaxBins,          // pairs on the redo list
     kNumCounters = kCtrRedoPairs + 2,   // (even, for whole 16-byte units in the copy to the host)
+};
+
+// Drifted sweeps (sw_sweep.h): the column-word schemes of a call that share a
+// gap extension cost, and so a drift.  A launch sweeps the pairs of one group.
+struct DriftGroup {
+    int32_t sid;      // one of its schemes (for empty lane groups)
+    int32_t e;        // the gap extension cost
+    int32_t period;   // steps between renormalisations
+    int32_t x;        // the largest o - e
 };
 
 // Arguments shared by every sweep launch.
@@ -173,13 +182,9 @@ struct KParams {
     int16_t few_long, few_idx, few_sub, few_run;
     int8_t fam_bins[kFamilyMax];   // family launch: member k's bin, or -1 (not launched)
     int8_t fam_more[kFamilyMax];
-    // Drifted sweeps (sw_sweep.h), [0] column words, [1] pair table and query
-    // profile: the gap extension cost of their schemes, the steps between
-    // renormalisations, one of their schemes (for empty lane groups).
-    int32_t drift_e[2];
-    int32_t drift_period[2];
-    int32_t drift_sid[2];
-    int32_t drift_x[2];          // the largest o - e of their schemes
+    DriftGroup drift[2];         // of [0] this launch's column words, [1] the pair table and the query profile
+    int16_t n_drift, group;      // groups of the call's column-word schemes, and this launch's
+    uint32_t drift_of;           // group of each column-word scheme, 8 bits a scheme
     int32_t* redo;               // redo list of the reverse pass (meta[kMetaRedo] pairs; room for n_pairs)
 };
 

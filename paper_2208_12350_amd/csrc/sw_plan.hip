@@ -116,7 +116,7 @@ __global__ __launch_bounds__(THREADS) void sw_classify_kernel(KParams P, Classif
                 // column-word kernel takes them), each part by decreasing
                 // reference length; only packed-int16 pairs use column words
                 const int col = (sel == 0 && C.col_ok[s] && bins[bin].col) ? 1 : 0;
-                key[u] = bin * kMBuckets + (col ? 0 : kMHalf) + (kMHalf - 1 - m_bucket((int)m));
+                key[u] = pair_key(P, bin, col != 0, s, (int)m);
                 atomicAdd(&s_bin_cells[col][bin], (unsigned long long)(n * m));
                 atomicAdd(&s_bin_pairs[col][bin], 1u);
             }
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kBinScanThreads) void sw_plan_bins_kernel(const Bin
         meta[kMetaItemSplit + t] = ifirst + col_items;
         meta[kMetaBinCol + t] = col;
         meta[kMetaHeads + t] = 0;
-        meta[kMetaColHeads + t] = 0;
+        for (int g = 0; g < SW_MAX_SCHEMES; ++g) meta[kMetaColHeads + g * kMaxBins + t] = 0;
     }
     if (t == 0) {
         meta[kMetaBinFirst + kMaxBins] = total;

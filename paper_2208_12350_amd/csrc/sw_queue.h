@@ -55,6 +55,13 @@ __device__ __forceinline__ bool left_to_others(const KParams& P) {
     return P.few_run != 0 && few_long_pairs(P) != (P.few_run > 0);
 }
 
+// Index of the queue head of bin b's column-word items (VAR kVarCol; the launch's
+// drift group has its own) or other items.
+template <int VAR>
+__device__ __forceinline__ int head_of(const KParams& P, int bin) {
+    return VAR == kVarCol ? kMetaColHeads + P.group * kMaxBins + bin : kMetaHeads + bin;
+}
+
 // The item range of the launch, read first: a launch for an empty bin (the
 // host does not know which bins are empty) costs its workgroups two loads
 // and an exit.  Returns false when there is nothing to do.
@@ -239,14 +246,18 @@ __device__ __forceinline__ void family_member(const KParams& P, Lds& L, uint16_t
             sweep_i16<W, R, REV, C>(P, L, wbuf, first, count, lane);
         else
             sweep_i32<W, R, REV, C>(P, L, wbuf, first, count, lane);
-    }, (VAR == kVarCol ? kMetaColHeads : kMetaHeads) + bin);
+    }, head_of<VAR>(P, bin));
 }
 
 template <int... Rs>
 constexpr int family_size() { return (int)sizeof...(Rs); }
 
+// (16-lane column words: at most 3 wavefronts per SIMD.  With the registers that
+// let a fourth in, the reverse sweeps of 1..8 rows of 200,000 DNA pairs took 249 us
+// in place of 209.)
 template <int PREC, int W, bool REV, int VAR, int WPE, int C, int... Rs>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) void sw_family_kernel(KParams P) {
+__global__ __launch_bounds__(kBlock) __attribute__((
+    amdgpu_waves_per_eu(WPE, W == 16 && VAR == kVarCol ? 3 : 8))) void sw_family_kernel(KParams P) {
     static_assert(sizeof...(Rs) <= kFamilyMax, "family too large");
     using Lds = typename std::conditional<VAR == kVarPtab, PtabLds, SchemeLds>::type;
     __shared__ __attribute__((aligned(16))) Lds L;

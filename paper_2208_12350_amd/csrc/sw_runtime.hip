@@ -240,7 +240,9 @@ struct sw_handle {
     static constexpr int kTraceFams = 8; // box-sweep family launches per chunk at most
     hipEvent_t tfam_ev[kTraceFams] = {}; // end of a box-sweep family launch, for its walks on other streams
     int32_t last_col_ok[SW_MAX_SCHEMES] = {0};   // column-word eligibility of the last score call's schemes
-    int32_t last_drift_e[2] = {0, 0}, last_drift_period[2] = {kChunk, kChunk}, last_drift_sid[2] = {0, 0};
+    DriftGroup drift[SW_MAX_SCHEMES] = {};       // and the drift groups they formed
+    int n_drift = 0;
+    uint32_t drift_of = 0;                       // (KParams::drift_of)
     BinInfo* d_tbins = nullptr;
     int8_t* d_tlut = nullptr;            // [2 * kLutRows] path-sweep bin per (precision, 16-row bucket of box rows)
     int64_t* d_rec_off = nullptr;        // [trace_cap + 1]
@@ -575,7 +577,21 @@ static int ensure_pairs(sw_handle* h, int64_t n) {
 static void set_range(KParams& K, int b, int v) {
     K.lo_idx = v ? kMetaItemFirst + b : kMetaItemSplit + b;
     K.hi_idx = v ? kMetaItemSplit + b : kMetaItemFirst + b + 1;
-    K.head_idx = v ? kMetaColHeads + b : kMetaHeads + b;
+    K.head_idx = v ? kMetaColHeads + K.group * kMaxBins + b : kMetaHeads + b;
+}
+
+// Drift group g of the call's column-word schemes for a launch of its sweeps ...
+static void set_group(KParams& K, const sw_handle* h, int g) {
+    K.group = (int16_t)g;
+    K.drift[0] = h->drift[g];
+}
+// ... of which there are this many over column words (v = 1) or other items.
+static int n_groups(const sw_handle* h, int v) { return v == 1 ? std::max(1, h->n_drift) : 1; }
+// What every launch of the call reads of them.
+static void set_groups(KParams& K, const sw_handle* h) {
+    K.n_drift = (int16_t)h->n_drift;
+    K.drift_of = h->drift_of;
+    if (h->n_drift > 0) set_group(K, h, 0);
 }
 
 // Workgroups the device holds at once of family kernel fn (0 if unknown).
@@ -694,9 +710,86 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         // source and pass takes the items of all its launchable member bins;
         // the bins it covers get no launch of their own below.
         std::vector<char> covered(2 * n_bins, 0);
-        int fam_slot = 0, few_fork[2] = {-1, -1};
+        int fam_slot = 0;
+        auto is_long = [&](const FamilyEntry* f) { return f->prec == 16 && f->W == 64 && f->rows[f->n - 1] > 8; };
         const bool families = h->opt_families && h->opt_chunk == kChunk;
+        // Launches family f for score range v on stream `at` (-1: the next one);
+        // `at` becomes the stream, or stays -1 when there is nothing to launch.
+        auto launch_family = [&](const FamilyEntry* f, int v, int& at) -> int {
+            int var = -1, members = 0;
+            const bool take_long = f == h->coop && few[v];
+            for (int k = 0; k < kFamilyMax; ++k) K.fam_bins[k] = -1;
+            for (int k = 0; k < f->n; ++k) {
+                const int mb = find_bin(h, f->prec, f->lanes_of(k), f->rows[k]);
+                if (mb < 0 || !(launchable[mb] || take_long)) continue;
+                const BinInfo& m = h->bins[mb];
+                if (!take_long && !in_range(mb, v)) continue;
+                const int mv = table_var(h, m, K, v);
+                if (mv == kVarQprof || (var >= 0 && mv != var)) continue;
+                var = mv;
+                K.fam_bins[k] = (int8_t)mb;
+                ++members;
+            }
+            // a family of one routed bin gains nothing over that
+            // shape's own kernel (measured: small batches on three
+            // bins of different widths ran 15% slower)
+            if (members < 2 || !f->k[var][pass] || fam_slot >= sw_handle::kFamLaunches) {
+                at = -1;
+                return SW_OK;
+            }
+            K.few_sub = (int16_t)(kMetaBinFirst + h->few_from[v]);
+            K.few_run = 0;
+            if (take_long) {
+                memcpy(K.fam_more, h->coop_more, sizeof(K.fam_more));
+                K.few_run = 1;
+                h->few_launch[pass][v] = n_launch;
+                h->few_slot[pass][v] = fam_slot;
+            } else if (few[v] && is_long(f)) {
+                K.few_run = -1;
+            }
+            for (int k = 0; k < f->n; ++k) {
+                const int mb = K.fam_bins[k];
+                if (mb < 0 || !launchable[mb] || !in_range(mb, v)) continue;
+                covered[2 * mb + v] = 1;
+                const int i2 = bin_ev_index(pass, mb, v, 0) / 2;
+                h->bin_launch[i2] = n_launch;
+                h->bin_fam_hi[i2] = f->rows[0];
+                h->bin_fam_lo[i2] = f->rows[f->n - 1];
+                h->bin_fam_slot[i2] = fam_slot;
+                h->bin_fam_waves[i2] = f->waves[var];
+                h->bin_fam_tile[i2] = f->tile[var];
+            }
+            const QueueFn fn = f->k[var][pass];
+            // (lanes_of(0): the widest, so the fewest pairs an item)
+            const int ppw = pairs_per_item(f->prec, f->lanes_of(0)), ipb = items_per_block(f->lanes_of(0));
+            const int64_t need = (cap / ppw + 1 + ipb - 1) / ipb;
+            const int blocks = (int)std::min<int64_t>(need, std::max(1, family_resident(h, fn)));
+            if (at < 0) at = launched++;
+            hipStream_t ls = forks > 1 ? h->fork[at % forks] : stream;
+            hipEvent_t* fe = per_bin ? &h->fam_ev[(pass * sw_handle::kFamLaunches + fam_slot) * 2] : nullptr;
+            if (fe) HIP_TRY(h, hipEventRecord(fe[0], ls));
+            for (int g = 0; g < n_groups(h, v); ++g) {
+                set_group(K, h, g);
+                hipLaunchKernelGGL(fn, dim3(blocks), dim3(kBlock), 0, ls, K);
+                HIP_TRY(h, hipGetLastError());
+            }
+            if (fe) HIP_TRY(h, hipEventRecord(fe[1], ls));
+            ++n_launch;
+            ++fam_slot;
+            return SW_OK;
+        };
         if (families) {
+            // Where only the long bins give them work (more than 262144 pairs),
+            // the cooperative groups follow the first 64-lane launch on its
+            // stream: before it, or on streams of their own, launches that find
+            // nothing to do wait for room on a full device and hold up what
+            // follows them (1,000,000 mixed pairs 2% slower).  In calls of up to
+            // 8192 pairs, where they have the longest queries besides, they come
+            // first and the 64-lane launch follows them, so that the other
+            // streams are free for the shorter bins.
+            const bool last = cls == kRouteClasses - 1;
+            int coop_fork[2] = {-1, -1};
+            bool pending[2] = {false, false};
             std::vector<const FamilyEntry*> seen;
             for (int b1 = 0; b1 < n_bins; ++b1) {
                 // the launch with most of the pairs first: the narrow shapes
@@ -709,68 +802,24 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                 if (!f || std::find(seen.begin(), seen.end(), f) != seen.end()) continue;
                 seen.push_back(f);
                 for (int v = 1; v >= 0; --v) {
-                    int var = -1, members = 0;
-                    const bool take_long = f == h->coop && few[v];
-                    for (int k = 0; k < kFamilyMax; ++k) K.fam_bins[k] = -1;
-                    for (int k = 0; k < f->n; ++k) {
-                        const int mb = find_bin(h, f->prec, f->lanes_of(k), f->rows[k]);
-                        if (mb < 0 || !(launchable[mb] || take_long)) continue;
-                        const BinInfo& m = h->bins[mb];
-                        if (!take_long && !in_range(mb, v)) continue;
-                        const int mv = table_var(h, m, K, v);
-                        if (mv == kVarQprof || (var >= 0 && mv != var)) continue;
-                        var = mv;
-                        K.fam_bins[k] = (int8_t)mb;
-                        ++members;
+                    const bool coop = f == h->coop && few[v], follows = few[v] && is_long(f);
+                    if (coop && last) {
+                        pending[v] = true;
+                        continue;
                     }
-                    // a family of one routed bin gains nothing over that
-                    // shape's own kernel (measured: small batches on three
-                    // bins of different widths ran 15% slower)
-                    if (members < 2 || !f->k[var][pass] || fam_slot >= sw_handle::kFamLaunches) continue;
-                    K.few_sub = (int16_t)(kMetaBinFirst + h->few_from[v]);
-                    if (take_long) {
-                        memcpy(K.fam_more, h->coop_more, sizeof(K.fam_more));
-                        K.few_run = 1;
-                        h->few_launch[pass][v] = n_launch;
-                        h->few_slot[pass][v] = fam_slot;
-                    } else if (few[v] && f->prec == 16 && long_bin(h->bins[find_bin(h, 16, f->W, f->rows[0])])) {
-                        K.few_run = -1;
-                    } else {
-                        K.few_run = 0;
+                    int at = cls <= 1 && follows ? coop_fork[v] : -1, rc = launch_family(f, v, at);
+                    if (coop) coop_fork[v] = at;
+                    if (follows && pending[v] && at >= 0 && rc == SW_OK) {
+                        pending[v] = false;
+                        rc = launch_family(h->coop, v, at);
                     }
-                    for (int k = 0; k < f->n; ++k) {
-                        const int mb = K.fam_bins[k];
-                        if (mb < 0 || !launchable[mb] || !in_range(mb, v)) continue;
-                        covered[2 * mb + v] = 1;
-                        const int i2 = bin_ev_index(pass, mb, v, 0) / 2;
-                        h->bin_launch[i2] = n_launch;
-                        h->bin_fam_hi[i2] = f->rows[0];
-                        h->bin_fam_lo[i2] = f->rows[f->n - 1];
-                        h->bin_fam_slot[i2] = fam_slot;
-                        h->bin_fam_waves[i2] = f->waves[var];
-                        h->bin_fam_tile[i2] = f->tile[var];
-                    }
-                    const QueueFn fn = f->k[var][pass];
-                    // (lanes_of(0): the widest, so the fewest pairs an item)
-                    const int ppw = pairs_per_item(f->prec, f->lanes_of(0)), ipb = items_per_block(f->lanes_of(0));
-                    const int64_t need = (cap / ppw + 1 + ipb - 1) / ipb;
-                    const int blocks = (int)std::min<int64_t>(need, std::max(1, family_resident(h, fn)));
-                    // calls of up to 8192 pairs: the two kinds of launch over the
-                    // long bins share a stream, as one of them has nothing to
-                    // do, and leave the others to the shorter bins
-                    const bool shared = cls <= 1 && K.few_run < 0 && few_fork[v] >= 0;
-                    const int fork = shared ? few_fork[v] : launched;
-                    if (take_long) few_fork[v] = fork;
-                    hipStream_t ls = forks > 1 ? h->fork[fork % forks] : stream;
-                    hipEvent_t* fe = per_bin ? &h->fam_ev[(pass * sw_handle::kFamLaunches + fam_slot) * 2] : nullptr;
-                    if (fe) HIP_TRY(h, hipEventRecord(fe[0], ls));
-                    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kBlock), 0, ls, K);
-                    HIP_TRY(h, hipGetLastError());
-                    if (fe) HIP_TRY(h, hipEventRecord(fe[1], ls));
-                    if (!shared) ++launched;
-                    ++n_launch;
-                    ++fam_slot;
+                    if (rc != SW_OK) return rc;
                 }
+            }
+            for (int v = 1; v >= 0; --v) {
+                int at = -1;
+                const int rc = pending[v] ? launch_family(h->coop, v, at) : SW_OK;
+                if (rc != SW_OK) return rc;
             }
         }
         for (int b = 0; b < n_bins; ++b) {
@@ -796,15 +845,23 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                     if (!families) {   // (a family launch takes them otherwise)
                         K.few_run = 1;
                         const int64_t most = std::min<int64_t>(cap / e.ppw + 1, h->resident_blocks[0][pass][var][cb]);
-                        hipLaunchKernelGGL(shape_kernel(16, 256, coop_rows(e), pass != 0, var), dim3((int)most),
-                                           dim3(kBlock), 0, ls, K);
-                        HIP_TRY(h, hipGetLastError());
+                        for (int g = 0; g < n_groups(h, v); ++g) {
+                            set_group(K, h, g);
+                            set_range(K, b, v);
+                            hipLaunchKernelGGL(shape_kernel(16, 256, coop_rows(e), pass != 0, var), dim3((int)most),
+                                               dim3(kBlock), 0, ls, K);
+                            HIP_TRY(h, hipGetLastError());
+                        }
                     }
                     K.few_run = -1;
                 }
-                hipLaunchKernelGGL(shape_kernel(e.prec, e.W, e.R, pass != 0, var, nw == 1), dim3(blocks), dim3(kBlock),
-                                   0, ls, K);
-                HIP_TRY(h, hipGetLastError());
+                for (int g = 0; g < n_groups(h, v); ++g) {
+                    set_group(K, h, g);
+                    set_range(K, b, v);
+                    hipLaunchKernelGGL(shape_kernel(e.prec, e.W, e.R, pass != 0, var, nw == 1), dim3(blocks),
+                                       dim3(kBlock), 0, ls, K);
+                    HIP_TRY(h, hipGetLastError());
+                }
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 1)], ls));
                 if (per_bin) h->bin_launched[bin_ev_index(pass, b, v, 0) / 2] = 1;
             }
@@ -831,9 +888,13 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
                 const int blocks = (items + items_per_block(W) - 1) / items_per_block(W);
                 h->bin_launch[bin_ev_index(pass, b, v, 0) / 2] = n_launch++;
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 0)], stream));
-                hipLaunchKernelGGL(shape_kernel(e.prec, W, R, pass != 0, var, nw == 1), dim3(blocks), dim3(kBlock),
-                                   0, stream, K);
-                HIP_TRY(h, hipGetLastError());
+                for (int g = 0; g < n_groups(h, v); ++g) {
+                    set_group(K, h, g);
+                    set_range(K, b, v);
+                    hipLaunchKernelGGL(shape_kernel(e.prec, W, R, pass != 0, var, nw == 1), dim3(blocks), dim3(kBlock),
+                                       0, stream, K);
+                    HIP_TRY(h, hipGetLastError());
+                }
                 if (per_bin) HIP_TRY(h, hipEventRecord(h->bin_ev[bin_ev_index(pass, b, v, 1)], stream));
                 if (per_bin) h->bin_launched[bin_ev_index(pass, b, v, 0) / 2] = 1;
             }
@@ -1359,7 +1420,6 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
 
     // substitution tables: [s][b][a] = M_s[a][b]; padding rows/columns score -1
     ClassifyArgs C;
-    int col_sid = -1, col_period = 0, col_x = 0;   // first column-word scheme; renormalisation period of them all
     h->tables.assign(kSchemeBytes, 0);
     for (int s = 0; s < SW_MAX_SCHEMES; ++s) {
         int8_t* T = h->tables.data() + s * kMatBytes;
@@ -1375,15 +1435,13 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
             }
         C.max_score[s] = mx;
         // small-alphabet column path: alphabet <= 4, gap costs that the
-        // drifted sweeps take and every M[a][b] + o + e a byte; one gap
-        // extension cost per launch, so schemes with another one than the
-        // first such scheme's take table lookups; column word of residue b =
-        // bytes M[a][b] + o + e, a = 0..3 (0 for residues outside the alphabet)
+        // drifted sweeps take and every M[a][b] + o + e a byte; column word of
+        // residue b = bytes M[a][b] + o + e, a = 0..3 (0 for residues outside
+        // the alphabet)
         uint32_t* cw = reinterpret_cast<uint32_t*>(h->tables.data() + SW_MAX_SCHEMES * kMatBytes) + s * kMatDim;
         const int lift = s < n_schemes ? schemes[s].gap_open + schemes[s].gap_extend : 0;
         bool ok = s < n_schemes && schemes[s].alphabet <= 4 &&
-                  drift_period(schemes[s].gap_open, schemes[s].gap_extend) > 0 &&
-                  (col_sid < 0 || schemes[s].gap_extend == schemes[col_sid].gap_extend);
+                  drift_period(schemes[s].gap_open, schemes[s].gap_extend) > 0;
         for (int b = 0; b < kMatDim; ++b) {
             uint32_t w = 0;
             for (int a = 0; ok && a < 4; ++a) {
@@ -1394,13 +1452,23 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
             }
             cw[b] = w;
         }
-        C.col_ok[s] = ok ? 1 : 0;
-        if (ok) {
-            if (col_sid < 0) col_sid = s;
-            const int per = drift_period(schemes[s].gap_open, schemes[s].gap_extend);
-            col_period = col_period == 0 ? per : std::min(col_period, per);
-            col_x = std::max(col_x, schemes[s].gap_open - schemes[s].gap_extend);
+        C.col_ok[s] = ok && h->opt_colpath ? 1 : 0;
+    }
+    // The only scheme of a call that does not share the gap extension cost of
+    // the first column-word scheme takes the pair table, which serves it as
+    // well in a launch of its own.  More of them would leave the call without a
+    // pair table: then each such cost has a drift group, and launches, of its own
+    // (100,000 + 100,000 DNA pairs of two costs and 50,000 protein pairs took
+    // 8.4 ms with the second cost and the protein on byte tables, 6.6 with these).
+    {
+        int first = -1, other = -1, n_other = 0;
+        for (int s = 0; s < n_schemes; ++s) {
+            if (C.col_ok[s] && first < 0) first = s;
+            if (C.col_ok[s] && schemes[s].gap_extend == schemes[first].gap_extend) continue;
+            other = s;
+            ++n_other;
         }
+        if (n_other == 1 && C.col_ok[other] && h->opt_ptab) C.col_ok[other] = 0;
     }
     // the packed path holds every value of a pair when its score bound
     // min(n, m) * max_score is at most kI16Limit
@@ -1418,7 +1486,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     if (h->opt_ptab) {
         int n_table = 0, cand = -1;
         for (int sidx = 0; sidx < n_schemes; ++sidx)
-            if (!(C.col_ok[sidx] && h->opt_colpath)) { ++n_table; cand = sidx; }
+            if (!C.col_ok[sidx]) { ++n_table; cand = sidx; }
         if (n_table == 1) {
             const sw_scheme& sc = schemes[cand];
             bool ok = sc.alphabet + 1 <= kPtabMaxDim && drift_period(sc.gap_open, sc.gap_extend) > 0;
@@ -1460,19 +1528,24 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     K.ptab_sid = ptab_sid;
     K.ptab_dim = D;
     K.redo = reinterpret_cast<int32_t*>(ws.keys);   // the keys of the reverse pass are not read any more when its sweeps run
-    K.drift_sid[0] = std::max(0, col_sid);
-    K.drift_e[0] = col_sid >= 0 ? schemes[col_sid].gap_extend : 0;
-    K.drift_period[0] = col_sid >= 0 ? col_period : kChunk;
-    K.drift_x[0] = col_x;
-    K.drift_x[1] = ptab_sid >= 0 ? schemes[ptab_sid].gap_open - schemes[ptab_sid].gap_extend : 0;
-    K.drift_sid[1] = std::max(0, ptab_sid);
-    K.drift_e[1] = ptab_sid >= 0 ? schemes[ptab_sid].gap_extend : 0;
-    K.drift_period[1] = ptab_sid >= 0 ? drift_period(schemes[ptab_sid].gap_open, schemes[ptab_sid].gap_extend) : kChunk;
-    for (int k2 = 0; k2 < 2; ++k2) {
-        h->last_drift_e[k2] = K.drift_e[k2];
-        h->last_drift_period[k2] = K.drift_period[k2];
-        h->last_drift_sid[k2] = K.drift_sid[k2];
+    h->n_drift = 0;
+    h->drift_of = 0;
+    for (int s = 0; s < n_schemes; ++s) {
+        if (!C.col_ok[s] && s != ptab_sid) continue;
+        const sw_scheme& sc = schemes[s];
+        const DriftGroup own{s, sc.gap_extend, drift_period(sc.gap_open, sc.gap_extend), sc.gap_open - sc.gap_extend};
+        if (s == ptab_sid) {
+            K.drift[1] = own;
+            continue;
+        }
+        int g = 0;
+        while (g < h->n_drift && h->drift[g].e != own.e) ++g;
+        if (g == h->n_drift) h->drift[h->n_drift++] = own;
+        h->drift[g].period = std::min(h->drift[g].period, own.period);
+        h->drift[g].x = std::max(h->drift[g].x, own.x);
+        h->drift_of |= (uint32_t)g << (8 * s);
     }
+    set_groups(K, h);
     // query profile: a search (every pair aligns queries[0 .. qprof_n)) with
     // the pair table's scheme profiles its query for the forward pass
     K.qprof = (search_n >= 1 && search_n <= SW_MAX_QUERY && ptab_sid >= 0 && h->opt_qprof) ? 1 : 0;
@@ -1483,8 +1556,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
         K.gap_open[s] = v ? schemes[s].gap_open : 1;
         K.gap_extend[s] = v ? schemes[s].gap_extend : 0;
         K.max_score[s] = C.max_score[s];
-        K.col_ok[s] = C.col_ok[s] && h->opt_colpath;
-        C.col_ok[s] = K.col_ok[s];
+        K.col_ok[s] = C.col_ok[s];
         h->last_col_ok[s] = K.col_ok[s];
     }
 
@@ -1854,12 +1926,7 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
         any_col = any_col || h->last_col_ok[s] != 0;
     }
     for (int s = 0; s < SW_MAX_SCHEMES; ++s) K.col_ok[s] = s < n_schemes && h->last_col_ok[s] ? 1 : 0;
-    // the column words' drift, as the score passes set it
-    for (int k = 0; k < 2; ++k) {
-        K.drift_e[k] = h->last_drift_e[k];
-        K.drift_period[k] = h->last_drift_period[k];
-        K.drift_sid[k] = h->last_drift_sid[k];
-    }
+    set_groups(K, h);   // the column words' drift, as the score passes set it
     // does bin e have pairs for variant v (1 column words, 0 byte table)?
     auto wants = [&](const BinInfo& e, int v) { return v == 1 ? (e.col && any_col) : !(e.col && all_col); };
     // Bins no pair can reach are not launched (a launch with no items still
@@ -2005,8 +2072,11 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
             for (int v = 1; v >= 0; --v) {
                 if (!fns[v]) continue;
                 hipStream_t vs = n_swept == 0 || forks <= 1 ? ls : h->fork[next_fork()];
-                hipLaunchKernelGGL(fns[v], dim3((int)std::min<int64_t>(need, res[v])), dim3(kBlock), 0, vs, K, T);
-                HIP_TRY(h, hipGetLastError());
+                for (int g = 0; g < n_groups(h, v); ++g) {
+                    set_group(K, h, g);
+                    hipLaunchKernelGGL(fns[v], dim3((int)std::min<int64_t>(need, res[v])), dim3(kBlock), 0, vs, K, T);
+                    HIP_TRY(h, hipGetLastError());
+                }
                 swept[n_swept] = h->tfam_ev[n_fam++];
                 if (forks > 1) HIP_TRY(h, hipEventRecord(swept[n_swept], vs));
                 ++n_swept;
@@ -2042,10 +2112,13 @@ static int trace_paths(sw_handle* h, const sw_batch* batch, const sw_scheme* sch
             for (int v = 1; v >= 0; --v) {
                 if (!wants(e, v)) continue;
                 const int blocks = (int)std::min<int64_t>(need, (v ? h->tresident_col : h->tresident)[b]);
-                set_range(K, b, v);
-                hipLaunchKernelGGL(trace_kernel(e.prec, e.W, e.R, v == 1), dim3(blocks), dim3(kBlock), 0, ls, K,
-                                   T);
-                HIP_TRY(h, hipGetLastError());
+                for (int g = 0; g < n_groups(h, v); ++g) {
+                    set_group(K, h, g);
+                    set_range(K, b, v);
+                    hipLaunchKernelGGL(trace_kernel(e.prec, e.W, e.R, v == 1), dim3(blocks), dim3(kBlock), 0, ls, K,
+                                       T);
+                    HIP_TRY(h, hipGetLastError());
+                }
             }
             if (timing) {
                 HIP_TRY(h, hipEventRecord(h->tbin_ev[3 * b + 1], ls));

@@ -459,8 +459,8 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
 //
 // 1. Drift.  The value kept for a cell in row r of its lane at sweep step t is
 //    H + z(r, t) with z(r, t) = K0 + e (r + t), where e is the gap extension
-//    cost (one for all pairs of the launch) and t counts from the last
-//    renormalisation.  A gap extension moves one row down or one column (one
+//    cost (one for all pairs of the launch: column-word schemes of several costs
+//    have a launch each, DriftGroup) and t counts from the last renormalisation.  A gap extension moves one row down or one column (one
 //    step) on and costs e, so in these terms E and F carry over unchanged:
 //        E(r, t+1) = max(E(r, t), Hm(r, t), z(r, t+1))    Hm = H - (o - e)
 //        F(r+1, t) = max(F(r, t), Hm(r, t))
@@ -556,13 +556,13 @@ struct ColScores {
     using Stager = RefStager<W, C>;
     using Lds = SchemeLds;
     using Entry = uint32_t;
-    static constexpr int kSide = 0;   // KParams::drift_e / drift_period entry
+    static constexpr int kSide = 0;   // KParams::drift entry
     static constexpr int kSets = 1, kCoopSets = R > 4 ? 2 : 1;
     uint32_t sel[R];
     uint32_t ca[2], cb[2];
 
     __device__ __forceinline__ void check(const KParams& P, PairJob& J, int pair) const {
-        if (pair < 0) J.sid = P.drift_sid[kSide];
+        if (pair < 0) J.sid = P.drift[kSide].sid;
     }
     __device__ __forceinline__ void rows(const KParams& P, const Lds& S, const PairJob& JA, const PairJob& JB, int l,
                                          int& bad) {
@@ -826,10 +826,14 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
     const int lr = COOP ? 64 * wave + l : l;   // lane within the pair's group: rows lr * R ..
 
     const int slot = g * 2;
-    const int pairA = slot < count ? P.order[first + slot] : -1;
-    const int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
+    int pairA = slot < count ? P.order[first + slot] : -1;
+    int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
     PairJob JA = load_job(P, pairA, REV ? 1 : 0);
     PairJob JB = load_job(P, pairB, REV ? 1 : 0);
+    if constexpr (Src::kSide == 0) {
+        keep_group(P, JA, pairA);
+        keep_group(P, JB, pairB);
+    }
     Src src;
     src.check(P, JA, pairA);
     src.check(P, JB, pairB);
@@ -850,8 +854,8 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
     src.stage(stA, bufA, P, S, JA, 0, l, bad);
     src.stage(stB, bufB, P, S, JB, 0, l, bad);
 
-    const uint32_t e = (uint32_t)P.drift_e[Src::kSide];
-    const int period = P.drift_period[Src::kSide];       // even, at least 2
+    const uint32_t e = (uint32_t)P.drift[Src::kSide].e;
+    const int period = P.drift[Src::kSide].period;       // even, at least 2
     const uint32_t e2 = __builtin_amdgcn_readfirstlane(e * 0x10001u), e8 = 8u * e2;
     const uint32_t goA = (uint32_t)S.gap_open[JA.sid], goB = (uint32_t)S.gap_open[JB.sid];
     const uint32_t cAB = (goA - e) | ((goB - e) << 16);   // o - e of both pairs
@@ -879,7 +883,7 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
     constexpr int kCode = kQ <= 1 ? 0 : kQ <= 2 ? 1 : kQ <= 4 ? 2 : kQ <= 8 ? 3 : kQ <= 16 ? 4 : 5;
     u16x2 best[REV ? 1 : R];
     uint32_t kA[kSets], kB[kSets];
-    const int x = P.drift_x[Src::kSide];
+    const int x = P.drift[Src::kSide].x;
     int k = 0;
     if constexpr (!REV) {
         int a, b;

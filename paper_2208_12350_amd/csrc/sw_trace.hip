@@ -570,12 +570,14 @@ __device__ __forceinline__ void sweep_trace_i16_col(const KParams& P, const Trac
     const int l = lane % W;
 
     const int slot = g * 2;
-    const int pairA = slot < count ? P.order[first + slot] : -1;
-    const int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
+    int pairA = slot < count ? P.order[first + slot] : -1;
+    int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
     PairJob JA = box_job(P, pairA, W * R);
     PairJob JB = box_job(P, pairB, W * R);
-    if (JA.m <= 0) JA.sid = P.drift_sid[0];
-    if (JB.m <= 0) JB.sid = P.drift_sid[0];
+    keep_group(P, JA, pairA);
+    keep_group(P, JB, pairB);
+    if (JA.m <= 0) JA.sid = P.drift[0].sid;
+    if (JB.m <= 0) JB.sid = P.drift[0].sid;
     uint32_t* recA = trace_record(P, T, pairA, JA, W, R);
     uint32_t* recB = trace_record(P, T, pairB, JB, W, R);
     const int stepsA = JA.m > 0 ? JA.m + W - 1 : 0;
@@ -623,8 +625,8 @@ __device__ __forceinline__ void sweep_trace_i16_col(const KParams& P, const Trac
     }
     stA.store_col(bufA, JA, AA, S.colw[JA.sid], 0, l, bad);
     stB.store_col(bufB, JB, AB, S.colw[JB.sid], 0, l, bad);
-    const uint32_t e = (uint32_t)P.drift_e[0];
-    const int period = P.drift_period[0];
+    const uint32_t e = (uint32_t)P.drift[0].e;
+    const int period = P.drift[0].period;
     const uint32_t e2 = __builtin_amdgcn_readfirstlane(e * 0x10001u);
     const uint32_t goA = (uint32_t)S.gap_open[JA.sid], goB = (uint32_t)S.gap_open[JB.sid];
     const u16x2 c2 = pk((goA - e) | ((goB - e) << 16));
@@ -817,7 +819,7 @@ __device__ __forceinline__ void trace_member(const KParams& P, const TraceArgs& 
         atomicOr(&P.flags[kFlagInternal], 1);
         return;
     }
-    const int head = (COL ? kMetaColHeads : kMetaHeads) + bin;
+    const int head = COL ? kMetaColHeads + P.group * kMaxBins + bin : kMetaHeads + bin;
     for (;;) {
         const int it = next_item(&P.meta[head]);
         if (it >= hi - lo) break;
@@ -1066,7 +1068,7 @@ __global__ __launch_bounds__(THREADS) void sw_trace_classify_kernel(KParams P, T
                         // column path only when every scheme of the call has it)
                         const int sid = P.scheme_id ? (int)P.scheme_id[i] : 0;
                         const int col = (T.bins[b].col && sid < SW_MAX_SCHEMES && P.col_ok[sid]) ? 1 : 0;
-                        key[u] = b * kMBuckets + (col ? 0 : kMHalf) + (kMHalf - 1 - m_bucket(cols));
+                        key[u] = pair_key(P, b, col != 0, sid, cols);
                         atomicAdd(&s_cells[b], (unsigned long long)rows * (unsigned long long)cols);
                         atomicAdd(&s_pairs[b], 1u);
                         if (col) atomicAdd(&s_col[b], 1u);
