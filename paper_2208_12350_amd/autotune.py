@@ -293,8 +293,9 @@ def tune_batch(batch, dbatch, device: int = 0, sample: int = 50000, repeats: int
                options: str = ""):
     """The routing a batch is timed with: shape rates measured on the batch's
     dominant scheme at its median reference length, the candidate tables of
-    a seeded sample of its pairs and the built-in routing by the size of the
-    call (an empty table), the fastest of them on the batch itself
+    a seeded sample of its pairs (among them, as "builtin", the one table that
+    the built-in routing starts from) and, as "by size", the built-in routing
+    itself (an empty table), the fastest of them on the batch itself
     (median of `repeats` graph-replayed calls each), then the faster tile
     width for it; the calls are timed with the tuning-string `options`.
     Returns (name, table, candidates, tile)."""

@@ -19,7 +19,10 @@ An *edit* sets one parameter of a configuration of libswalign:
   ``graph``, ``colpath``, ``pairtable``, ``chunk``, ``families``).
 
 A genome is a list of edits, applied in order to the default configuration
-(later edits override earlier ones where they overlap).  A configuration
+(later edits override earlier ones where they overlap).  Without a routing edit
+the library's own routing stands, which depends on the size of a call and the
+score source; a genome that has one installs a table, which starts as the
+library's one-table form.  A configuration
 *fails* when it cannot be built (a shape that does not cover its rows) or
 when its results differ from the default configuration's: every variant must
 reproduce the reference results exactly, as in the paper's validation step.
@@ -75,7 +78,8 @@ def apply_edits(default_route: Sequence[Tuple[int, int]], edits: Sequence[Edit],
 
 
 def tuning_string(route: Sequence[Tuple[int, int]], opts: Dict[str, int]) -> str:
-    """sw_create's tuning string for a configuration."""
+    """sw_create's tuning string for a configuration (no shapes: the library's
+    own routing)."""
     table = []
     for k, (W, R) in enumerate(route):
         hi = BUCKET * (k + 1)
@@ -83,7 +87,7 @@ def tuning_string(route: Sequence[Tuple[int, int]], opts: Dict[str, int]) -> str
             table[-1] = (hi, W, R)
         else:
             table.append((hi, W, R))
-    parts = ["route16=" + "/".join("%dx%d@%d" % (W, R, hi) for hi, W, R in table)]
+    parts = ["route16=" + "/".join("%dx%d@%d" % (W, R, hi) for hi, W, R in table)] if table else []
     parts += ["%s=%d" % (k, v) for k, v in sorted(opts.items())]
     return ";".join(parts)
 
@@ -347,14 +351,21 @@ class LibraryFitness:
 
     DEFAULT_OPTIONS = {"streams": 4, "mode": 1, "graph": 1, "colpath": 1, "pairtable": 1, "chunk": 128, "families": 1}
 
-    def key(self, edits: Sequence[Edit]) -> str:
-        """The configuration an edit list builds, with options at their
-        default values dropped ("fail" for an invalid one)."""
+    def tuning(self, edits: Sequence[Edit]) -> Optional[str]:
+        """The tuning string an edit list builds, with options at their
+        default values dropped, and the library's own routing left alone where
+        the edits do not change it (None for an invalid list)."""
         cfg = apply_edits(self.default_route, edits, self.shapes)
         if cfg is None:
-            return "fail"
+            return None
         route, opts = cfg
-        return tuning_string(route, {k: v for k, v in opts.items() if self.DEFAULT_OPTIONS.get(k) != v})
+        return tuning_string([] if route == self.default_route else route,
+                             {k: v for k, v in opts.items() if self.DEFAULT_OPTIONS.get(k) != v})
+
+    def key(self, edits: Sequence[Edit]) -> str:
+        """The configuration an edit list builds ("fail" for an invalid one)."""
+        t = self.tuning(edits)
+        return "fail" if t is None else t
 
     def noise(self, n: int = 5) -> float:
         """Spread (max - min) / median of n measurements of the default
@@ -363,10 +374,8 @@ class LibraryFitness:
         return (ts[-1] - ts[0]) / ts[len(ts) // 2]
 
     def __call__(self, edits: Sequence[Edit]) -> Optional[float]:
-        cfg = apply_edits(self.default_route, edits, self.shapes)
-        if cfg is None:
-            return None
-        return self._run(tuning_string(*cfg))
+        t = self.tuning(edits)
+        return None if t is None else self._run(t)
 
 
 def main(argv=None):
@@ -402,7 +411,7 @@ def main(argv=None):
            "generations": args.generations, "measurements": ev.calls, "search_s": round(t_search, 1),
            "t_default_ms": ev([]), "t_best_ms": best_ms, "history_ms": history, "noise": round(noise, 4),
            "threshold": round(thr, 4),
-           "best_edits": best, "best_tuning": tuning_string(*apply_edits(fit.default_route, best, fit.shapes)),
+           "best_edits": best, "best_tuning": fit.tuning(best),
            "analysis": {k: v for k, v in rep.items() if k != "savings"},
            "savings": rep["savings"]}
     print(json.dumps(res), flush=True)
