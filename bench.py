@@ -25,17 +25,17 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# Algorithmic integer operations per DP cell: H-o (1), E (2), F (2),
-# diag+s (1), max of four terms with 0 (3), running best / argmax (3).
-OPS_PER_CELL = 12
-# Alignment paths: per cell of a result box, the recurrence without the
-# running best (9) plus the traceback choices it records: H from the
-# diagonal? from F? (2), F opens? (1), E opens? (1).
-PATH_OPS_PER_CELL = 13
-# MI355X: 256 CUs x 64 lanes x 2.4 GHz of 32-bit VALU issue; packed 16-bit
-# instructions carry two operations per lane.
-VALU_INT32_TOPS = 256 * 64 * 2.4e9 / 1e12
-VALU_INT16X2_TOPS = 2 * VALU_INT32_TOPS
+# The sweeps are bound by VALU issue.  Lane-instructions that a cell cannot do
+# without, (forward, reverse), by score source: packed int16 cells share each
+# instruction between two pairs.  Recurrence 6 and score 1 for two drifted cells
+# (8 and 3 with byte tables, which carry no drift), best tracking 1 and 0.3 more
+# a cell (1.5 with byte tables); the pair table's loads cost half an address a row.
+LANE_INSTR = {(16, 0): (7.0, 7.0), (16, 1): (4.0, 3.3), (16, 2): (4.5, 3.8), (16, 3): (4.0, 4.0), (32, 0): (11.0, 11.0)}
+# Alignment paths, per cell of a result box, (precision, column words): the
+# recurrence and the four traceback choices it records.
+PATH_LANE_INSTR = {(16, 1): 9.0, (16, 0): 11.5, (32, 0): 16.0}
+# MI355X: 256 CUs x 64 lanes x 2.4 GHz of VALU issue.
+VALU_TINSTR = 256 * 64 * 2.4e9 / 1e12
 
 
 def log(*a):
@@ -141,8 +141,8 @@ def roofline_leg(args, db, out, tuning, mode, workload, steps):
     shape family, or per bin), serialised on one stream with a HIP event
     pair around each (library option timing=2), and cells per launch from
     the device counters of the bins each launch swept.  The dominant kernel
-    is the launch with the most device time; achieved = 12 * its cells / its
-    average time."""
+    is the launch with the most device time; achieved = the lane-instructions its
+    cells cannot do without (LANE_INSTR) / its average time."""
     from paper_2208_12350_amd.binding import Aligner
     alr = Aligner(0, tuning, mode=mode, graph=0, timing=2)
     per_launch = {}
@@ -167,15 +167,19 @@ def roofline_leg(args, db, out, tuning, mode, workload, steps):
                                                                                       key=lambda kv: kv[1][0])
     launch_ms = dms / dn
     cells_per_launch = dcells / dn
-    peak = VALU_INT16X2_TOPS if dprec == 16 else VALU_INT32_TOPS
-    achieved = OPS_PER_CELL * cells_per_launch / (launch_ms / 1e3) / 1e12
-    # every sweep launch of a step together, each at its own precision's peak
+    instr = lambda k: LANE_INSTR[(k[1], k[4] if k[1] == 16 else 0)][k[0]]
+    per_cell = instr((dpass, dprec, dlanes, None, dcol))
+    peak = VALU_TINSTR
+    achieved = per_cell * cells_per_launch / (launch_ms / 1e3) / 1e12
+    # every sweep launch of a step together
     fam_ms = sum(v[0] for v in per_launch.values()) / roof_steps
-    fam_ops = OPS_PER_CELL * sum(v[1] for v in per_launch.values()) / roof_steps
-    fam_peak_s = sum(OPS_PER_CELL * v[1] / roof_steps / ((VALU_INT16X2_TOPS if k[1] == 16 else VALU_INT32_TOPS) * 1e12)
-                     for k, v in per_launch.items())
+    fam_ops = sum(instr(k) * v[1] for k, v in per_launch.items()) / roof_steps
     direction = "true" if dpass else "false"
-    if dlo:
+    if dlo and (dlanes > 64 or drows == 8 and dlanes == 64 and dlo == 3):
+        # the cooperative family: <reverse, score source, rows largest first>
+        kernel_name = "sw::sw_coop_family_kernel<%s, %d, %s>" % (
+            direction, dcol, ", ".join(str(r) for r in range(drows, dlo - 1, -1)))
+    elif dlo:
         # family kernel: <precision, lanes, reverse, score source, waves per
         # SIMD, reference tile, rows largest first>
         kernel_name = "sw::sw_family_kernel<%d, %d, %s, %d, %d, %d, %s>" % (
@@ -194,12 +198,12 @@ def roofline_leg(args, db, out, tuning, mode, workload, steps):
         kernel_name = "sw::sw_queue_chunk_kernel<%d, %d, %d, %s, %s, %d>" % (
             dprec, dlanes, drows, direction, "true" if dcol else "false", dtile)
     return {"bound": "alu", "achieved": round(achieved, 3), "peak": round(peak, 2),
-            "unit": "Tops/s", "frac": round(achieved / peak, 4),
+            "unit": "T lane-instructions/s", "frac": round(achieved / peak, 4),
             "traffic": stored_traffic(kernel_name, workload, cells_per_launch=cells_per_launch),
             "kernel": kernel_name, "launches": dn, "launch_ms": round(launch_ms, 4),
-            "cells_per_launch": int(cells_per_launch), "ops_per_cell": OPS_PER_CELL,
-            "all_sweeps": {"ms": round(fam_ms, 3), "achieved": round(fam_ops / (fam_ms / 1e3) / 1e12, 3),
-                           "frac": round(fam_peak_s / (fam_ms / 1e3), 4)}}
+            "cells_per_launch": int(cells_per_launch), "lane_instr_per_cell": per_cell,
+            "all_sweeps": {"ms": round(fam_ms, 3), "lane_instr": int(fam_ops), "achieved": round(fam_ops / (fam_ms / 1e3) / 1e12, 3),
+                           "frac": round(fam_ops / (fam_ms / 1e3) / 1e12 / peak, 4)}}
 
 
 def cigar_leg(args, db, out, ref_out, tuning, score_ms, workload):
@@ -207,7 +211,7 @@ def cigar_leg(args, db, out, ref_out, tuning, score_ms, workload):
     GCUPS counts forward cells per second of whole-call wall time, as the
     headline does.  The box sweeps' kernels are then timed per launch (the
     library's timing=2, launches serialised) for their roofline:
-    PATH_OPS_PER_CELL per box cell against the int32 VALU peak."""
+    PATH_LANE_INSTR per box cell against the VALU's issue rate."""
     import numpy as np
     import torch
     from paper_2208_12350_amd.binding import Aligner
@@ -245,8 +249,8 @@ def cigar_leg(args, db, out, ref_out, tuning, score_ms, workload):
                 acc[0] += ms; acc[1] += cells
     alt.close()
     (P_, W_, (R_, lo_), C_), (dms, dcells) = max(per_bin.items(), key=lambda kv: kv[1][0])
-    peak = VALU_INT16X2_TOPS if P_ == 16 else VALU_INT32_TOPS
-    achieved = PATH_OPS_PER_CELL * dcells / (dms / 1e3) / 1e12
+    peak, per_cell = VALU_TINSTR, PATH_LANE_INSTR[(P_, C_)]
+    achieved = per_cell * dcells / (dms / 1e3) / 1e12
     launches = reps * chunks
     if lo_:
         # box-sweep family: <precision, lanes, column words, rows largest first (steps of 4)>
@@ -260,12 +264,12 @@ def cigar_leg(args, db, out, ref_out, tuning, score_ms, workload):
             "box_cells": int(box_cells), "record_gb": round(rec_bytes / 1e9, 3), "chunks": chunks,
             "sweep_ms": round(float(np.mean(sweep_ms)), 3), "walk_ms": round(float(np.mean(walk_ms)), 3),
             "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": round(peak, 2),
-                         "unit": "Tops/s", "frac": round(achieved / peak, 4),
+                         "unit": "T lane-instructions/s", "frac": round(achieved / peak, 4),
                          "traffic": stored_traffic(kernel_name, workload, cells_per_launch=dcells / launches),
                          "kernel": kernel_name, "launches": launches,
                          "launch_ms": round(dms / launches, 4),
                          "cells_per_launch": int(dcells / launches),
-                         "ops_per_cell": PATH_OPS_PER_CELL,
+                         "lane_instr_per_cell": per_cell,
                          "record_bytes_per_cell": 0.5}}
 
 
@@ -732,11 +736,10 @@ def align_leg(args, workload, steps, warmup, with_cigar, with_cpu, full):
 
     ms_per_step = elapsed * 1e3 / steps
     gcups = fwd_cells * steps / elapsed / 1e9
-    # the whole call (planning, both sweeps, launch gaps) against the peak
-    # of the precision its cells ran at
-    peak = VALU_INT16X2_TOPS if i32_pairs == 0 else VALU_INT32_TOPS
-    whole = OPS_PER_CELL * (fwd_cells + rev_cells) / (ms_per_step / 1e3) / 1e12
-    roof["whole_call"] = {"ms": round(ms_per_step, 3), "achieved": round(whole, 3), "frac": round(whole / peak, 4)}
+    # the whole call: planning, both sweeps, launch gaps
+    whole = roof["all_sweeps"]["lane_instr"] / (ms_per_step / 1e3) / 1e12
+    roof["whole_call"] = {"ms": round(ms_per_step, 3), "achieved": round(whole, 3),
+                          "frac": round(whole / VALU_TINSTR, 4)}
     cigar = cigar_leg(args, db, out, ref_out, tuning, ms_per_step, workload) if with_cigar else None
     int16 = i32_pairs < batch.n_pairs
     res = {
