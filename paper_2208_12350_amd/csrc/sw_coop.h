@@ -258,7 +258,7 @@ __device__ __forceinline__ void sweep_coop(const KParams& P, const SchemeLds& S,
             P.out[pair] = res;
         } else if (J[p].fwd_score > 0) {
             if (best[p] != J[p].fwd_score) {
-                if (tid == 0) push_redo(P, pair);
+                if (tid == 0) atomicOr(&P.flags[kFlagReverseMismatch], 1);
             } else {
                 P.out[pair].q_start = J[p].fwd_qe - row[p];
                 P.out[pair].r_start = J[p].fwd_re - col[p];

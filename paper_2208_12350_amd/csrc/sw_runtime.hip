@@ -305,6 +305,7 @@ static void build_bins(sw_handle* h) {
         b.ppw = (uint16_t)pairs_per_item(s.prec, s.W);
         b.col = shape_kernel(s.prec, s.W, s.R, false, kVarCol) != nullptr ? 1 : 0;
         b.ptab = shape_kernel(s.prec, s.W, s.R, false, kVarPtab) != nullptr ? 1 : 0;
+        // (both passes of a pair have the same score source: every int16 shape has all of them)
         h->bins.push_back(b);
     }
 }
@@ -901,8 +902,10 @@ static int enqueue_pass(sw_handle* h, KParams K, const ClassifyArgs& C, const Wo
         }
     }
     // pairs whose drifted forward sweep left the end column open
-    if (pass == 1 && K.redo)
+    for (int g = 0; pass == 1 && (h->n_drift > 0 || K.ptab_sid >= 0) && g < n_groups(h, 1); ++g) {
+        set_group(K, h, g);
         HIP_TRY(h, launch_redo(K, lut, h->d_bins, counters(h->d_small), 2 * std::max(1, h->n_cu), stream));
+    }
     if (timing) HIP_TRY(h, hipEventRecord(h->ev[pass == 0 ? 2 : 4], stream));
     return SW_OK;
 }
@@ -1004,6 +1007,7 @@ sw_handle* sw_create(int device, const char* tuning) {
         default_routing(h, sel);
     }
     rebuild_lut(h);
+    for (const BinInfo& e : h->bins) ok = ok && (e.prec != 16 || (e.col && e.ptab));
     ok = ok && h->bins.size() <= (size_t)kMaxBins &&
          hipMalloc(&h->d_mats, kSchemeBytes) == hipSuccess &&
          hipMalloc(&h->d_lut, kRouteClasses * kLutEntries) == hipSuccess &&

@@ -76,8 +76,6 @@ namespace sw {
 constexpr int kWaveBuf = 2 * 4 * 2 * RefStager<16>::kBuf;
 constexpr int kNoRow = 0x7FFFFFFF;   // no cell found
 
-__device__ __forceinline__ void push_redo(const KParams& P, int pair);
-
 // One sweep (forward, or reverse when REV) of the wave item
 // order[first .. first+count), one pair per W-lane group, int32 arithmetic.
 template <int W, int R, bool REV, int C = kChunk>
@@ -254,9 +252,7 @@ __device__ __forceinline__ u16x2 load_scores(const int8_t* mat, int addrA, int a
 }
 
 // One sweep of the wave item order[first .. first+count), two pairs per
-// W-lane group packed into int16 halves.  A pair whose reverse sweep does not
-// find the forward score (its forward sweep may have been a drifted one, see
-// below) goes to the redo list.
+// W-lane group packed into int16 halves.
 template <int W, int R, bool REV, int C = kChunk>
 __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, uint16_t* wbuf,
                                           int first, int count, int lane) {
@@ -441,7 +437,7 @@ __device__ __forceinline__ void sweep_i16(const KParams& P, const SchemeLds& S, 
                 P.out[pair] = res;
             } else if (J.fwd_score > 0) {
                 if (lb[p] != J.fwd_score) {
-                    push_redo(P, pair);
+                    atomicOr(&P.flags[kFlagReverseMismatch], 1);
                 } else {
                     P.out[pair].q_start = J.fwd_qe - li[p];
                     P.out[pair].r_start = J.fwd_re - lj[p];
@@ -810,13 +806,16 @@ struct CoopX {
     int32_t item;
 };
 
-// One sweep of the wave item order[first .. first+count), two pairs per
-// W-lane group packed into int16 halves, scores from Src.  With COOP the four
-// wavefronts of the workgroup sweep one item as a group of 256 lanes: this
-// wavefront is number `wave` of it (see sw_coop.h), W is 64.
-template <class Src, int W, int R, bool REV, int C, bool COOP = false>
-__device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src::Lds& S, uint16_t* wbuf, int first,
-                                            int count, int lane, CoopX* X = nullptr, int wave = 0) {
+// One sweep of two jobs per W-lane group packed into int16 halves, scores from
+// Src.  Forward, the results of pairs A and B (-1: none) are written; REV looks
+// for the row-major-first cell that holds a job's score (J.fwd_score, 0: none)
+// and calls found(row, col) in every lane, row kNoRow without one.  With COOP
+// the four wavefronts of the workgroup sweep one item as a group of 256 lanes:
+// this wavefront is number `wave` of it (see sw_coop.h), W is 64.
+template <class Src, int W, int R, bool REV, int C, bool COOP, class Found>
+__device__ __forceinline__ void sweep_jobs(const KParams& P, const typename Src::Lds& S, uint16_t* wbuf,
+                                           PairJob JA, PairJob JB, int pairA, int pairB, int lane, CoopX* X, int wave,
+                                           Found&& found) {
     static_assert(!COOP || (W == 64 && C == 128), "a cooperative group is four 64-lane wavefronts");
     using Stager = RefStager<W, C>;
     using Entry = typename Src::Entry;
@@ -824,16 +823,6 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
     const int g = lane / W;
     const int l = lane % W;
     const int lr = COOP ? 64 * wave + l : l;   // lane within the pair's group: rows lr * R ..
-
-    const int slot = g * 2;
-    int pairA = slot < count ? P.order[first + slot] : -1;
-    int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
-    PairJob JA = load_job(P, pairA, REV ? 1 : 0);
-    PairJob JB = load_job(P, pairB, REV ? 1 : 0);
-    if constexpr (Src::kSide == 0) {
-        keep_group(P, JA, pairA);
-        keep_group(P, JB, pairB);
-    }
     Src src;
     src.check(P, JA, pairA);
     src.check(P, JB, pairB);
@@ -1124,20 +1113,7 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
                 for (int w = kWavesPerBlock - 1; w >= 0; --w)
                     if (X->res[w][p][1] != kNoRow) { row[p] = X->res[w][p][1]; col[p] = X->res[w][p][2]; }
         }
-        if (lr == 0) {
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int pair = p == 0 ? pairA : pairB;
-                const PairJob& J = p == 0 ? JA : JB;
-                if (pair < 0 || J.fwd_score <= 0) continue;
-                if (row[p] == kNoRow) {
-                    push_redo(P, pair);
-                } else {
-                    P.out[pair].q_start = J.fwd_qe - row[p];
-                    P.out[pair].r_start = J.fwd_re - col[p];
-                }
-            }
-        }
+        found(row, col);
     } else {
         // per pair: best of this lane, its upper row, and the lane's first
         // column that reaches it; then the group's, upper rows first
@@ -1203,6 +1179,38 @@ __device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src
             }
         }
     }
+}
+
+// The sweep of the wave item order[first .. first+count): its pairs, forward or,
+// REV, back from their ends.
+template <class Src, int W, int R, bool REV, int C, bool COOP = false>
+__device__ __forceinline__ void sweep_drift(const KParams& P, const typename Src::Lds& S, uint16_t* wbuf, int first,
+                                            int count, int lane, CoopX* X = nullptr, int wave = 0) {
+    const int slot = lane / W * 2;
+    int pairA = slot < count ? P.order[first + slot] : -1;
+    int pairB = slot + 1 < count ? P.order[first + slot + 1] : -1;
+    PairJob JA = load_job(P, pairA, REV ? 1 : 0);
+    PairJob JB = load_job(P, pairB, REV ? 1 : 0);
+    if constexpr (Src::kSide == 0) {
+        keep_group(P, JA, pairA);
+        keep_group(P, JB, pairB);
+    }
+    sweep_jobs<Src, W, R, REV, C, COOP>(P, S, wbuf, JA, JB, pairA, pairB, lane, X, wave,
+                                        [&](const int (&row)[2], const int (&col)[2]) {
+        if ((COOP && wave > 0) || lane % W != 0) return;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int pair = p == 0 ? pairA : pairB;
+            const PairJob& J = p == 0 ? JA : JB;
+            if (pair < 0 || J.fwd_score <= 0) continue;
+            if (row[p] == kNoRow) {
+                push_redo(P, pair);
+            } else {
+                P.out[pair].q_start = J.fwd_qe - row[p];
+                P.out[pair].r_start = J.fwd_re - col[p];
+            }
+        }
+    });
 }
 
 }  // namespace sw
