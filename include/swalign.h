@@ -131,13 +131,14 @@ const char* sw_last_error(sw_handle* h);
  *               scores plus gap_open and gap_extend fit a byte) read their
  *               substitution scores from per-column words instead of table
  *               lookups (default 1; 0 = always table lookups).  Gap costs too
- *               large for the drifted sweeps (gap_open + 42 gap_extend >
- *               1024) take table lookups, and a scheme that is the only one
- *               of a call not to share the first such scheme's gap_extend
- *               takes the pair table
+ *               large for the drifted sweeps (gap_open + 26 gap_extend > 1024
+ *               or 5 gap_extend - gap_open > 127; with an installed routing
+ *               table, gap_open + 42 gap_extend > 1024) take table lookups, and
+ *               a scheme that is the only one of a call not to share the first
+ *               such scheme's gap_extend takes the pair table
  *   "pairtable" 1 = when exactly one scheme of a call takes table lookups
  *               (alphabet of at most 24 residues, scores plus gap_open
- *               and gap_extend a byte, gap_open + 42 gap_extend <= 1024),
+ *               and gap_extend a byte, gap costs as for "colpath"),
  *               its packed int16 pairs read two
  *               rows' scores per load from a pair table (default 1);
  *               0 = byte-table lookups.  Read-only "pairtable_used": whether

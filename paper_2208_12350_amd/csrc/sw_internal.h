@@ -214,12 +214,16 @@ constexpr int kLutRows = SW_MAX_QUERY / 16;
 enum : int { kLutI16Col = 0, kLutI32 = 1, kLutI16 = 2, kLutSels = 3 };
 
 // Drifted sweeps: the steps between renormalisations of a scheme with gap
-// costs o and e, or 0 when it cannot take them.  The drift of a period plus
-// a lane's rows, e (R + period + 1), and the values o + e below zero must
-// fit in the bias: o + e (32 + period + 2) <= kI16Bias.
-inline int drift_period(int o, int e) {
+// costs o and e in shapes of up to `rows` rows per lane, or 0 when they cannot
+// take it.  The drift of a period plus a lane's rows, e (R + period + 1), and the
+// values o + e below zero must fit in the bias: o + e (R + period + 2) <=
+// kI16Bias.  The reverse sweep brings rows up to 4 beyond the last to one drift:
+// 4 e - (o - e) must stay within the packed range's 127 spare values.
+constexpr int kDriftRows = 32, kDriftRowsShort = 16;
+inline int drift_period(int o, int e, int rows) {
+    if (5 * (int64_t)e - o > 127) return 0;
     for (int period : {128, 64, 32, 16, 8})
-        if ((int64_t)o + (int64_t)e * (32 + period + 2) <= kI16Bias) return period;
+        if ((int64_t)o + (int64_t)e * (rows + period + 2) <= kI16Bias) return period;
     return 0;
 }
 struct ClassifyArgs {

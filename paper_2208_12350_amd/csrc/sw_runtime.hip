@@ -1422,6 +1422,19 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
         ws.cap = h->cap_pairs;
     }
 
+    // Renormalisation periods of the schemes.  Gap costs too large for 32 rows
+    // per lane may do for 16, all that the built-in routing of calls of up to
+    // 262144 pairs uses: such a call, if larger, takes that routing as well
+    // (100,000 DNA pairs with o = e = 30 took 2.70 ms on byte tables, 1.92 drifted).
+    int period[SW_MAX_SCHEMES] = {0};
+    bool tall_ok[SW_MAX_SCHEMES] = {false};   // 32 rows per lane: every shape, and the path sweeps
+    for (int s = 0; s < n_schemes; ++s) {
+        const int o = schemes[s].gap_open, e = schemes[s].gap_extend;
+        period[s] = drift_period(o, e, kDriftRows);
+        tall_ok[s] = period[s] > 0;
+        if (!tall_ok[s] && h->builtin16) period[s] = drift_period(o, e, kDriftRowsShort);
+    }
+
     // substitution tables: [s][b][a] = M_s[a][b]; padding rows/columns score -1
     ClassifyArgs C;
     h->tables.assign(kSchemeBytes, 0);
@@ -1444,8 +1457,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
         // the alphabet)
         uint32_t* cw = reinterpret_cast<uint32_t*>(h->tables.data() + SW_MAX_SCHEMES * kMatBytes) + s * kMatDim;
         const int lift = s < n_schemes ? schemes[s].gap_open + schemes[s].gap_extend : 0;
-        bool ok = s < n_schemes && schemes[s].alphabet <= 4 &&
-                  drift_period(schemes[s].gap_open, schemes[s].gap_extend) > 0;
+        bool ok = s < n_schemes && schemes[s].alphabet <= 4 && period[s] > 0;
         for (int b = 0; b < kMatDim; ++b) {
             uint32_t w = 0;
             for (int a = 0; ok && a < 4; ++a) {
@@ -1493,7 +1505,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
             if (!C.col_ok[sidx]) { ++n_table; cand = sidx; }
         if (n_table == 1) {
             const sw_scheme& sc = schemes[cand];
-            bool ok = sc.alphabet + 1 <= kPtabMaxDim && drift_period(sc.gap_open, sc.gap_extend) > 0;
+            bool ok = sc.alphabet + 1 <= kPtabMaxDim && period[cand] > 0;
             for (int k2 = 0; ok && k2 < sc.alphabet * sc.alphabet; ++k2) {
                 const int v = sc.matrix[k2] + sc.gap_open + sc.gap_extend;
                 ok = v >= 0 && v <= 255;
@@ -1537,7 +1549,7 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     for (int s = 0; s < n_schemes; ++s) {
         if (!C.col_ok[s] && s != ptab_sid) continue;
         const sw_scheme& sc = schemes[s];
-        const DriftGroup own{s, sc.gap_extend, drift_period(sc.gap_open, sc.gap_extend), sc.gap_open - sc.gap_extend};
+        const DriftGroup own{s, sc.gap_extend, period[s], sc.gap_open - sc.gap_extend};
         if (s == ptab_sid) {
             K.drift[1] = own;
             continue;
@@ -1561,10 +1573,12 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
         K.gap_extend[s] = v ? schemes[s].gap_extend : 0;
         K.max_score[s] = C.max_score[s];
         K.col_ok[s] = C.col_ok[s];
-        h->last_col_ok[s] = K.col_ok[s];
+        h->last_col_ok[s] = K.col_ok[s] && tall_ok[s];
     }
 
-    const int cls = h->pin_class >= 0 ? h->pin_class : route_class(P);
+    int cls = h->pin_class >= 0 ? h->pin_class : route_class(P);
+    for (int s = 0; s < n_schemes; ++s)
+        if ((C.col_ok[s] || s == ptab_sid) && !tall_ok[s]) cls = std::min(cls, kRouteClasses - 2);
     const bool use_graph = h->opt_mode == 1 && h->opt_graph != 0 && !timing && !no_alloc;
     GraphKey key;
     memset(&key, 0, sizeof(key));
