@@ -225,7 +225,7 @@ int sw_poll(sw_handle* h, uint64_t ticket, int wait);
  * serving loop, harnesses that forbid hipMalloc): the same call as
  * sw_align_batch, with the same arguments, results and errors, except that
  * it allocates and frees nothing.  Its planning workspace (sort keys, pair
- * order and work items; 16 bytes per pair) is one static device array of
+ * order and work items; 20 bytes per pair) is one static device array of
  * 20 MiB that each GPU the library runs on holds until the process ends;
  * the handle (created beforehand with sw_create, which does allocate) gives
  * everything else.  The call never captures or replays a graph; its kernels

@@ -306,10 +306,10 @@ struct CoopWork {
     }
     __device__ __forceinline__ int32_t& item() { return X.item; }
     template <int R, bool REV>
-    __device__ __forceinline__ void sweep(const KParams& P, int first, int count, int tid, int wave) {
+    __device__ __forceinline__ void sweep(const KParams& P, int first, int count, int, int wave) {
         using S = typename std::conditional<VAR == kVarPtab, PtabScores<64, R, kChunk>, ColScores<64, R, kChunk>>::type;
         sweep_drift<S, 64, R, REV, kChunk, true>(P, L, reinterpret_cast<uint16_t*>(wbufs[wave]), first, count,
-                                                 opaque_lane(tid & 63), &X, wave);
+                                                 item_lane(), &X, wave);
     }
 };
 template <int RMAX>
@@ -319,8 +319,8 @@ struct CoopWork<kVarTable, RMAX> {
     __device__ __forceinline__ void load(const KParams& P, int tid) { load_schemes(L, P, tid); }
     __device__ __forceinline__ int32_t& item() { return C.item; }
     template <int R, bool REV>
-    __device__ __forceinline__ void sweep(const KParams& P, int first, int count, int tid, int) {
-        sweep_coop<R, REV>(P, L, C, first, count, tid);
+    __device__ __forceinline__ void sweep(const KParams& P, int first, int count, int, int wave) {
+        sweep_coop<R, REV>(P, L, C, first, count, 64 * wave + item_lane());
     }
 };
 

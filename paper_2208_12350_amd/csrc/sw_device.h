@@ -150,21 +150,31 @@ __device__ __forceinline__ int pair_key(const KParams& P, int bin, bool col, int
 }
 
 // Sets an error flag from any lanes (a plain store: every writer stores 1).
-// No lane-divergent branch: see opaque_lane.
+// No lane-divergent branch: see item_lane.
 __device__ __forceinline__ void set_flag(int32_t* flags, int which, bool raise) {
     if (__builtin_amdgcn_ballot_w64(raise) != 0)
         __hip_atomic_store(&flags[which], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The lane index as a value the compiler cannot carry over from one work item
-// to the next.  Everything a sweep derives from it is then computed per item:
-// kept across items those values fill registers that the sweep needs, and
-// this compiler has moved such values between registers inside a
-// lane-divergent branch, where the lanes outside it lose them.  For the same
-// reason the sweeps keep lane-divergent branches out of their code where
-// registers are short.
-__device__ __forceinline__ int opaque_lane(int lane) {
-    asm volatile("" : "+v"(lane));
+// The lane index, taken from the hardware for each work item.  What must hold for
+// the sweeps: this compiler has moved a register that stays live around a
+// lane-divergent branch to another one inside the branch, where the lanes outside
+// it keep their old contents, once registers were short.  So
+//   * nothing is held per lane from one item to the next: the lane index and all
+//     that is derived from it are made anew for every item (kept across items
+//     they also fill registers that the sweep needs);
+//   * within an item lane-divergent branches come only before its sweep (an
+//     item's jobs: load_job, keep_group, box_job, trace_record), when only they and
+//     the lane are live, and after it (results, push_redo), when only what they
+//     write is; between, flags are raised by set_flag and residues are checked
+//     without branches, and the rare branches of a sweep are taken by whole
+//     wavefronts, on ballots.
+__device__ __forceinline__ int item_lane() {
+    int lane;
+    asm volatile(
+        "v_mbcnt_lo_u32_b32 %0, -1, 0\n\t"
+        "v_mbcnt_hi_u32_b32 %0, -1, %0"
+        : "=&v"(lane));
     return lane;
 }
 
@@ -269,7 +279,7 @@ struct RefStager {
             buf[l + k * W] = (uint16_t)(row_bytes * b);
         }
     }
-    // Small-alphabet path: write the chunk as column words (bytes M[a][b] + o
+    // Small-alphabet path: write the chunk as column words (bytes M[a][b] + o + e
     // for a = 0..3); out-of-range columns and invalid residues get word 0
     // (the word of residue kPad, which no small alphabet holds).
     __device__ __forceinline__ void store_col(uint32_t* buf, const PairJob& J, int A, const uint32_t* colw,

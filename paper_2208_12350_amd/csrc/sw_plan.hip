@@ -167,9 +167,8 @@ __device__ __forceinline__ int32_t wave_scan(int32_t v, int lane) {
 
 // Plan of a pass from the classified pairs' histogram, whose last entries
 // are every bin's pairs and column-path pairs.  Workgroup b < kMaxBins scans
-// bin b's kMBuckets entries in place, offset by the pairs of bins 0..b-1 (a
-// bin without pairs is left as it is: no key of it occurs); workgroup
-// kMaxBins writes the metadata.  The column-path pairs (the first half of a
+// bin b's kMBuckets entries in place, offset by the pairs of bins 0..b-1;
+// workgroup kMaxBins writes the metadata.  The column-path pairs (the first half of a
 // bin's keys) and the others are cut into items separately, so no item mixes
 // the two.  Bound by the latency of its loads: the ranges of all bins come
 // from one scan over the lanes (21 us with a loop over the bins, now 6).

@@ -38,7 +38,7 @@ __device__ __forceinline__ void queue_loop(const KParams& P, int lane, int lo, i
         const bool valid = first >= 0 && count >= 1 && count <= kPPW && first + count <= n_pairs;
         if (valid) {
             wave_lds_sync();
-            sweep(first, count, opaque_lane(lane));
+            sweep(first, count, item_lane());
         } else {
             atomicOr(&P.flags[kFlagInternal], 1);
         }

@@ -85,8 +85,9 @@ __device__ __forceinline__ PairJob start_job(const KParams& P, const Listed& x) 
     return J;
 }
 
-// Redo of two pairs.  search(J, row, col) finds the cells of their jobs; max_rows is the most rows it can take, and the thread with `writes`
-// set writes.
+// Redo of two pairs.  search(J, row, col) finds the cells of their jobs;
+// max_rows is the most rows it can take, and the first lane of the wavefront
+// with `writes` set writes.
 template <class Search>
 __device__ __forceinline__ void redo_pairs(const KParams& P, int pairA, int pairB, int max_rows, bool writes,
                                            const int8_t* lut, const BinInfo* bins, unsigned long long* counters,
@@ -126,7 +127,7 @@ __device__ __forceinline__ void redo_pairs(const KParams& P, int pairA, int pair
                 x[p].re = J[p].fwd_re + col[p];
                 continue;
             }
-            if (writes) {
+            if (writes && item_lane() == 0) {
                 sw_result* o = P.out + x[p].pair;
                 o->q_start = x[p].qe - row[p];
                 o->r_start = x[p].re - col[p];
@@ -169,13 +170,13 @@ template <int VAR, int R, bool COOP>
 __device__ __forceinline__ void redo(const KParams& P, CoopWork<VAR, 8>& K, int idA, int idB, int tid, int wave,
                                      const int8_t* lut, const BinInfo* bins, unsigned long long* counters) {
     using Src = typename std::conditional<VAR == kVarPtab, PtabScores<64, R, kChunk>, ColScores<64, R, kChunk>>::type;
-    redo_pairs(P, idA, idB, (COOP ? kCoopW : 64) * R, COOP ? tid == 0 : (tid & 63) == 0, lut, bins, counters,
+    redo_pairs(P, idA, idB, (COOP ? kCoopW : 64) * R, !COOP || wave == 0, lut, bins, counters,
                [&](const PairJob (&J)[2], int (&row)[2], int (&col)[2]) {
         if (COOP) __syncthreads();   // the last search's LDS is free
         else wave_lds_sync();
         sweep_jobs<Src, 64, R, true, kChunk, COOP>(
             P, K.L, reinterpret_cast<uint16_t*>(K.wbufs[wave]), J[0], J[1], J[0].fwd_score > 0 ? idA : -1,
-            J[1].fwd_score > 0 ? idB : -1, opaque_lane(tid & 63), &K.X, wave,
+            J[1].fwd_score > 0 ? idB : -1, item_lane(), &K.X, wave,
             [&](const int (&r)[2], const int (&c)[2]) {
                 row[0] = r[0]; row[1] = r[1];
                 col[0] = c[0]; col[1] = c[1];

@@ -636,11 +636,12 @@ struct PtabScores {
     __device__ __forceinline__ void check(const KParams& P, PairJob& J, int pair) const {
         // every pair of a pair-table item uses the table's scheme; anything
         // else is an internal error, swept as an empty pair
-        if (pair < 0) J.sid = P.ptab_sid;
-        if (pair >= 0 && J.sid != P.ptab_sid) {
-            atomicOr(&P.flags[kFlagInternal], 1);
-            J.n = J.m = 0; J.fwd_score = 0; J.sid = P.ptab_sid;
-        }
+        const bool other = pair >= 0 && J.sid != P.ptab_sid;
+        set_flag(P.flags, kFlagInternal, other);
+        J.n = other ? 0 : J.n;
+        J.m = other ? 0 : J.m;
+        J.fwd_score = other ? 0 : J.fwd_score;
+        J.sid = P.ptab_sid;
     }
     __device__ __forceinline__ void rows(const KParams& P, const Lds& S, const PairJob& JA, const PairJob& JB, int l,
                                          int& bad) {
@@ -746,11 +747,11 @@ struct QprofScores {
 
     __device__ __forceinline__ void check(const KParams& P, PairJob& J, int pair) const {
         // every pair aligns the profiled query with the profile's scheme
-        if (pair < 0) J.sid = P.ptab_sid;
-        if (pair >= 0 && (J.sid != P.ptab_sid || J.n != P.qprof_n)) {
-            atomicOr(&P.flags[kFlagInternal], 1);
-            J.n = J.m = 0; J.sid = P.ptab_sid;
-        }
+        const bool other = pair >= 0 && (J.sid != P.ptab_sid || J.n != P.qprof_n);
+        set_flag(P.flags, kFlagInternal, other);
+        J.n = other ? 0 : J.n;
+        J.m = other ? 0 : J.m;
+        J.sid = P.ptab_sid;
     }
     __device__ __forceinline__ void rows(const KParams&, const Lds& S, const PairJob&, const PairJob&, int l, int&) {
         lprof = S.prof + l * RD * 4;

@@ -789,11 +789,11 @@ __global__ __launch_bounds__(kBlock) void sw_trace_kernel(KParams P, TraceArgs T
         if (valid) {
             wave_lds_sync();
             if constexpr (PREC == 16 && COL)
-                sweep_trace_i16_col<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, opaque_lane(lane));
+                sweep_trace_i16_col<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, item_lane());
             else if constexpr (PREC == 16)
-                sweep_trace_i16<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, opaque_lane(lane));
+                sweep_trace_i16<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, item_lane());
             else
-                sweep_trace<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, opaque_lane(lane));
+                sweep_trace<W, R>(P, T, L, wbuf, stages + wave * kStageDwords, first, count, item_lane());
         } else {
             atomicOr(&P.flags[kFlagInternal], 1);
         }
@@ -830,11 +830,11 @@ __device__ __forceinline__ void trace_member(const KParams& P, const TraceArgs& 
         if (valid) {
             wave_lds_sync();
             if constexpr (PREC == 16 && COL)
-                sweep_trace_i16_col<W, R>(P, T, L, wbuf, stage, first, count, opaque_lane(lane));
+                sweep_trace_i16_col<W, R>(P, T, L, wbuf, stage, first, count, item_lane());
             else if constexpr (PREC == 16)
-                sweep_trace_i16<W, R>(P, T, L, wbuf, stage, first, count, opaque_lane(lane));
+                sweep_trace_i16<W, R>(P, T, L, wbuf, stage, first, count, item_lane());
             else
-                sweep_trace<W, R>(P, T, L, wbuf, stage, first, count, opaque_lane(lane));
+                sweep_trace<W, R>(P, T, L, wbuf, stage, first, count, item_lane());
         } else {
             atomicOr(&P.flags[kFlagInternal], 1);
         }
