@@ -348,9 +348,10 @@ int sw_shapes(sw_handle* h, int32_t* precision, int32_t* lanes, int32_t* rows, i
  * shape (lanes[k], rows[k]).  rows_max must increase in steps that are
  * multiples of 16 and end at SW_MAX_QUERY; each shape must be compiled and
  * cover its rows (lanes * rows >= rows_max).  n == 0 restores the built-in
- * routing.  An installed table is used for calls of every size; the built-in
- * int16 routing also depends on the pairs of a call (up to 4096, 8192, 262144
- * or more).  HOST arrays; SW_EINVAL on a malformed table (the routing is then
+ * routing.  An installed table is used for calls of every size and all
+ * schemes; the built-in int16 routing also depends on the pairs of a call (up to
+ * 4096, 8192, 262144 or more) and, above 512 residues, on whether a pair's
+ * scheme takes column words and on how many such queries a pass has.  HOST arrays; SW_EINVAL on a malformed table (the routing is then
  * unchanged).  Results never depend on the routing, only speed does. */
 int sw_set_routing(sw_handle* h, int precision, const int32_t* rows_max, const int32_t* lanes, const int32_t* rows,
                    int n);
