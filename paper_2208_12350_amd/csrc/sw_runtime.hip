@@ -1579,6 +1579,15 @@ static int submit_spans(sw_handle* h, const uint8_t* queries, const int64_t* q_b
     int cls = h->pin_class >= 0 ? h->pin_class : route_class(P);
     for (int s = 0; s < n_schemes; ++s)
         if ((C.col_ok[s] || s == ptab_sid) && !tall_ok[s]) cls = std::min(cls, kRouteClasses - 2);
+    // A search of a long query fills the device with 64-lane groups later than a
+    // batch: its references are short and unlike the query, so its reverse boxes
+    // are small.  ms in 64 lanes against cooperative groups, references of
+    // 200..1000: protein query of 1000 residues, 4500 references 2.31 and 1.72, 6000
+    // 2.43 and 2.17, 8000 2.51 and 2.96; DNA query of 700, 4500 references 1.55 and
+    // 1.17, 6000 1.61 and 1.65.  The lower limit is for queries whose forward sweeps
+    // move as well; at 850 rows only the reverse ones do: 6000 references 1.95 and 1.72.
+    const bool col_moves = C.col_ok[0] && search_n <= most_rows64(1, true);
+    if (search_n > 512 && h->pin_class < 0 && cls == 1 && P <= (col_moves ? 5120 : 6144)) cls = 0;
     const bool use_graph = h->opt_mode == 1 && h->opt_graph != 0 && !timing && !no_alloc;
     GraphKey key;
     memset(&key, 0, sizeof(key));

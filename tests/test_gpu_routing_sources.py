@@ -53,3 +53,25 @@ def test_shape_of_each_source(n, rows, column, other):
         assert _lanes(al, True, 512, 2048) == _lanes(al, False, 512, 2048) == {64}
     finally:
         al.close()
+
+
+@pytest.mark.parametrize("n,lanes", [(4096, {256}), (6144, {256}), (6145, {64})])
+def test_search_of_a_long_query(n, lanes):
+    """Searches keep to cooperative groups for longer than batches."""
+    import torch
+    from paper_2208_12350_amd.binding import Aligner
+    rng = np.random.default_rng(n)
+    sc = W.protein_scheme(5)
+    query = rng.integers(0, 20, 1000).astype(np.uint8)
+    off = np.concatenate([[0], np.cumsum(rng.integers(1, 30, n))]).astype(np.int64)
+    refs = rng.integers(0, 20, off[-1]).astype(np.uint8)
+    al = Aligner(0)
+    try:
+        got = al.search(torch.from_numpy(query).cuda(), torch.from_numpy(refs).cuda(), torch.from_numpy(off).cuda(),
+                        sc).cpu().numpy()
+        assert _lanes(al, False, 512, 1024) == lanes
+    finally:
+        al.close()
+    idx = np.arange(0, n, 11)
+    o = O.align_batch(W.SearchSet(query, refs, off, sc).as_batch(), index=idx)
+    assert np.array_equal(got[idx], np.stack([o[f] for f in FIELDS], axis=1))
